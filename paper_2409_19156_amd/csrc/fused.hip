@@ -1,0 +1,507 @@
+// FP64 Zernike series without a stored basis: the recurrence runs inside the
+// contraction, and its values go from the lane that forms them straight into
+// an FP64 MFMA operand (forward and forward-mode derivative).
+//
+// MFMA 16x16x4 (FP64): lane l = x + 16 y (x < 16, y < 4) supplies A[x][y] and
+// B[y][x] and receives D[y + 4 t][x], t = 0..3.
+//
+// Forward (fwd_kernel): D = points x sets.  Lane (x, y) walks chain y of a
+// quad at point x, so at every degree its value is A[x][y] with the
+// contraction index running over the quad's four chains; the cos and the sin
+// columns of a degree are two contraction steps over one recurrence value
+// times two angular factors.  B is the four coefficient rows.
+//
+// Arithmetic of the walk: as the basis kernel (chain_kernel.hip).
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+
+#include "series.hpp"
+
+namespace zp {
+namespace {
+
+typedef double d2 __attribute__((ext_vector_type(2)));
+typedef double d4 __attribute__((ext_vector_type(4)));
+
+constexpr int kThreads = 256; // kSlices waves
+static_assert(kThreads == 64 * kSlices, "one wave per slice");
+
+// x^e for e >= 0 by binary powewin.
+__device__ __forceinline__ double ipow(double x, int e)
+{
+    double acc = 1.0;
+    while (e) {
+        if (e & 1) acc *= x;
+        x *= x;
+        e >>= 1;
+    }
+    return acc;
+}
+
+// Anchor, s(r) and ds/dr of a point (zp_internal.hpp).
+struct Anchor {
+    double s, s1;
+    bool high;
+    __device__ __forceinline__ explicit Anchor(double r)
+    {
+        const double r2 = r * r;
+        high = !(r2 < 0.5);
+        s = high ? __builtin_fma(-2.0 * r, r, 2.0) : 2.0 * r2;
+        s1 = high ? -4.0 * r : 4.0 * r;
+    }
+    __device__ __forceinline__ Anchor() {}
+};
+
+// cos and sin of alpha theta for many alpha at one theta.  theta in quarter
+// turns, theta 2/pi, is kept as an unevaluated sum hi + lo, formed once per
+// point; alpha (hi + lo) less its nearest integer is then good to rounding
+// (the product alpha hi is exact inside the fused multiply-add), and the
+// Taylor polynomials of sin (to x^15) and cos (to x^16) on [-pi/4, pi/4] are
+// within a rounding of the functions.  About 40 instructions, where a general
+// sincos takes about 150.  Whole turns are taken off first, so that any finite
+// theta gives values in range; the sum carries 106 bits, so the angle is good
+// to rounding for |theta| up to about 2^50 / alpha.
+struct Turn {
+    double hi, lo;
+    __device__ __forceinline__ explicit Turn(double theta)
+    {
+        constexpr double k2pi_hi = 0x1.45f306dc9c883p-1, k2pi_lo = -0x1.6b01ec5417056p-55; // 2/pi
+        const double h = theta * k2pi_hi;
+        const double l = __builtin_fma(theta, k2pi_lo, __builtin_fma(theta, k2pi_hi, -h));
+        const double h4 = __builtin_fma(-4.0, __builtin_rint(0.25 * h), h);
+        const double l4 = __builtin_fma(-4.0, __builtin_rint(0.25 * l), l);
+        hi = h4 + l4;
+        lo = l4 - (hi - h4);
+    }
+    __device__ __forceinline__ Turn() {}
+    __device__ __forceinline__ void angle(double fa, double &cs, double &sn) const
+    {
+        const double n = __builtin_rint(fa * hi);
+        const double f = __builtin_fma(fa, lo, __builtin_fma(fa, hi, -n));
+        constexpr double pio2_hi = 0x1.921fb54442d18p+0, pio2_lo = 0x1.1a62633145c07p-54; // pi/2
+        const double x = __builtin_fma(f, pio2_hi, f * pio2_lo);
+        const double z = x * x;
+        double ps = -1.0 / 1307674368000.0, pc = 1.0 / 20922789888000.0; // 1/15!, 1/16!
+        ps = __builtin_fma(ps, z, 1.0 / 6227020800.0);
+        pc = __builtin_fma(pc, z, -1.0 / 87178291200.0);
+        ps = __builtin_fma(ps, z, -1.0 / 39916800.0);
+        pc = __builtin_fma(pc, z, 1.0 / 479001600.0);
+        ps = __builtin_fma(ps, z, 1.0 / 362880.0);
+        pc = __builtin_fma(pc, z, -1.0 / 3628800.0);
+        ps = __builtin_fma(ps, z, -1.0 / 5040.0);
+        pc = __builtin_fma(pc, z, 1.0 / 40320.0);
+        ps = __builtin_fma(ps, z, 1.0 / 120.0);
+        pc = __builtin_fma(pc, z, -1.0 / 720.0);
+        ps = __builtin_fma(ps, z, -1.0 / 6.0);
+        pc = __builtin_fma(pc, z, 1.0 / 24.0);
+        const double s = __builtin_fma(x * z, ps, x);
+        const double c = __builtin_fma(z, __builtin_fma(pc, z, -0.5), 1.0);
+        const int q = (int)n;
+        const double a = q & 1 ? c : s, b = q & 1 ? s : c;
+        sn = q & 2 ? -a : a;
+        cs = (q + 1) & 2 ? -b : b;
+    }
+};
+
+// The recurrence of one (chain, point): v^(i) and d^(i), i <= J, and the
+// factor a (QuadStep) of the current degree times v.
+template <int J> struct Walk {
+    double v[J + 1], d[J + 1], a;
+    __device__ __forceinline__ void start()
+    {
+#pragma unroll
+        for (int i = 0; i <= J; ++i) {
+            v[i] = i == 0 ? 1.0 : 0.0;
+            d[i] = 0.0;
+        }
+        a = 1.0;
+    }
+    __device__ __forceinline__ void step(double cc, double bs, double s)
+    {
+#pragma unroll
+        for (int i = J; i >= 1; --i)
+            d[i] = __builtin_fma(cc, d[i], -bs * __builtin_fma(s, v[i], (double)i * v[i - 1]));
+        d[0] = __builtin_fma(cc, d[0], -bs * (s * v[0]));
+#pragma unroll
+        for (int i = 0; i <= J; ++i) v[i] += d[i];
+    }
+};
+
+typedef int i2 __attribute__((ext_vector_type(2)));
+
+// Orders a wave's own LDS writes before its reads (and the other way round);
+// the hardware does, this keeps the compiler to it.
+__device__ __forceinline__ void wave_lds_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// A wave's window of kWindow rows of its quad's recurrence steps in LDS.  The
+// steps come from LDS so that a step is never waited for behind the
+// coefficient loads in flight (loads from memory return in order); the next
+// step's record is read a step ahead, each point's lane reading its own
+// anchor's half (no selects).
+constexpr int kWindow = kStepTail;
+template <int N> struct StepWindow {
+    QuadStep *lds; // [kWindow][4][2]
+    const QuadStep *rows;
+    int lane, off[N]; // off: place of (chain, anchor) of each point within a row
+    int K;
+    double cc[N], bs[N], fa[N]; // step K + 1
+    d2 pre[kWindow * 16 / 64];
+    // Rows 0 .. kWindow - 1 on their way (fetch), then in place (start).
+    __device__ __forceinline__ void fetch(const QuadStep *from)
+    {
+#pragma unroll
+        for (int k = 0; k < kWindow * 16 / 64; ++k) pre[k] = ((const d2 *)from + lane)[64 * k];
+    }
+    __device__ __forceinline__ void place()
+    {
+        wave_lds_order();
+#pragma unroll
+        for (int k = 0; k < kWindow * 16 / 64; ++k) ((d2 *)lds + lane)[64 * k] = pre[k];
+        wave_lds_order();
+    }
+    __device__ __forceinline__ void read()
+    {
+        const QuadStep *row = lds + 8 * ((K + 1) & (kWindow - 1));
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const d2 c = *(const d2 *)&row[off[i]];
+            cc[i] = c[0];
+            bs[i] = c[1];
+            fa[i] = row[off[i]].a;
+        }
+    }
+    __device__ __forceinline__ void start()
+    {
+        place();
+        K = 0;
+        read();
+    }
+    template <int J> __device__ __forceinline__ void advance(Walk<J> (&w)[N], const Anchor (&an)[N])
+    {
+        ++K;
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            w[i].step(cc[i], bs[i], an[i].s);
+            w[i].a = fa[i];
+        }
+        if (((K + 1) & (kWindow - 1)) == 0) { // the window moves on
+            fetch(rows + 8 * (K + 1));
+            place();
+        }
+        read();
+    }
+};
+
+// r^e for the four chains of a quad: the power of the smallest alpha is the
+// same for every lane, and where the others are within three of it the rest
+// is a product of r and r^2 chosen by the lane.
+__device__ __forceinline__ double quad_pow(double r, double r2, int e, int e_min, int spread)
+{
+    if (spread > 3) return ipow(r, e);
+    const int k = e - e_min;
+    double w = ipow(r, __builtin_amdgcn_readfirstlane(e_min));
+    w = k & 1 ? w * r : w;
+    return k & 2 ? w * r2 : w;
+}
+
+// Logical workgroup number: consecutive ones run on one XCD (workgroups are
+// dealt round-robin to the 8 XCDs, each with its own L2).
+__device__ __forceinline__ int64_t xcd_order(int64_t id, int64_t total)
+{
+    const int64_t t8 = total / 8 * 8;
+    return id < t8 ? (id % 8) * (t8 / 8) + id / 8 : id;
+}
+
+// ---------------------------------------------------------------- forward --
+
+struct FwdArgs {
+    const Quad *quads;
+    const QuadStep *steps;
+    const int32_t *hdr, *cols, *slice;
+    const double *r, *th;
+    int64_t P;
+    const double *c;  // Z's coefficients (DIR: may be null)
+    const double *c2; // DIR: the directional derivative's coefficients
+    const double *tr, *tt;
+    uint32_t B;
+    double *f;
+    int64_t npb; // point blocks
+};
+
+// FM x FN output tiles of 16 points x 16 sets per wave; a workgroup's four
+// waves take the plan's four slices of the modes for the same tiles and add
+// their sums through LDS.
+//
+// What bounds it: on gfx950 FP64 MFMAs and vector instructions do not overlap
+// (counters of the n <= 64 forward add up to MFMA cycles + 4 cycles per vector
+// instruction within 7% of the elapsed cycles), so the split takes vector
+// instructions out: the recurrence runs once per point and chain for both
+// angular factors and all sets of the tile, table values come from LDS in the
+// lane that needs them, angles by Turn.  Two waves per SIMD (at most 256
+// registers, accumulators in vector registers: a build that kept them in
+// accumulation registers moved them at every step).  Measured, n <= 64, 65536
+// points: 1 set 130 us where the basis + GEMM took 745 (the basis alone writes
+// 1.1 GB), 64 sets 376 us (47.9 TFLOP/s) from 755; n <= 20, 5000 points, 8
+// sets 54 -> under 15 us a call.
+template <int FM, int FN, bool DIR>
+__global__ __launch_bounds__(kThreads, 2) void fwd_kernel(FwdArgs g)
+{
+    constexpr int J = DIR ? 1 : 0;
+    __shared__ double red[kSlices][FN * 256];
+    __shared__ QuadStep windows[kSlices][8 * kWindow];
+    const int lane = threadIdx.x & 63, x = lane & 15, y = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int64_t lid = xcd_order(blockIdx.x, gridDim.x);
+    const int64_t pb = lid % g.npb;
+    const uint32_t b0 = (uint32_t)(lid / g.npb) * (16 * FN);
+    const int64_t p0 = pb * (16 * FM);
+
+    d4 acc[FM][FN];
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int n = 0; n < FN; ++n) acc[i][n] = d4{0, 0, 0, 0};
+
+    const int q0 = g.slice[wave], q1 = g.slice[wave + 1];
+    if (q0 < q1) {
+        double rr[FM], r2[FM], tr[DIR ? FM : 1], tt[DIR ? FM : 1];
+        Turn th[FM];
+        Anchor an[FM];
+        StepWindow<FM> win;
+        win.lds = windows[wave];
+        win.lane = lane;
+#pragma unroll
+        for (int i = 0; i < FM; ++i) {
+            const int64_t p = p0 + 16 * i + x;
+            const int64_t pl = p < g.P ? p : g.P - 1; // lanes past the end repeat the last point
+            rr[i] = g.r[pl];
+            r2[i] = rr[i] * rr[i];
+            th[i] = Turn(g.th[pl]);
+            an[i] = Anchor(rr[i]);
+            win.off[i] = 2 * y + an[i].high;
+            if constexpr (DIR) {
+                tr[i] = g.tr ? g.tr[pl] : 0.0;
+                tt[i] = g.tt ? g.tt[pl] : 0.0;
+            }
+        }
+        const bool with_c = !DIR || g.c != nullptr;
+        // byte offsets of this lane's sets in a row; sets past the end repeat
+        // the last one (their sums are not stored)
+        uint32_t bo[FN];
+#pragma unroll
+        for (int n = 0; n < FN; ++n) bo[n] = 8 * (b0 + 16 * n + x < g.B ? b0 + 16 * n + x : g.B - 1);
+        // Groups of two entries, four contraction steps: coefficients are
+        // fetched a group ahead of their use, their row numbers two.  The
+        // fetched values are first touched by take(), a group later, so that
+        // nothing waits for them in between.
+        uint32_t col[4];
+        auto load_cols = [&](int e) {
+            const int32_t *c = g.cols + 8 * (int64_t)e + y;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) col[j] = (uint32_t)c[4 * j];
+        };
+        auto load_c = [&](const double *c, double (&dst)[4][FN]) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t row = __umul24(col[j], 8 * g.B);
+#pragma unroll
+                for (int n = 0; n < FN; ++n) dst[j][n] = *(const double *)((const char *)c + (row + bo[n]));
+            }
+        };
+        // zero where a degree has no such column on this lane's chain
+        auto take = [&](const i2 h, const double (&src)[4][FN], double (&dst)[4][FN]) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int n = 0; n < FN; ++n) dst[j][n] = src[j][n];
+            if (((h[0] >> 16) & (h[1] >> 16)) != 255) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const bool has = (h[j >> 1] >> (16 + 4 * (j & 1) + y)) & 1;
+#pragma unroll
+                    for (int n = 0; n < FN; ++n) dst[j][n] = has ? dst[j][n] : 0.0;
+                }
+            }
+        };
+        int e = g.quads[q0].entry_off;
+        double cur[4][FN], nxt[4][FN], cur2[DIR ? 4 : 1][FN], nxt2[DIR ? 4 : 1][FN];
+        i2 hn = *(const i2 *)(g.hdr + e);
+        load_cols(e);
+        if (with_c) load_c(g.c, nxt);
+        if constexpr (DIR) load_c(g.c2, nxt2);
+        load_cols(e + 2);
+        if (with_c) take(hn, nxt, cur);
+        if constexpr (DIR) take(hn, nxt2, cur2);
+        for (int q = q0; q < q1; ++q) {
+            const Quad *Q = g.quads + q;
+            const int alpha = Q->alpha[y];
+            const int e_end = Q->entry_end;
+            win.rows = g.steps + (int64_t)Q->step_off * 8;
+            win.fetch(win.rows);
+            // angular factors times r^alpha; DIR: the directional derivative
+            // as kc0 R + kc1 dv/ds terms of a cos column, ks* of a sin column
+            double wc[FM], ws[FM], kc0[DIR ? FM : 1], kc1[DIR ? FM : 1], ks0[DIR ? FM : 1], ks1[DIR ? FM : 1], av[FM];
+            Walk<J> w[FM];
+#pragma unroll
+            for (int i = 0; i < FM; ++i) {
+                const double fa = (double)alpha;
+                double cs, sn;
+                th[i].angle(fa, cs, sn);
+                const double w0 = quad_pow(rr[i], r2[i], alpha, Q->alpha_min, Q->spread);
+                wc[i] = w0 * cs;
+                ws[i] = w0 * sn;
+                if constexpr (DIR) {
+                    const double w1 = alpha ? fa * ipow(rr[i], alpha - 1) : 0.0;
+                    kc0[i] = __builtin_fma(tr[i], w1 * cs, -(tt[i] * fa) * ws[i]);
+                    ks0[i] = __builtin_fma(tr[i], w1 * sn, (tt[i] * fa) * wc[i]);
+                    kc1[i] = tr[i] * an[i].s1 * wc[i];
+                    ks1[i] = tr[i] * an[i].s1 * ws[i];
+                }
+                w[i].start();
+                av[i] = 1.0;
+            }
+            win.start();
+            for (e = Q->entry_off; e < e_end; e += 2) {
+                const i2 hg = hn;
+                hn = *(const i2 *)(g.hdr + e + 2);
+                if (with_c) load_c(g.c, nxt);
+                if constexpr (DIR) load_c(g.c2, nxt2);
+                load_cols(e + 4);
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const int h = hg[j];
+                    if (h < 0x10000) continue; // the padding of an odd number of entries
+                    while (win.K < (h & 0xffff)) {
+                        win.advance(w, an);
+#pragma unroll
+                        for (int i = 0; i < FM; ++i) av[i] = w[i].a * w[i].v[0];
+                    }
+#pragma unroll
+                    for (int f = 0; f < 2; ++f) {
+                        const int mask = (h >> (16 + 4 * f)) & 15;
+                        if (mask == 0) continue;
+                        double a[FM], a2[DIR ? FM : 1];
+#pragma unroll
+                        for (int i = 0; i < FM; ++i) {
+                            a[i] = (f ? ws[i] : wc[i]) * av[i];
+                            if constexpr (DIR)
+                                a2[i] = __builtin_fma(f ? ks0[i] : kc0[i], av[i], (f ? ks1[i] : kc1[i]) * (w[i].a * w[i].v[J]));
+                        }
+                        if (mask != 15) { // a chain without this column: its lanes contribute nothing
+                            asm volatile(""); // (kept as a branch: most degrees have all four)
+                            const bool has = (mask >> y) & 1;
+#pragma unroll
+                            for (int i = 0; i < FM; ++i) {
+                                a[i] = has ? a[i] : 0.0;
+                                if constexpr (DIR) a2[i] = has ? a2[i] : 0.0;
+                            }
+                        }
+                        if (with_c) {
+#pragma unroll
+                            for (int n = 0; n < FN; ++n)
+#pragma unroll
+                                for (int i = 0; i < FM; ++i)
+                                    acc[i][n] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], cur[2 * j + f][n], acc[i][n], 0, 0, 0);
+                        }
+                        if constexpr (DIR) {
+#pragma unroll
+                            for (int n = 0; n < FN; ++n)
+#pragma unroll
+                                for (int i = 0; i < FM; ++i)
+                                    acc[i][n] = __builtin_amdgcn_mfma_f64_16x16x4f64(a2[i], cur2[2 * j + f][n], acc[i][n], 0, 0, 0);
+                        }
+                    }
+                }
+                if (with_c) take(hn, nxt, cur);
+                if constexpr (DIR) take(hn, nxt2, cur2);
+            }
+        }
+    }
+    // the four slices' sums, always as (0 + 1) + (2 + 3)
+    constexpr int C = 16 * FN;
+#pragma unroll
+    for (int i = 0; i < FM; ++i) {
+        if (i) __syncthreads();
+#pragma unroll
+        for (int n = 0; n < FN; ++n)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) red[wave][(y + 4 * t) * C + 16 * n + x] = acc[i][n][t];
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < FN; ++k) {
+            const int e = k * kThreads + (int)threadIdx.x;
+            const int64_t p = p0 + 16 * i + e / C;
+            const uint32_t b = b0 + e % C;
+            if (p < g.P && b < g.B) g.f[p * g.B + b] = (red[0][e] + red[1][e]) + (red[2][e] + red[3][e]);
+        }
+    }
+}
+
+template <int FM, int FN, bool DIR> void launch_fwd_t(FwdArgs g, hipStream_t s)
+{
+    g.npb = (g.P + 16 * FM - 1) / (16 * FM);
+    const int64_t nsb = (g.B + 16 * FN - 1) / (16 * FN);
+    hipLaunchKernelGGL((fwd_kernel<FM, FN, DIR>), dim3((unsigned)(g.npb * nsb)), dim3(kThreads), 0, s, g);
+}
+
+template <int FN, bool DIR> void launch_fwd_n(const FwdArgs &g, int fm, hipStream_t s)
+{
+    if (fm == 4 && FN == 1 && !DIR)
+        launch_fwd_t<FN == 1 && !DIR ? 4 : 2, FN, DIR>(g, s);
+    else if (fm >= 2)
+        launch_fwd_t<2, FN, DIR>(g, s);
+    else
+        launch_fwd_t<1, FN, DIR>(g, s);
+}
+
+// Two workgroups of four waves per CU is what the larger tiles' registers
+// allow; a smaller point tile is taken where that would leave CUs idle.
+int64_t wanted_workgroups() { return 2 * (int64_t)std::max(1, device_cus()); }
+
+// 24-bit products and 32-bit byte offsets into the coefficients.
+bool small_rows(int64_t M, int64_t B) { return M < (1 << 24) && B < (1 << 20) && 8 * M * B < ((int64_t)1 << 32); }
+
+} // namespace
+
+// Chosen by the sets alone (and the 32-bit offsets), so that a point's row
+// does not depend on how many points a call has.  Forward, basis + GEMM ->
+// fused: (n <= 64, 65536 points) 755 -> 382 us with 64 sets, 787 -> 751 with
+// 128; (n <= 40, 2048 points, 128 sets) 139 -> 23 us; (n <= 40, 16384 points)
+// 156 -> 94 us with 128 sets, 157 -> 137 with 192, 162 -> 180 with 256, where
+// the GEMM's larger tiles win.  With the directional derivative (n <= 64,
+// 65536 points) 1502 -> 1288 us with 96 sets, 1521 -> 1712 with 128.
+bool fused_fwd_ok(int64_t M, int64_t P, int64_t B, bool dir)
+{
+    return B <= (dir ? 96 : 128) && small_rows(M, B) && (P + 15) / 16 * ((B + 15) / 16) <= INT32_MAX;
+}
+
+zp_status launch_fused_fwd(const Plan &p, const double *r, const double *th, int64_t P, const double *c,
+                           const double *c2, const double *tr, const double *tt, int64_t B, double *f, hipStream_t s)
+{
+    FwdArgs g{p.d_quads, p.d_qsteps, p.d_entry_hdr, p.d_entry_cols, p.d_slice_off, r, th, P, c, c2, tr, tt,
+              (uint32_t)B, f, 0};
+    // as few blocks of sets as 256 registers hold, of equal width
+    const int64_t tiles = (B + 15) / 16, widest = c2 ? 2 : 4, nsb = (tiles + widest - 1) / widest;
+    const int fn = (int)((tiles + nsb - 1) / nsb);
+    int fm = 4;
+    while (fm > 1 && (P + 16 * fm - 1) / (16 * fm) * nsb < wanted_workgroups()) fm /= 2;
+    if (c2) {
+        fn == 2 ? launch_fwd_n<2, true>(g, fm, s) : launch_fwd_n<1, true>(g, fm, s);
+    } else {
+        switch (fn) {
+        case 1: launch_fwd_n<1, false>(g, fm, s); break;
+        case 2: launch_fwd_n<2, false>(g, fm, s); break;
+        case 3: launch_fwd_n<3, false>(g, fm, s); break;
+        default: launch_fwd_n<4, false>(g, fm, s); break;
+        }
+    }
+    return hip_check(hipGetLastError(), "fused forward launch");
+}
+
+} // namespace zp

@@ -32,6 +32,7 @@ struct DevState {
     unsigned char *ptr = nullptr;       // device address of this device's scratch
     std::shared_ptr<zp::Plan> plan;     // plan whose tables are in scratch (null: none)
     std::vector<unsigned char> image;   // host image of those tables
+    bool fused = false;                 // the fused kernels' tables are in scratch too
 };
 
 std::mutex g_mu;
@@ -55,12 +56,14 @@ extern "C" zp_status zp_series_fwd_noalloc(const int32_t *h_n, const int32_t *h_
 
     std::lock_guard<std::mutex> lock(g_mu);
     DevState &d = g_dev[dev];
-    const bool same = d.plan && (int64_t)d.plan->n.size() == M && std::equal(d.plan->n.begin(), d.plan->n.end(), h_n) &&
+    const bool same_list = d.plan && (int64_t)d.plan->n.size() == M && std::equal(d.plan->n.begin(), d.plan->n.end(), h_n) &&
                       std::equal(d.plan->m.begin(), d.plan->m.end(), h_m);
-    std::shared_ptr<Plan> plan = same ? d.plan : build_plan_host(h_n, h_m, M);
+    std::shared_ptr<Plan> plan = same_list ? d.plan : build_plan_host(h_n, h_m, M);
     PlanOffsets off{};
-    const size_t tables = (plan_image(*plan, nullptr, &off) + 255) / 256 * 256;
-    const size_t need = tables + series_fwd_min_ws(M, P, B, prec);
+    auto al = [](size_t x) { return (x + 255) / 256 * 256; };
+    const size_t all = al(plan_image(*plan, nullptr, &off)), base = al(off.base);
+    const size_t min_ws = series_fwd_min_ws(M, P, B, prec);
+    const size_t need = base + min_ws;
     if (need > (size_t)ZP_NOALLOC_SCRATCH_BYTES) { // before any device work
         char buf[200];
         std::snprintf(buf, sizeof buf,
@@ -75,17 +78,25 @@ extern "C" zp_status zp_series_fwd_noalloc(const int32_t *h_n, const int32_t *h_
         if (st != ZP_OK) return st;
         d.ptr = (unsigned char *)p;
     }
-    if (!same) {
+    // The fused kernels' tables (the last of the image) come along where they
+    // fit: the fused forward needs no workspace beside them, the others keep
+    // theirs.  A call that needs them, or their room, other than the call
+    // before left it, copies again.
+    const bool wants = series_fwd_fused(M, P, B, prec);
+    const bool fused = all + (wants ? 0 : min_ws) <= (size_t)ZP_NOALLOC_SCRATCH_BYTES;
+    if (!same_list || fused != d.fused) {
         d.plan.reset(); // the tables in scratch are about to change
         plan_image(*plan, &d.image, &off);
-        st = hip_check(hipMemcpyAsync(d.ptr, d.image.data(), off.total, hipMemcpyHostToDevice, s),
+        st = hip_check(hipMemcpyAsync(d.ptr, d.image.data(), fused ? off.total : off.base, hipMemcpyHostToDevice, s),
                        "hipMemcpyAsync(plan tables)");
         if (st == ZP_OK) st = hip_check(hipStreamSynchronize(s), "hipStreamSynchronize");
         if (st != ZP_OK) return st;
         plan->device = dev;
-        plan_bind(*plan, d.ptr, off);
+        plan_bind(*plan, d.ptr, off, fused);
         d.plan = plan;
+        d.fused = fused;
     }
+    const size_t tables = fused ? all : base;
     return series_fwd_run(*plan, M, d_r, d_theta, P, d_c, B, prec, d_f, nullptr, d.ptr + tables,
                           (size_t)ZP_NOALLOC_SCRATCH_BYTES - tables, false, s);
 }

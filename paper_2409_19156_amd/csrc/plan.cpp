@@ -36,6 +36,100 @@ static double signed_binom(int K, int alpha)
     return (double)((K & 1) ? -v : v);
 }
 
+// Recurrence step k >= 1 of the chain of alpha (the formulas of zp_internal.hpp).
+static Coef step_coef(int64_t K, int64_t A)
+{
+    Coef cf{};
+    if (K > 1) {
+        cf.cc_lo = ratio((K - 1) * (K - 1) * (2 * K + A), (K + A) * (K + A) * (2 * K + A - 2));
+        cf.cc_hi = ratio((K + A - 1) * (K - 1) * (2 * K + A), K * (K + A) * (2 * K + A - 2));
+    }
+    cf.bs_lo = ratio((2 * K + A - 1) * (2 * K + A), 2 * (K + A) * (K + A));
+    cf.bs_hi = ratio((2 * K + A - 1) * (2 * K + A), 2 * K * (K + A));
+    return cf;
+}
+
+// The fused series kernels' tables, from the whole chains in emission order.
+static void build_quads(Plan &plan)
+{
+    const std::vector<Chain> &ch = plan.achains;
+    for (size_t c = 0; c < ch.size(); ++c)
+        while (plan.row_chain.size() * 16 < (size_t)(ch[c].emit_off + ch[c].emit_cnt)) plan.row_chain.push_back((int32_t)c);
+    std::vector<int32_t> order(ch.size());
+    for (size_t c = 0; c < ch.size(); ++c) order[c] = (int32_t)c;
+    std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) { return ch[(size_t)x].kmax > ch[(size_t)y].kmax; });
+    // four chains at a time, longest first; each quad to the slice with the
+    // least work so far (contraction steps, recurrence steps, and the set-up
+    // of a chain's angle and power, about six contraction steps' worth)
+    const size_t nq = (ch.size() + 3) / 4;
+    std::vector<std::vector<size_t>> slice(kSlices);
+    std::vector<double> load(kSlices, 0.0);
+    auto chain_of = [&](size_t q, size_t y) { return order[std::min(4 * q + y, ch.size() - 1)]; };
+    for (size_t q = 0; q < nq; ++q) {
+        int most = 0;
+        for (size_t y = 0; y < 4 && 4 * q + y < ch.size(); ++y) most = std::max(most, ch[(size_t)chain_of(q, y)].emit_cnt);
+        const size_t w = (size_t)(std::min_element(load.begin(), load.end()) - load.begin());
+        slice[w].push_back(q);
+        load[w] += (double)most + 0.5 * ch[(size_t)chain_of(q, 0)].kmax + 6.0;
+    }
+    plan.slice_off.push_back(0);
+    for (int w = 0; w < kSlices; ++w) {
+        for (size_t q : slice[(size_t)w]) {
+            Quad Q{};
+            Q.kmax = ch[(size_t)chain_of(q, 0)].kmax;
+            Q.step_off = (int32_t)(plan.qsteps.size() / 8);
+            Q.entry_off = (int32_t)plan.entry_hdr.size();
+            long double a_lo[4] = {1.0L, 1.0L, 1.0L, 1.0L};
+            int next[4], end[4];
+            for (size_t y = 0; y < 4; ++y) {
+                const Chain &c = ch[(size_t)chain_of(q, y)];
+                Q.alpha[y] = c.alpha;
+                next[y] = c.emit_off;
+                end[y] = 4 * q + y < ch.size() ? c.emit_off + c.emit_cnt : c.emit_off; // a repeated chain has no columns
+            }
+            Q.alpha_min = *std::min_element(Q.alpha, Q.alpha + 4);
+            Q.spread = *std::max_element(Q.alpha, Q.alpha + 4) - Q.alpha_min;
+            for (int k = 0; k <= Q.kmax; ++k) {
+                for (size_t y = 0; y < 4; ++y) {
+                    const Coef cf = k ? step_coef(k, Q.alpha[y]) : Coef{};
+                    if (k) a_lo[y] = -a_lo[y] * (long double)(Q.alpha[y] + k) / (long double)k;
+                    plan.qsteps.push_back({cf.cc_lo, cf.bs_lo, (double)a_lo[y], 0.0});
+                    plan.qsteps.push_back({cf.cc_hi, cf.bs_hi, 1.0, 0.0});
+                }
+                // columns of degree k: cos and sin lists per chain, one entry per position
+                std::vector<int32_t> cols[2][4];
+                size_t depth = 0;
+                for (size_t y = 0; y < 4; ++y)
+                    for (; next[y] < end[y] && plan.emits[(size_t)next[y]].K == k; ++next[y]) {
+                        const Emit &e = plan.emits[(size_t)next[y]];
+                        cols[e.flags & 1][y].push_back(e.col);
+                        depth = std::max(depth, cols[e.flags & 1][y].size());
+                    }
+                for (size_t d = 0; d < depth; ++d) {
+                    int hdr = k;
+                    for (int f = 0; f < 2; ++f)
+                        for (size_t y = 0; y < 4; ++y) {
+                            const bool has = d < cols[f][y].size();
+                            hdr |= has ? 1 << (16 + 4 * f + (int)y) : 0;
+                            plan.entry_cols.push_back(has ? cols[f][y][d] : 0);
+                        }
+                    plan.entry_hdr.push_back(hdr);
+                }
+            }
+            Q.entry_end = (int32_t)plan.entry_hdr.size();
+            if (plan.entry_hdr.size() % 2) {
+                plan.entry_hdr.push_back(Q.kmax);
+                plan.entry_cols.insert(plan.entry_cols.end(), 8, 0);
+            }
+            plan.quads.push_back(Q);
+        }
+        plan.slice_off.push_back((int32_t)plan.quads.size());
+    }
+    plan.entry_hdr.insert(plan.entry_hdr.end(), kEntryTail, 0);
+    plan.entry_cols.insert(plan.entry_cols.end(), 8 * kEntryTail, 0);
+    plan.qsteps.insert(plan.qsteps.end(), 8 * kStepTail, QuadStep{});
+}
+
 std::shared_ptr<Plan> build_plan_host(const int32_t *n, const int32_t *m, int64_t M)
 {
     auto plan = std::make_shared<Plan>();
@@ -73,25 +167,14 @@ std::shared_ptr<Plan> build_plan_host(const int32_t *n, const int32_t *m, int64_
         c.coef_off = (int32_t)plan->coefs.size();
         c.emit_off = (int32_t)plan->emits.size();
         c.emit_cnt = (int32_t)v.size();
-        for (int k = 1; k <= c.kmax; ++k) {
-            const int64_t K = k, A = a;
-            Coef cf{};
-            if (k == 1) {
-                cf.cc_lo = 0.0;
-                cf.cc_hi = 0.0;
-            } else {
-                cf.cc_lo = ratio((K - 1) * (K - 1) * (2 * K + A), (K + A) * (K + A) * (2 * K + A - 2));
-                cf.cc_hi = ratio((K + A - 1) * (K - 1) * (2 * K + A), K * (K + A) * (2 * K + A - 2));
-            }
-            cf.bs_lo = ratio((2 * K + A - 1) * (2 * K + A), 2 * (K + A) * (K + A));
-            cf.bs_hi = ratio((2 * K + A - 1) * (2 * K + A), 2 * K * (K + A));
-            plan->coefs.push_back(cf);
-        }
+        for (int k = 1; k <= c.kmax; ++k) plan->coefs.push_back(step_coef(k, a));
         plan->emits.insert(plan->emits.end(), v.begin(), v.end());
         // Work estimate: stores dominate; the recurrence costs about one
         // store-equivalent per few steps.
         tmp.push_back({c, 4.0 * c.emit_cnt + 0.5 * c.kmax});
     }
+    for (auto &t : tmp) plan->achains.push_back(t.c); // still in emission order
+    build_quads(*plan);
     std::stable_sort(tmp.begin(), tmp.end(), [](const Tmp &x, const Tmp &y) { return x.cost > y.cost; });
     for (auto &t : tmp) plan->chains.push_back(t.c);
 
@@ -220,7 +303,8 @@ Plan::~Plan()
 }
 
 // Device image of a plan's tables: chains and pieces side by side, then the
-// coefficients, the emissions and the permutation, each 256-byte aligned.
+// coefficients, the emissions, the permutation and the fused series kernels'
+// tables, each 256-byte aligned.
 size_t plan_image(const Plan &p, std::vector<unsigned char> *host, PlanOffsets *o)
 {
     const size_t a = (p.chains.size() + p.pieces.size()) * sizeof(Chain);
@@ -230,10 +314,33 @@ size_t plan_image(const Plan &p, std::vector<unsigned char> *host, PlanOffsets *
     o->coefs = (a + 255) / 256 * 256;
     o->emits = o->coefs + (b + 255) / 256 * 256;
     o->perm = o->emits + (c + 255) / 256 * 256;
-    o->total = o->perm + d;
+    size_t end = o->base = o->perm + d;
+    auto place = [&end](size_t bytes) {
+        const size_t at = (end + 255) / 256 * 256;
+        end = at + bytes;
+        return at;
+    };
+    o->achains = place(p.achains.size() * sizeof(Chain));
+    o->row_chain = place(p.row_chain.size() * sizeof(int32_t));
+    o->quads = place(p.quads.size() * sizeof(Quad));
+    o->slice_off = place(p.slice_off.size() * sizeof(int32_t));
+    o->qsteps = place(p.qsteps.size() * sizeof(QuadStep));
+    o->entry_hdr = place(p.entry_hdr.size() * sizeof(int32_t));
+    o->entry_cols = place(p.entry_cols.size() * sizeof(int32_t));
+    o->total = end;
     if (!host) return o->total;
     host->assign(o->total, 0);
     unsigned char *h = host->data();
+    auto put = [h](size_t at, const auto &v) {
+        std::copy_n((const unsigned char *)v.data(), v.size() * sizeof(v[0]), h + at);
+    };
+    put(o->achains, p.achains);
+    put(o->row_chain, p.row_chain);
+    put(o->quads, p.quads);
+    put(o->slice_off, p.slice_off);
+    put(o->qsteps, p.qsteps);
+    put(o->entry_hdr, p.entry_hdr);
+    put(o->entry_cols, p.entry_cols);
     std::copy_n((const unsigned char *)p.chains.data(), p.chains.size() * sizeof(Chain), h);
     std::copy_n((const unsigned char *)p.pieces.data(), p.pieces.size() * sizeof(Chain),
                 h + p.chains.size() * sizeof(Chain));
@@ -246,7 +353,7 @@ size_t plan_image(const Plan &p, std::vector<unsigned char> *host, PlanOffsets *
     return o->total;
 }
 
-void plan_bind(Plan &p, const void *base, const PlanOffsets &o)
+void plan_bind(Plan &p, const void *base, const PlanOffsets &o, bool fused)
 {
     const unsigned char *b = (const unsigned char *)base;
     p.d_chains = (const Chain *)b;
@@ -254,6 +361,15 @@ void plan_bind(Plan &p, const void *base, const PlanOffsets &o)
     p.d_coefs = (const Coef *)(b + o.coefs);
     p.d_emits = (const Emit *)(b + o.emits);
     p.d_perm = (const int32_t *)(b + o.perm);
+    p.d_quads = nullptr;
+    if (!fused) return;
+    p.d_achains = (const Chain *)(b + o.achains);
+    p.d_row_chain = (const int32_t *)(b + o.row_chain);
+    p.d_quads = (const Quad *)(b + o.quads);
+    p.d_slice_off = (const int32_t *)(b + o.slice_off);
+    p.d_qsteps = (const QuadStep *)(b + o.qsteps);
+    p.d_entry_hdr = (const int32_t *)(b + o.entry_hdr);
+    p.d_entry_cols = (const int32_t *)(b + o.entry_cols);
 }
 
 static zp_status upload(Plan &p)

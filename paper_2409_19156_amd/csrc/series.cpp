@@ -5,6 +5,8 @@
 //   1. basis Z of the chunk in the contraction type (zero padded) -> cache or ws
 //      (with a cache, also dZ/dr and dZ/dtheta for the backward)
 //   2. f[p0.., :] = Z^T c                     (GEMM, K = modes)
+// In FP64 with few sets (fused_fwd_ok) both steps are one kernel and no basis
+// is stored (fused.hip).
 // Backward, per chunk:
 //   1. Z, dZ/dr, dZ/dtheta from the cache, or recomputed into ws
 //   2. g of the chunk converted to the contraction type
@@ -356,6 +358,11 @@ size_t series_fwd_min_ws(int64_t M, int64_t P, int64_t B, int32_t prec)
     return WsLayout(M, std::min<int64_t>(P, kPad), B, ct_of(prec), true, false, false).total;
 }
 
+bool series_fwd_fused(int64_t M, int64_t P, int64_t B, int32_t prec)
+{
+    return ct_of(prec) == CT_F64 && fused_fwd_ok(M, P, B, false);
+}
+
 zp_status series_fwd_run(const Plan &pl, int64_t M, const double *d_r, const double *d_theta, int64_t P,
                          const double *d_c, int64_t B, int32_t prec, double *d_f, void *d_cache, void *d_ws,
                          size_t ws_bytes, bool allow_pipe, hipStream_t s)
@@ -364,6 +371,16 @@ zp_status series_fwd_run(const Plan &pl, int64_t M, const double *d_r, const dou
     zp_status st = ZP_OK;
     const int ct = ct_of(prec);
     const bool have_cache = d_cache != nullptr;
+    if (pl.d_quads && series_fwd_fused(M, P, B, prec)) { // the basis is formed inside the contraction
+        if (have_cache) { // the backward may still read it
+            const CacheLayout CL(M, P, ct);
+            char *cache = (char *)d_cache;
+            st = basis_into(pl, d_r, d_theta, 0, P, ct, cache + CL.z_off, cache + CL.zr_off, cache + CL.zt_off, CL.Pp,
+                            CL.Mp, M, s);
+            if (st != ZP_OK) return st;
+        }
+        return launch_fused_fwd(pl, d_r, d_theta, P, d_c, nullptr, nullptr, nullptr, B, d_f, s);
+    }
     int64_t Pc = chunk_for(M, P, B, ct, true, false, have_cache, ws_bytes);
     if (Pc <= 0) return set_error(ZP_ERR_WORKSPACE, "workspace smaller than the minimum (zp_series_workspace)");
 
@@ -645,6 +662,9 @@ extern "C" zp_status zp_series_jvp(const int32_t *h_n, const int32_t *h_m, int64
     std::shared_ptr<Plan> plan;
     st = get_plan(h_n, h_m, M, &plan);
     if (st != ZP_OK) return st;
+    if (ct == CT_F64 && fused_fwd_ok(M, P, B, with_dir))
+        return launch_fused_fwd(*plan, d_r, d_theta, P, with_c ? d_tc : nullptr, with_dir ? d_c : nullptr, d_tr,
+                                d_ttheta, B, d_tf, s);
     // pipelined chunks when the workspace holds two chunk buffers (as the forward)
     const int64_t Pq = Pc == P ? pipe_chunk(P, B, ct) : 0;
     const size_t zstride = Pq > 0 ? al(ct_bytes(ct) * (size_t)(2 * pad_up(M)) * (size_t)Pq) : 0;

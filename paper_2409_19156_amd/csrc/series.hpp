@@ -79,6 +79,19 @@ size_t series_fwd_min_ws(int64_t M, int64_t P, int64_t B, int32_t prec);
 zp_status series_fwd_run(const Plan &plan, int64_t M, const double *d_r, const double *d_theta, int64_t P,
                          const double *d_c, int64_t B, int32_t prec, double *d_f, void *d_cache, void *d_ws,
                          size_t ws_bytes, bool allow_pipe, hipStream_t s);
+// Whether series_fwd_run takes the fused kernel, which needs no workspace but
+// the fused tables of the plan (plan.d_quads not null).
+bool series_fwd_fused(int64_t M, int64_t P, int64_t B, int32_t prec);
+
+// ---- FP64 without a stored basis (fused.hip) ----
+
+// f[p][b] = sum_k Z_k(p) c[k][b] + sum_k (tr[p] dZ_k/dr + tt[p] dZ_k/dtheta) c2[k][b]
+// (c or c2 nullable, one of them given; tr, tt nullable), where
+// fused_fwd_ok(.., dir = c2 given) says that the kernel takes the sizes and
+// is the faster one.
+bool fused_fwd_ok(int64_t M, int64_t P, int64_t B, bool dir);
+zp_status launch_fused_fwd(const Plan &p, const double *r, const double *th, int64_t P, const double *c,
+                           const double *c2, const double *tr, const double *tt, int64_t B, double *f, hipStream_t s);
 
 // dst (compute type, [R_pad][C_pad] or transposed [C_pad][R_pad]) from a
 // row-major FP64 src [R][C] (leading dimension lds); zero padding.

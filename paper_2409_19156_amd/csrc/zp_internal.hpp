@@ -60,6 +60,43 @@ struct Emit {
     double a_lo; // (-1)^K C(K+alpha, K): low-anchor factor from v_K to R / r^alpha
 };
 
+// ---- tables of the fused FP64 series kernels (fused.hip) ----
+//
+// A wave of those kernels evaluates four chains at once: lane l works on
+// chain l / 16 of a quad, which is the layout of an FP64 MFMA operand whose
+// contraction index runs over the four chains.  The chains of a plan are
+// taken four at a time, longest first, and walk their steps together.
+//
+// QuadStep: recurrence step k of one chain (k = 0: no step) for one anchor,
+// and the factor a from v_k to R / r^alpha: (-1)^k C(k+alpha, k) for the low
+// anchor, 1 for the high one.  Rows of eight: [chain y][low, high].  Every
+// chain of a quad has steps up to the quad's kmax, whether it is asked for
+// their degrees or not.
+struct QuadStep {
+    double cc, bs, a, pad;
+};
+
+// Entries: one per degree of a quad (more where columns repeat).  Entry e
+// has, for each of the quad's four chains y, at most one cos and one sin
+// column of degree K: hdr[e] = K | cos mask << 16 | sin mask << 20 (bit y:
+// chain y has one), cols[8 e + y] and cols[8 e + 4 + y] (0 where none).
+// A quad's entries are in ascending K, padded to an even count with one that
+// has no column; the whole list ends with kEntryTail such entries.
+constexpr int kEntryTail = 8;
+constexpr int kStepTail = 32; // empty rows of steps at the end: whole windows of rows are loaded
+struct Quad {
+    int32_t alpha[4];
+    int32_t step_off; // row of this quad's step 0
+    int32_t kmax;
+    int32_t entry_off, entry_end; // even; the end without the padding
+    int32_t alpha_min, spread; // smallest alpha, largest alpha - alpha_min
+};
+
+// The quads are dealt to kSlices slices of about equal work, one per wave of
+// a workgroup; the slices' partial sums are always combined in the same
+// order, so a point's sums do not depend on the launch.
+constexpr int kSlices = 4;
+
 struct Plan {
     int device = -1;
     std::vector<int32_t> n, m; // the key
@@ -72,6 +109,12 @@ struct Plan {
     std::vector<Chain> pieces;
     std::vector<Coef> coefs;
     std::vector<Emit> emits;
+    std::vector<Chain> achains;      // whole chains, ascending emission index
+    std::vector<int32_t> row_chain;  // row_chain[t]: index into achains of the chain of emission 16 t
+    std::vector<Quad> quads;         // slice by slice: quads slice_off[w] .. slice_off[w+1] - 1 are slice w's
+    std::vector<int32_t> slice_off;  // [kSlices + 1]
+    std::vector<QuadStep> qsteps;    // [step_off + k][chain][anchor]
+    std::vector<int32_t> entry_hdr, entry_cols;
     int32_t nmax = 0;
     // device copies (one allocation)
     void *dmem = nullptr;
@@ -80,6 +123,12 @@ struct Plan {
     const Coef *d_coefs = nullptr;
     const Emit *d_emits = nullptr;
     const int32_t *d_perm = nullptr; // d_perm[e] = emits[e].col: chain-major order -> column
+    const Chain *d_achains = nullptr;
+    const int32_t *d_row_chain = nullptr;
+    const Quad *d_quads = nullptr;
+    const int32_t *d_slice_off = nullptr;
+    const QuadStep *d_qsteps = nullptr;
+    const int32_t *d_entry_hdr = nullptr, *d_entry_cols = nullptr;
     // Coefficient table of the direct (closed-form) evaluation, built on first
     // use: per mode, for j = 0..3, the K+1 values c_s (n-2s)!/(n-2s-j)! of
     // d^j/dr^j of Eq. (radial-part-eq), rounded to double.
@@ -122,13 +171,16 @@ std::shared_ptr<Plan> build_plan_host(const int32_t *n, const int32_t *m, int64_
 
 // Byte offsets of a plan's device tables within one contiguous image (the
 // chains and pieces start at offset 0).
+// The fused series kernels' tables come last: an image of base bytes leaves
+// them out.
 struct PlanOffsets {
-    size_t coefs, emits, perm, total;
+    size_t coefs, emits, perm, base, achains, row_chain, quads, slice_off, qsteps, entry_hdr, entry_cols, total;
 };
 // Size of the image (and, if host is not null, the image itself).
 size_t plan_image(const Plan &p, std::vector<unsigned char> *host, PlanOffsets *o);
-// Point the plan's device table pointers into an image at base.
-void plan_bind(Plan &p, const void *base, const PlanOffsets &o);
+// Point the plan's device table pointers into an image at base (fused: the
+// fused kernels' tables are there too; null otherwise).
+void plan_bind(Plan &p, const void *base, const PlanOffsets &o, bool fused = true);
 
 // Cached plan for the current device, uploaded on first use.
 zp_status get_plan(const int32_t *n, const int32_t *m, int64_t M, std::shared_ptr<Plan> *out);
