@@ -189,6 +189,15 @@ def _budget(mem_budget):
     return int(os.environ.get("ZP_MEM_BUDGET_BYTES", str(32 << 30)))
 
 
+# FP64 series of up to this many sets form the basis inside their contractions,
+# in the backward too (kFusedDotSets in csrc/series.hpp): nothing to keep.
+_FUSED_SETS = 96
+
+
+def _keeps_basis(B: int, prec) -> bool:
+    return _prec_code(prec) != PREC["fp64"] or B > _FUSED_SETS
+
+
 def _workspace(M, P, B, prec, budget, device):
     full, mn, _ = series_sizes(M, P, B, prec)
     nbytes = full if full <= budget else max(mn, budget)
@@ -361,8 +370,8 @@ class ZernikeSeries(torch.autograd.Function):
     rule (zp_series_jvp).
 
     The basis (Z, dZ/dr, dZ/dtheta) is kept from the forward when its size is
-    within the memory budget, and recomputed chunk by chunk in the backward
-    otherwise."""
+    within the memory budget and the backward reads it (FP64 with few sets
+    does not), and recomputed chunk by chunk in the backward otherwise."""
 
     @staticmethod
     def forward(ctx, c, r, theta, n, m, prec="fp64", mem_budget=None):
@@ -371,7 +380,7 @@ class ZernikeSeries(torch.autograd.Function):
         budget = _budget(mem_budget)
         _, _, cache_bytes = series_sizes(M, P, B, prec)
         cache = None
-        if M and P and B and cache_bytes <= budget:
+        if M and P and B and cache_bytes <= budget and _keeps_basis(B, prec):
             cache = torch.empty(cache_bytes, dtype=torch.uint8, device=r.device)
         f = series_forward(nh, mh, r, theta, c, prec, cache=cache, mem_budget=budget)
         ctx.modes = (nh, mh)
@@ -562,7 +571,7 @@ class ZernikeSeries3D(torch.autograd.Function):
         cache = None
         if J and P and Q and B:
             _, _, cache_bytes = series3d_sizes(nh, mh, lh, P, Q, B, prec)
-            if cache_bytes <= budget:
+            if cache_bytes <= budget and _keeps_basis(Q * B, prec):
                 cache = torch.empty(cache_bytes, dtype=torch.uint8, device=r.device)
         f = series3d_forward(nh, mh, lh, r, theta, phi, c, prec, cache=cache, mem_budget=budget)
         ctx.modes = (nh, mh, lh)

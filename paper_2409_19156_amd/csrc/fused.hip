@@ -1,6 +1,7 @@
 // FP64 Zernike series without a stored basis: the recurrence runs inside the
 // contraction, and its values go from the lane that forms them straight into
-// an FP64 MFMA operand (forward and forward-mode derivative).
+// an FP64 MFMA operand (forward and forward-mode derivative) or weigh what an
+// MFMA returns to it (column dots of the backward).
 //
 // MFMA 16x16x4 (FP64): lane l = x + 16 y (x < 16, y < 4) supplies A[x][y] and
 // B[y][x] and receives D[y + 4 t][x], t = 0..3.
@@ -10,6 +11,11 @@
 // contraction index running over the quad's four chains; the cos and the sin
 // columns of a degree are two contraction steps over one recurrence value
 // times two angular factors.  B is the four coefficient rows.
+// Column dots (dot_kernel): D = modes x points, H = c g^T for two degrees at a
+// time: D[y + 4 t][x] is the cos (t even) or sin column of degree t / 2 on
+// chain y at point x, so lane (x, y) receives exactly the modes of the chain
+// that it walks itself, and weighs them with its own recurrence values.  Over a chain only the sums of H v^(i) are kept;
+// the powers, angles and chain-rule factors are applied once per chain.
 //
 // Arithmetic of the walk: as the basis kernel (chain_kernel.hip).
 #include <hip/hip_runtime.h>
@@ -460,6 +466,291 @@ template <int FN, bool DIR> void launch_fwd_n(const FwdArgs &g, int fm, hipStrea
         launch_fwd_t<1, FN, DIR>(g, s);
 }
 
+// ------------------------------------------------------------ column dots --
+
+struct DotArgs {
+    const Quad *quads;
+    const QuadStep *steps;
+    const int32_t *hdr, *cols, *slice;
+    const double *r, *th;
+    int64_t P;
+    const double *c;      // first order: coefficients; second order: those of the Er, Et term
+    const double *u;      // second order: coefficients of the dZ/dr, dZ/dtheta term
+    const double *ur, *ut; // second order
+    uint32_t B;
+    const double *g;
+    double *part; // [set chunk][2][P]
+    double *out_r, *out_t; // with one set chunk: the outputs (nullable) instead of part
+    int64_t npb;
+    bool vec; // c, u and g are 16-byte aligned
+};
+
+// FP blocks of 16 points per wave, KB contraction steps of four sets (one
+// chunk of 4 KB sets, on the grid).  SEC: the second-order sums; HU / HC:
+// with the u and / or the c term (first order: HC alone).
+//
+// Bound as the forward, by MFMA and vector cycles together; the gradient's
+// fragments stay in registers for the whole walk and H is weighed in the
+// registers that the MFMA leaves it in, so no derivative plane is written or
+// read.  n <= 64, 65536 points: 1 set 1096 -> 115 us, 64 sets 1104 -> 581 us.
+template <int FP, int KB, bool SEC, bool HU, bool HC>
+__global__ __launch_bounds__(kThreads, 2) void dot_kernel(DotArgs g)
+{
+    constexpr int J = SEC && HC ? 2 : 1;
+    // sums of H v^(i): first-order term (i <= 1) and, SEC, the c term (i <= 2)
+    constexpr bool FIRST = !SEC || HU;
+    __shared__ double red[kSlices][2][FP * 16];
+    __shared__ QuadStep windows[kSlices][8 * kWindow];
+    const int lane = threadIdx.x & 63, x = lane & 15, y = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int64_t lid = xcd_order(blockIdx.x, gridDim.x);
+    const int64_t pb = lid % g.npb, chunk = lid / g.npb;
+    const int64_t p0 = pb * (16 * FP);
+    const uint32_t b0 = (uint32_t)chunk * (4 * KB);
+
+    double gr[FP], gt[FP];
+#pragma unroll
+    for (int i = 0; i < FP; ++i) gr[i] = gt[i] = 0.0;
+    const int q0 = g.slice[wave], q1 = g.slice[wave + 1];
+    if (q0 < q1) {
+        double rr[FP], r2[FP], ur[SEC ? FP : 1], ut[SEC ? FP : 1];
+        Turn th[FP];
+        Anchor an[FP];
+        StepWindow<FP> win;
+        win.lds = windows[wave];
+        win.lane = lane;
+        // Set of contraction step k: pairs of steps take neighbouring sets, so
+        // that a lane's two coefficients are one 16-byte load where rows
+        // allow it.  Sets past the end count as zero.
+        auto set_of = [&](int k) -> uint32_t { return KB == 1 ? b0 + y : b0 + 8 * (k >> 1) + 2 * y + (k & 1); };
+        const bool pairs = KB > 1 && (g.B & 1) == 0 && g.vec;
+        const bool whole = b0 + 4 * KB <= g.B;
+        double gv[FP][KB]; // B[y][x]: set of k at point x
+        auto load_row = [&](const char *base, uint32_t off, double (&dst)[KB]) {
+            if (pairs) {
+#pragma unroll
+                for (int k = 0; k + 1 < KB; k += 2) {
+                    const uint32_t b = set_of(k);
+                    const d2 v = *(const d2 *)(base + (off + 8 * (whole || b < g.B ? b : 0)));
+                    dst[k] = v[0];
+                    dst[k + 1] = v[1];
+                }
+            } else {
+#pragma unroll
+                for (int k = 0; k < KB; ++k) {
+                    const uint32_t b = set_of(k);
+                    dst[k] = *(const double *)(base + (off + 8 * (whole || b < g.B ? b : 0)));
+                }
+            }
+        };
+        // zero for sets past the end, and for a row without a column (as in
+        // the forward: values are first touched here, a group after the load)
+        auto take = [&](const double (&src)[KB], bool some, bool valid, double (&dst)[KB]) {
+#pragma unroll
+            for (int k = 0; k < KB; ++k) dst[k] = src[k];
+            if (some || !whole) {
+#pragma unroll
+                for (int k = 0; k < KB; ++k) dst[k] = valid && (whole || set_of(k) < g.B) ? dst[k] : 0.0;
+            }
+        };
+#pragma unroll
+        for (int i = 0; i < FP; ++i) {
+            const int64_t p = p0 + 16 * i + x;
+            const int64_t pl = p < g.P ? p : g.P - 1;
+            rr[i] = g.r[pl];
+            r2[i] = rr[i] * rr[i];
+            th[i] = Turn(g.th[pl]);
+            an[i] = Anchor(rr[i]);
+            win.off[i] = 2 * y + an[i].high;
+            load_row((const char *)(g.g + pl * g.B), 0, gv[i]);
+            take(gv[i], false, true, gv[i]);
+            if constexpr (SEC) {
+                ur[i] = g.ur ? g.ur[pl] : 0.0;
+                ut[i] = g.ut ? g.ut[pl] : 0.0;
+            }
+        }
+        // A[x][y]: row x of the group of two entries is entry x / 8, cos or
+        // sin (x / 4) % 2, chain x % 4
+        uint32_t col;
+        auto has_row = [&](const i2 h) -> bool { return ((x & 8 ? h[1] : h[0]) >> (16 + (x & 7))) & 1; };
+        auto some_absent = [&](const i2 h) -> bool { return ((h[0] >> 16) & (h[1] >> 16)) != 255; };
+        double cur[KB], nxt[KB], curu[HU ? KB : 1], nxtu[HU ? KB : 1];
+        int e = g.quads[q0].entry_off;
+        auto load_next = [&]() {
+            if constexpr (HC) load_row((const char *)g.c, __umul24(col, 8 * g.B), nxt);
+            if constexpr (HU) load_row((const char *)g.u, __umul24(col, 8 * g.B), nxtu);
+        };
+        auto take_next = [&](const i2 h) {
+            const bool some = some_absent(h), valid = has_row(h);
+            if constexpr (HC) take(nxt, some, valid, cur);
+            if constexpr (HU) take(nxtu, some, valid, curu);
+        };
+        i2 hn = *(const i2 *)(g.hdr + e);
+        col = (uint32_t)g.cols[8 * (int64_t)e + x];
+        load_next();
+        col = (uint32_t)g.cols[8 * (int64_t)(e + 2) + x];
+        take_next(hn);
+        for (int q = q0; q < q1; ++q) {
+            const Quad *Q = g.quads + q;
+            const int alpha = Q->alpha[y];
+            const int e_end = Q->entry_end;
+            win.rows = g.steps + (int64_t)Q->step_off * 8;
+            win.fetch(win.rows);
+            Walk<J> w[FP];
+            double F[FP][2][FIRST ? 2 : 1], S[FP][2][SEC && HC ? 3 : 1]; // [point][cos | sin][i]
+#pragma unroll
+            for (int i = 0; i < FP; ++i) {
+                w[i].start();
+#pragma unroll
+                for (int f = 0; f < 2; ++f) {
+#pragma unroll
+                    for (int k = 0; k < (FIRST ? 2 : 1); ++k) F[i][f][k] = 0.0;
+#pragma unroll
+                    for (int k = 0; k < (SEC && HC ? 3 : 1); ++k) S[i][f][k] = 0.0;
+                }
+            }
+            win.start();
+            for (e = Q->entry_off; e < e_end; e += 2) {
+                const i2 hg = hn;
+                hn = *(const i2 *)(g.hdr + e + 2);
+                load_next();
+                col = (uint32_t)g.cols[8 * (int64_t)(e + 4) + x];
+                d4 H[FP], U[HU ? FP : 1];
+#pragma unroll
+                for (int i = 0; i < FP; ++i) {
+                    H[i] = d4{0, 0, 0, 0};
+                    if constexpr (HU) U[i] = d4{0, 0, 0, 0};
+                }
+#pragma unroll
+                for (int k = 0; k < KB; ++k)
+#pragma unroll
+                    for (int i = 0; i < FP; ++i) {
+                        if constexpr (HC) H[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(cur[k], gv[i][k], H[i], 0, 0, 0);
+                        if constexpr (HU) U[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(curu[k], gv[i][k], U[i], 0, 0, 0);
+                    }
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const int h = hg[j];
+                    if (h < 0x10000) continue;
+                    while (win.K < (h & 0xffff)) win.advance(w, an);
+                    const bool all = (h >> 16) == 255;
+#pragma unroll
+                    for (int f = 0; f < 2; ++f) {
+                        const bool has = (h >> (16 + 4 * f + y)) & 1;
+#pragma unroll
+                        for (int i = 0; i < FP; ++i) {
+                            if constexpr (FIRST) {
+                                double hv = (HU ? U[HU ? i : 0][2 * j + f] : H[i][2 * j + f]) * w[i].a;
+                                if (!all) {
+                                    asm volatile("");
+                                    hv = has ? hv : 0.0;
+                                }
+#pragma unroll
+                                for (int k = 0; k < 2; ++k)
+                                    F[i][f][FIRST ? k : 0] = __builtin_fma(hv, w[i].v[k], F[i][f][FIRST ? k : 0]);
+                            }
+                            if constexpr (SEC && HC) {
+                                double hv = H[i][2 * j + f] * w[i].a;
+                                if (!all) {
+                                    asm volatile("");
+                                    hv = has ? hv : 0.0;
+                                }
+#pragma unroll
+                                for (int k = 0; k < 3; ++k) S[i][f][k] = __builtin_fma(hv, w[i].v[k < J ? k : J], S[i][f][k]);
+                            }
+                        }
+                    }
+                }
+                take_next(hn);
+            }
+            // the chain's factors: w_i = d^i/dr^i r^alpha, angles, and the
+            // chain rule through s(r)
+#pragma unroll
+            for (int i = 0; i < FP; ++i) {
+                const double fa = (double)alpha;
+                double cs, sn;
+                th[i].angle(fa, cs, sn);
+                const double w0 = quad_pow(rr[i], r2[i], alpha, Q->alpha_min, Q->spread);
+                const double w1 = alpha ? fa * ipow(rr[i], alpha - 1) : 0.0;
+                const double s1 = an[i].s1;
+                // R and dR/dr summed with the cos and the sin columns' weights
+                if constexpr (FIRST) {
+                    const double zc = w0 * F[i][0][0], zs = w0 * F[i][1][0];
+                    const double rc = __builtin_fma(w0 * s1, F[i][0][FIRST ? 1 : 0], w1 * F[i][0][0]);
+                    const double rs = __builtin_fma(w0 * s1, F[i][1][FIRST ? 1 : 0], w1 * F[i][1][0]);
+                    gr[i] += __builtin_fma(rc, cs, rs * sn);
+                    gt[i] += fa * __builtin_fma(zs, cs, -(zc * sn));
+                }
+                if constexpr (SEC && HC) {
+                    const double s2 = an[i].high ? -4.0 : 4.0;
+                    const double w2 = alpha > 1 ? fa * (fa - 1.0) * ipow(rr[i], alpha - 2) : 0.0;
+                    double z[2], r1[2], r2[2];
+#pragma unroll
+                    for (int f = 0; f < 2; ++f) {
+                        z[f] = w0 * S[i][f][0];
+                        r1[f] = __builtin_fma(w0 * s1, S[i][f][1], w1 * S[i][f][0]);
+                        r2[f] = __builtin_fma(w0 * s1 * s1, S[i][f][2],
+                                              __builtin_fma(__builtin_fma(w0, s2, 2.0 * w1 * s1), S[i][f][1], w2 * S[i][f][0]));
+                    }
+                    const double zrr = __builtin_fma(r2[0], cs, r2[1] * sn);
+                    const double zrt = fa * __builtin_fma(r1[1], cs, -(r1[0] * sn));
+                    const double ztt = -fa * fa * __builtin_fma(z[0], cs, z[1] * sn);
+                    gr[i] += __builtin_fma(ur[SEC ? i : 0], zrr, ut[SEC ? i : 0] * zrt);
+                    gt[i] += __builtin_fma(ur[SEC ? i : 0], zrt, ut[SEC ? i : 0] * ztt);
+                }
+            }
+        }
+    }
+    // over the four chains of each lane column, then over the four slices
+#pragma unroll
+    for (int i = 0; i < FP; ++i) {
+        gr[i] += __shfl_xor(gr[i], 16);
+        gt[i] += __shfl_xor(gt[i], 16);
+        gr[i] += __shfl_xor(gr[i], 32);
+        gt[i] += __shfl_xor(gt[i], 32);
+        if (y == 0) {
+            red[wave][0][16 * i + x] = gr[i];
+            red[wave][1][16 * i + x] = gt[i];
+        }
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < 2 * FP * 16; e += kThreads) {
+        const int o = e / (FP * 16), pl = e % (FP * 16);
+        const int64_t p = p0 + pl;
+        if (p >= g.P) continue;
+        const double v = (red[0][o][pl] + red[1][o][pl]) + (red[2][o][pl] + red[3][o][pl]);
+        if (g.part)
+            g.part[(chunk * 2 + o) * g.P + p] = v;
+        else if (double *out = o ? g.out_t : g.out_r)
+            out[p] = v;
+    }
+}
+
+template <int FP, int KB, bool SEC, bool HU, bool HC> void launch_dot_t(DotArgs g, hipStream_t s)
+{
+    g.npb = (g.P + 16 * FP - 1) / (16 * FP);
+    const int64_t chunks = (g.B + 4 * KB - 1) / (4 * KB);
+    hipLaunchKernelGGL((dot_kernel<FP, KB, SEC, HU, HC>), dim3((unsigned)(g.npb * chunks)), dim3(kThreads), 0, s, g);
+}
+
+template <int FP, bool SEC, bool HU, bool HC> void launch_dot_k(const DotArgs &g, int kb, hipStream_t s)
+{
+    switch (kb) {
+    case 1: launch_dot_t<FP, 1, SEC, HU, HC>(g, s); break;
+    case 2: launch_dot_t<FP, 2, SEC, HU, HC>(g, s); break;
+    case 4: launch_dot_t<FP, 4, SEC, HU, HC>(g, s); break;
+    default: launch_dot_t<SEC && HU && HC ? 1 : FP, 8, SEC, HU, HC>(g, s); break; // (two blocks would spill)
+    }
+}
+
+template <bool SEC, bool HU, bool HC> void launch_dot_p(const DotArgs &g, int fp, int kb, hipStream_t s)
+{
+    if (fp == 2)
+        launch_dot_k<2, SEC, HU, HC>(g, kb, s);
+    else
+        launch_dot_k<1, SEC, HU, HC>(g, kb, s);
+}
+
 // Two workgroups of four waves per CU is what the larger tiles' registers
 // allow; a smaller point tile is taken where that would leave CUs idle.
 int64_t wanted_workgroups() { return 2 * (int64_t)std::max(1, device_cus()); }
@@ -502,6 +793,47 @@ zp_status launch_fused_fwd(const Plan &p, const double *r, const double *th, int
         }
     }
     return hip_check(hipGetLastError(), "fused forward launch");
+}
+
+// As the forward, by the sets alone.  Column-dot GEMM (basis kept) -> fused:
+// (n <= 64, 65536 points) 1104 -> 586 us with 64 sets, 1113 -> 876 with 96,
+// 1097 -> 1164 with 128; (n <= 40, 16384 points) 114 -> 78, 115 -> 113, 104 ->
+// 148 us; the derivative planes then need not be written either.
+bool fused_dot_ok(int64_t M, int64_t P, int64_t B)
+{
+    return B <= kFusedDotSets && small_rows(M, B) && (P + 15) / 16 * ((B + 3) / 4) <= INT32_MAX;
+}
+
+namespace {
+// Contraction steps of four sets per chunk: 32 sets at most (with 64 the
+// gradient's fragments alone take 64 registers and one wave fits a SIMD:
+// 155 us on n <= 64, 4257 points, 64 sets, where two chunks of 32 took 94).
+int dot_steps(int64_t B) { return B <= 4 ? 1 : B <= 8 ? 2 : B <= 16 ? 4 : 8; }
+} // namespace
+
+int64_t fused_dot_chunks(int64_t B) { return (B + 4 * dot_steps(B) - 1) / (4 * dot_steps(B)); }
+
+zp_status launch_fused_dot(const Plan &p, const double *r, const double *th, int64_t P, const double *c,
+                           const double *u, const double *ur, const double *ut, bool second, int64_t B,
+                           const double *g_up, double *part, double *out_r, double *out_t, hipStream_t s)
+{
+    const int kb = dot_steps(B);
+    const int64_t chunks = fused_dot_chunks(B);
+    DotArgs g{p.d_quads, p.d_qsteps, p.d_entry_hdr, p.d_entry_cols, p.d_slice_off, r, th, P, c, u, ur, ut, (uint32_t)B, g_up,
+              chunks > 1 ? part : nullptr, out_r, out_t, 0,
+              (((uintptr_t)c | (uintptr_t)u | (uintptr_t)g_up) & 15) == 0};
+    const int fp = (P + 31) / 32 * chunks >= wanted_workgroups() ? 2 : 1;
+    if (!second)
+        launch_dot_p<false, false, true>(g, fp, kb, s);
+    else if (u && c)
+        launch_dot_p<true, true, true>(g, fp, kb, s);
+    else if (u)
+        launch_dot_p<true, true, false>(g, fp, kb, s);
+    else
+        launch_dot_p<true, false, true>(g, fp, kb, s);
+    zp_status st = hip_check(hipGetLastError(), "fused column-dot launch");
+    if (st != ZP_OK || chunks == 1) return st;
+    return launch_coldot_reduce(part, (int)chunks, P, out_r, out_t, s);
 }
 
 } // namespace zp

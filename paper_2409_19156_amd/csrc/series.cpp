@@ -16,6 +16,8 @@
 //   4. H^T = c g^T tile by tile (K = coefficient sets) with the epilogue
 //      grad_r[p] = sum_k H^T[k][p] dZ_k/dr(p), grad_theta likewise; H is never
 //      stored.  Per-tile partial sums are reduced in a fixed order.
+//      In FP64 with few sets (fused_dot_ok) this is one kernel that needs no
+//      derivative planes (fused.hip).
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -188,6 +190,23 @@ int64_t chunk_for(int64_t M, int64_t P, int64_t B, int ct, bool fwd, bool bwd, b
             hi = mid - 1;
     }
     return std::min<int64_t>(lo * kPad, P);
+}
+
+// launch_fused_dot over chunks of points whose partial sums fit ws.
+zp_status fused_dot(const Plan &plan, const double *r, const double *th, int64_t P, const double *c, const double *u,
+                    const double *ur, const double *ut, bool second, int64_t B, const double *g, double *out_r,
+                    double *out_t, void *ws, size_t ws_bytes, hipStream_t s)
+{
+    const int64_t chunks = fused_dot_chunks(B);
+    const int64_t Pc = chunks == 1 ? P : std::min<int64_t>(P, (int64_t)(ws_bytes / (16 * (size_t)chunks)));
+    if (Pc <= 0) return set_error(ZP_ERR_WORKSPACE, "workspace smaller than the minimum (zp_series_workspace)");
+    for (int64_t p0 = 0; p0 < P; p0 += Pc) {
+        zp_status st = launch_fused_dot(plan, r + p0, th + p0, std::min(Pc, P - p0), c, u, ur ? ur + p0 : nullptr,
+                                        ut ? ut + p0 : nullptr, second, B, g + p0 * B, (double *)ws,
+                                        out_r ? out_r + p0 : nullptr, out_t ? out_t + p0 : nullptr, s);
+        if (st != ZP_OK) return st;
+    }
+    return ZP_OK;
 }
 
 zp_status common_checks(const int32_t *n, const int32_t *m, int64_t M, int64_t P, int64_t B, int32_t prec)
@@ -533,7 +552,15 @@ zp_status zp_series_bwd(const int32_t *h_n, const int32_t *h_m, int64_t M, const
     const WsLayout L(M, Pc, B, ct, false, true, have_cache);
     char *ws = (char *)d_ws;
     const int64_t Mp = L.Mp, Bp = L.Bp;
-    const bool need_rt = d_grad_r || d_grad_theta;
+    bool need_rt = d_grad_r || d_grad_theta;
+    if (need_rt && ct == CT_F64 && fused_dot_ok(M, P, B)) {
+        // dL/dr and dL/dtheta first, with the whole workspace, which is free
+        // again (in stream order) for dL/dc below
+        st = fused_dot(*plan, d_r, d_theta, P, d_c, nullptr, nullptr, nullptr, false, B, d_g, d_grad_r, d_grad_theta,
+                       ws, ws_bytes, s);
+        if (st != ZP_OK || !d_grad_c) return st;
+        need_rt = false;
+    }
     // c [Mp][Bp]: H's B operand, element (x = q, k = b), k contiguous.
     void *cbuf = ws + L.c_off;
     if (need_rt) {
@@ -868,8 +895,8 @@ zp_status zp_series_bwd2(const int32_t *h_n, const int32_t *h_m, int64_t M, cons
     const bool need_dir = d_ur != nullptr || d_ut != nullptr; // terms with ur, ut
     const bool want_rt = d_out_r || d_out_t;
     const bool run_c = d_out_c && need_dir;
-    const bool run_u = want_rt && need_u;   // column-dot of uc g^T with dZ/dr, dZ/dtheta
-    const bool run_e = want_rt && need_dir; // column-dot of c g^T with Er, Et
+    bool run_u = want_rt && need_u;   // column-dot of uc g^T with dZ/dr, dZ/dtheta
+    bool run_e = want_rt && need_dir; // column-dot of c g^T with Er, Et
     if (d_out_c && !need_dir) {
         st = launch_zero_pad(d_out_c, CT_F64, 0, 0, M, B, 0, s);
         if (st != ZP_OK) return st;
@@ -877,6 +904,14 @@ zp_status zp_series_bwd2(const int32_t *h_n, const int32_t *h_m, int64_t M, cons
     const Bwd2Layout L(M, Pc, B, ct);
     char *ws = (char *)d_ws;
     const int64_t Mp = L.Mp, Bp = L.Bp;
+    bool rt_done = false;
+    if ((run_u || run_e) && ct == CT_F64 && fused_dot_ok(M, P, B)) { // before the workspace is used otherwise
+        st = fused_dot(*plan, d_r, d_theta, P, run_e ? d_c : nullptr, run_u ? d_uc : nullptr, d_ur, d_ut, true, B, d_g,
+                       d_out_r, d_out_t, ws, ws_bytes, s);
+        if (st != ZP_OK) return st;
+        run_u = run_e = false;
+        rt_done = true;
+    }
     if (run_e) {
         st = launch_convert(d_c, M, B, B, ct, ws + L.c_off, Bp, Mp, Mp * Bp, false, s);
         if (st != ZP_OK) return st;
@@ -892,6 +927,7 @@ zp_status zp_series_bwd2(const int32_t *h_n, const int32_t *h_m, int64_t M, cons
         const int64_t pc = std::min(Pc, P - p0);
         const int64_t pcp = pad_up(pc);
         if (!run_c && !run_u && !run_e) { // the r / theta outputs of this chunk are zero
+            if (rt_done) break;
             if (d_out_r) st = launch_zero_pad(d_out_r + p0, CT_F64, 0, 0, 1, pc, 0, s);
             if (st == ZP_OK && d_out_t) st = launch_zero_pad(d_out_t + p0, CT_F64, 0, 0, 1, pc, 0, s);
             if (st != ZP_OK) return st;

@@ -67,6 +67,11 @@ zp_status launch_gemm(const GemmDesc &g, hipStream_t s);
 // Compute units of the current device (cached per device; 0 if unknown).
 int device_cus();
 
+// Largest number of sets for which the FP64 backward forms the derivative
+// planes of dL/dr and dL/dtheta inside the contraction (fused.hip).  The
+// autograd functions keep no basis up to here.
+constexpr int64_t kFusedDotSets = 96;
+
 // Series forward pieces shared by zp_series_fwd and its allocation-free
 // variant: argument checks (ZP_OK also for the M, P or B == 0 no-op), the
 // smallest workspace without a cache, and the work itself for a plan whose
@@ -92,6 +97,17 @@ bool series_fwd_fused(int64_t M, int64_t P, int64_t B, int32_t prec);
 bool fused_fwd_ok(int64_t M, int64_t P, int64_t B, bool dir);
 zp_status launch_fused_fwd(const Plan &p, const double *r, const double *th, int64_t P, const double *c,
                            const double *c2, const double *tr, const double *tt, int64_t B, double *f, hipStream_t s);
+
+// First order (second = false): out_r[p] = sum_b g[p][b] sum_k dZ_k/dr c[k][b], out_t with dZ_k/dtheta.
+// Second order: the same with u in place of c (if u), plus the sums of the
+// second-order planes Er, Et along (ur, ut) with c (if c).  out_r, out_t
+// nullable.  part: 16 fused_dot_chunks(B) P bytes, needed when there is more
+// than one chunk.
+bool fused_dot_ok(int64_t M, int64_t P, int64_t B);
+int64_t fused_dot_chunks(int64_t B);
+zp_status launch_fused_dot(const Plan &p, const double *r, const double *th, int64_t P, const double *c,
+                           const double *u, const double *ur, const double *ut, bool second, int64_t B,
+                           const double *g, double *part, double *out_r, double *out_t, hipStream_t s);
 
 // dst (compute type, [R_pad][C_pad] or transposed [C_pad][R_pad]) from a
 // row-major FP64 src [R][C] (leading dimension lds); zero padding.

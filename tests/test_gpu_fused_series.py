@@ -100,6 +100,60 @@ def test_forward_and_forward_mode(zp, oracle_mod, modes, P, B):
         _close(tf, ref, bound, f"tf {use_c}{use_r}{use_t}")
 
 
+@pytest.mark.parametrize("modes,P,B", CASES)
+def test_backward_and_second_order(zp, oracle_mod, modes, P, B):
+    rng, n, m, r, th, c = _case(modes, P, B)
+    print(f"fused backward: {modes} M={n.size} P={P} B={B}", flush=True)
+    g = rng.standard_normal((P, B))
+    Z, Zr, Zt = oracle_mod.series_basis(n, m, r, th)
+    Zrr = oracle_mod.basis(n, m, r, th, 4)[0]
+    a = np.abs(m).astype(np.float64)[:, None]
+    R1 = oracle_mod.radial(n, m, r, 1)[1]
+    Zrt = np.where(m[:, None] >= 0, -a * np.sin(a * th), a * np.cos(a * th)) * R1
+    Ztt = -a * a * Z
+    t0, t1, t2 = 2e-13 + 0 * n, 2e-13 * (n + 1.0) ** 2, 2e-13 * (n + 1.0)
+    t11, t20, t02 = 2e-13 * (n + 1.0) ** 3, 2e-13 * (n + 1.0) ** 4, 2e-13 * (n + 1.0) ** 2
+    ag, ac = np.abs(g), np.abs(c)
+    dot = lambda d, x: (g * (d.T @ x)).sum(1)  # noqa: E731
+    bnd = lambda t, x: ag @ (t @ np.abs(x)) + 1e-300  # noqa: E731
+    gc, gr, gt = zp.series_backward(n, m, _dev(r), _dev(th), _dev(c), _dev(g), "fp64")
+    _close(gr, dot(Zr, c), bnd(t1, c), "grad_r")
+    _close(gt, dot(Zt, c), bnd(t2, c), "grad_theta")
+    _close(gc, Z @ g, t0[:, None] * ag.sum(0)[None, :] + 1e-300, "grad_c")
+    uc = rng.standard_normal(c.shape) / (n + 1.0)[:, None]
+    ur, ut = rng.standard_normal(P), rng.standard_normal(P)
+    for wc, wr, wt in ((1, 1, 1), (1, 0, 0), (0, 1, 0), (0, 0, 1)):
+        D = wr * ur * Zr + wt * ut * Zt
+        tD = wr * np.abs(ur) * t1[:, None] + wt * np.abs(ut) * t2[:, None]  # [M, P]
+        og, oc, orr, ot = zp.series_backward2(n, m, _dev(r), _dev(th), _dev(c), _dev(g), _dev(uc) if wc else None,
+                                              _dev(ur) if wr else None, _dev(ut) if wt else None, "fp64")
+        what = f"{wc}{wr}{wt}"
+        _close(orr, wc * dot(Zr, uc) + dot(wr * ur * Zrr + wt * ut * Zrt, c),
+               wc * bnd(t1, uc) + wr * np.abs(ur) * bnd(t20, c) + wt * np.abs(ut) * bnd(t11, c), "out_r " + what)
+        _close(ot, wc * dot(Zt, uc) + dot(wr * ur * Zrt + wt * ut * Ztt, c),
+               wc * bnd(t2, uc) + wr * np.abs(ur) * bnd(t11, c) + wt * np.abs(ut) * bnd(t02, c), "out_t " + what)
+        _close(oc, D @ g, tD @ ag + 1e-300, "out_c " + what)
+        _close(og, wc * (Z.T @ uc) + D.T @ c, wc * t0[0] * np.abs(uc).sum(0)[None, :] + tD.T @ ac + 1e-300,
+               "out_g " + what)
+
+
+def test_backward_rows_and_smallest_workspace(zp):
+    """dL/dr and dL/dtheta of a point do not depend on the other points, and
+    with the smallest workspace every gradient is the full workspace's."""
+    rng, n, m, r, th, c = _case("ansi12", 3000, 70)
+    g = _dev(rng.standard_normal((3000, 70)))
+    rd, td, cd = _dev(r), _dev(th), _dev(c)
+    gc, gr, gt = zp.series_backward(n, m, rd, td, cd, g, "fp64")
+    for P in (1, 31, 700):
+        _, a, b = zp.series_backward(n, m, rd[:P], td[:P], cd, g[:P], "fp64")
+        assert torch.equal(a, gr[:P]) and torch.equal(b, gt[:P]), P
+    _, mn, _ = zp.series_sizes(n.size, 3000, 70, "fp64")
+    ws = torch.empty(mn, dtype=torch.uint8, device="cuda")
+    gc2, gr2, gt2 = zp.series_backward(n, m, rd, td, cd, g, "fp64", ws=ws)
+    assert torch.equal(gr2, gr) and torch.equal(gt2, gt)
+    assert ((gc2 - gc).abs().max() / gc.abs().max()).item() <= 1e-13
+
+
 def test_forward_rows_and_caches(zp):
     """A point's row does not depend on the other points or on whether the
     basis is kept; NaN and infinite inputs stay in their rows and columns."""
