@@ -308,9 +308,9 @@ __device__ __forceinline__ void gemm_body(const GemmDesc &g)
     const int64_t j0 = (int64_t)by * BN;
 
     // k range of this workgroup (split-K along the third grid dimension)
-    const int64_t kchunk = g.K / g.splits;
+    const int64_t kchunk = g.kchunk;
     const int64_t kbeg = (int64_t)bz * kchunk;
-    const int ntiles = (int)(kchunk / BK);
+    const int ntiles = (int)((kbeg + kchunk < g.K ? kchunk : g.K - kbeg) / BK);
 
     using Acc = typename std::conditional<CT == CT_F64, d4, f4>::type;
     Acc acc[FM][FN];
@@ -899,11 +899,14 @@ int coldot_bm(int ct)
     return ct == CT_F64 ? Cfg<CT_F64>::BM : ct == CT_F32 ? Cfg<CT_F32>::BM : Cfg<CT_BF3>::BM;
 }
 
-zp_status launch_gemm(const GemmDesc &g, hipStream_t s)
+zp_status launch_gemm(const GemmDesc &desc, hipStream_t s)
 {
+    GemmDesc g = desc;
     if (g.M <= 0 || g.N <= 0) return ZP_OK;
-    if (g.K % kPad != 0 || g.splits < 1 || (g.K / g.splits) % kPad != 0 || g.K / g.splits * g.splits != g.K)
-        return set_error(ZP_ERR_ARG, "internal: GEMM K split is not a multiple of the pad");
+    if (g.K % kPad != 0 || g.K <= 0 || g.splits < 1)
+        return set_error(ZP_ERR_ARG, "internal: GEMM K is not a multiple of the pad");
+    g.kchunk = (g.K / kPad + g.splits - 1) / g.splits * kPad;
+    if ((g.splits - 1) * g.kchunk >= g.K) return set_error(ZP_ERR_ARG, "internal: GEMM K split leaves a split empty");
     if (g.ct == CT_BF3 ? false : (g.a.lay == LAY_KB8 || g.b.lay == LAY_KB8))
         return set_error(ZP_ERR_ARG, "internal: k-blocked operands are bf16 only");
     hipError_t e;

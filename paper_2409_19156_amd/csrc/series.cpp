@@ -72,18 +72,17 @@ struct CacheLayout {
     }
 };
 
-// Split-K count for grad_c: enough workgroups to fill the chip several times,
-// preferring a count that is a whole number of waves over the 256 CUs (one
-// workgroup per CU at a time), each split a whole number of pads and at least
-// kMinSplitPads of them: shorter splits spend more on writing and reducing
-// their partial sums than they gain in parallelism (n <= 64 on 8192 points:
-// 32 -> 8 splits made forward + backward 3-12% faster; n <= 40 on 16384
-// points: 64 -> 16 splits, 2%).
+// Split-K count for grad_c on large problems: enough workgroups to fill the
+// chip several times, preferring a count that is a whole number of waves over
+// the 256 CUs (one workgroup per CU at a time), each split a whole number of
+// pads and at least kMinSplitPads of them: shorter splits spend more on
+// writing and reducing their partial sums than they gain in parallelism (n <=
+// 64 on 8192 points: 32 -> 8 splits made forward + backward 3-12% faster; n <=
+// 40 on 16384 points: 64 -> 16 splits, 2%).
 constexpr int64_t kMinSplitPads = 8;
 
-int splits_for(int64_t M, int64_t B, int64_t Kp, int ct)
+int splits_large(int64_t M, int64_t B, int64_t Kp)
 {
-    (void)ct;
     const int64_t tiles = ((M + 127) / 128) * ((B + 127) / 128);
     const int64_t units = Kp / kPad;
     int best = 1;
@@ -103,6 +102,49 @@ int splits_for(int64_t M, int64_t B, int64_t Kp, int ct)
     return best;
 }
 
+// Split-K count for grad_c: the one above, unless few output tiles leave the
+// chip idle with it.  Model of a split count s, with n workgroups on the
+// busiest CU and q pads per split: q max(alone, n busy) + the partial sums
+// written and read back, where a pad (128 k of one tile) takes `alone` us in a
+// workgroup that has its CU to itself and `busy` us of a full CU's time (from
+// the contractions of n <= 64 on 65536 points: 4390, 2570 and 1972 us; alone:
+// 34 workgroups took 157 us for 17 pads in FP64).  Another count is taken
+// when the model gives it a tenth less: analysis n <= 64, 4257 points, 64
+// sets: 2 -> 12 splits of at most 3 pads, FP64 contraction 157 -> 39 us; n <=
+// 40, 16384 points, 64 sets: 16 -> 32 splits, dL/dc 88 -> 56 us.
+int splits_for(int64_t M, int64_t B, int64_t Kp, int ct)
+{
+    const int large = splits_large(M, B, Kp);
+    const int64_t units = Kp / kPad;
+    const int64_t bn = ct == CT_BF3 ? 128 : 64; // the contraction's tile width (FP64: on problems this size)
+    const double alone = ct == CT_F64 ? 9.2 : ct == CT_F32 ? 6.0 : 8.0;
+    const double busy = ct == CT_F64 ? 8.1 : ct == CT_F32 ? 4.7 : 7.3;
+    const int64_t tiles = ((M + 127) / 128) * ((B + bn - 1) / bn);
+    auto cost = [&](int64_t s) {
+        const double n = (double)((tiles * s + 255) / 256), q = (double)((units + s - 1) / s);
+        return q * std::max(alone, busy * n) + (double)s * (double)M * (double)B * 16.0 / 4e6;
+    };
+    int best = large;
+    double best_cost = 0.9 * cost(large);
+    for (int64_t q = 1; q <= units && q <= 64; ++q) { // pads per split
+        const int64_t s = (units + q - 1) / q;
+        if (s > 128 || cost(s) >= best_cost) continue;
+        best_cost = cost(s);
+        best = (int)s;
+    }
+    return best;
+}
+
+// The count used with a workspace laid out for S_room splits.  (units over
+// pads per split, rounded up, so that no split is empty.)
+int splits_within(int64_t M, int64_t B, int64_t Kp, int ct, int S_room)
+{
+    const int64_t units = Kp / kPad;
+    const int64_t s = std::min<int64_t>(splits_for(M, B, Kp, ct), S_room);
+    const int64_t q = (units + s - 1) / s;
+    return (int)((units + q - 1) / q);
+}
+
 // Workspace for one chunk of Pc points.
 //   c      : coefficients in the contraction type, [Mp][Bp]; for the bf16
 //            forward transposed and in chain-major mode order, [Bp][Mp]
@@ -115,13 +157,14 @@ struct WsLayout {
     int64_t Mp, Bp, Pcp;
     int S, T;
     size_t c_off, z_off, zr_off, zt_off, g_off, gt_off, pc_off, pr_off, total;
-    WsLayout(int64_t M, int64_t Pc, int64_t B, int ct, bool fwd, bool bwd, bool have_cache)
+    // few: room for splits_large splits only, which every workspace accepted has
+    WsLayout(int64_t M, int64_t Pc, int64_t B, int ct, bool fwd, bool bwd, bool have_cache, bool few = true)
     {
         Mp = pad_up(M);
         Bp = pad_up(B);
         Pcp = pad_up(Pc);
         const size_t e = ct_bytes(ct);
-        S = splits_for(M, B, Pcp, ct);
+        S = few ? splits_large(M, B, Pcp) : std::max(splits_large(M, B, Pcp), splits_for(M, B, Pcp, ct));
         T = (int)((M + coldot_bm(ct) - 1) / coldot_bm(ct));
         size_t o = 0;
         c_off = o;
@@ -351,7 +394,7 @@ zp_status zp_series_workspace(int64_t M, int64_t P, int64_t B, int32_t prec, siz
     // Sized for the most demanding use: backward without a cache, or the
     // forward-mode derivative.
     const int64_t P1 = std::min<int64_t>(P, kPad);
-    *full_bytes = std::max({WsLayout(M, P, B, ct, true, true, false).total, JvpLayout(M, P, B, ct).total, (size_t)256});
+    *full_bytes = std::max({WsLayout(M, P, B, ct, true, true, false, false).total, JvpLayout(M, P, B, ct).total, (size_t)256});
     if (min_bytes)
         *min_bytes = std::max({WsLayout(M, P1, B, ct, true, true, false).total, JvpLayout(M, P1, B, ct).total, (size_t)256});
     return ZP_OK;
@@ -549,7 +592,10 @@ zp_status zp_series_bwd(const int32_t *h_n, const int32_t *h_m, int64_t M, const
     st = get_plan(h_n, h_m, M, &plan);
     if (st != ZP_OK) return st;
 
-    const WsLayout L(M, Pc, B, ct, false, true, have_cache);
+    // room for the partial sums of as many splits as are wanted, if it is there
+    // with the basis in the workspace (so that a cache changes no sum)
+    const bool few = WsLayout(M, Pc, B, ct, false, true, false, false).total > ws_bytes;
+    const WsLayout L(M, Pc, B, ct, false, true, have_cache, few);
     char *ws = (char *)d_ws;
     const int64_t Mp = L.Mp, Bp = L.Bp;
     bool need_rt = d_grad_r || d_grad_theta;
@@ -571,12 +617,17 @@ zp_status zp_series_bwd(const int32_t *h_n, const int32_t *h_m, int64_t M, const
     const size_t zsz = zsize_of(ct);
     // With one chunk and few output tiles (fewer than eight per CU), the
     // dL/dr, dL/dtheta contraction runs on the helper stream beside the dL/dc
-    // contraction, since neither fills the chip alone: the n <= 40 series
-    // (896 tiles) went 0.61 -> 0.56 ms, n <= 64 on 8192 points (1088 tiles)
-    // 4-7% faster; n <= 64 on 65536 points (8704 tiles) lost 5% with the
-    // overlap and keeps one stream.
+    // contraction, since neither fills the chip alone, unless both are so
+    // short that the events cost more than the overlap gives.  Side by side
+    // against in order, FP64 / FP32 / bf16 x 3: n <= 64, 4096 points, 1024 sets
+    // 625 / 455 / 319 against 690 / 457 / 363 us; 2048 points, 512 sets 198 /
+    // 140 / 113 against 235 / 160 / 135; n <= 40, 16384 points, 64 sets (9e8
+    // products) - / 121 / 132 against - / 111 / 122; n <= 24, 2048 points, 192
+    // sets 75 / 57 / 71 against 62 / 44 / 52.  n <= 64 on 65536 points (8704
+    // tiles) lost 5% with the overlap.
     const int64_t rt_tiles = ((M + 127) / 128) * ((Pc + 127) / 128);
-    ChunkPipe side(s, d_grad_c && need_rt && Pc >= P && rt_tiles < 8 * (int64_t)device_cus());
+    const bool overlap = rt_tiles < 8 * (int64_t)device_cus() && (double)M * (double)Pc * (double)B >= 1.5e9;
+    ChunkPipe side(s, d_grad_c && need_rt && Pc >= P && overlap);
     for (int64_t p0 = 0; p0 < P; p0 += Pc) {
         const int64_t pc = std::min(Pc, P - p0);
         const int64_t pcp = pad_up(pc);
@@ -627,7 +678,7 @@ zp_status zp_series_bwd(const int32_t *h_n, const int32_t *h_m, int64_t M, const
             g.M = M;
             g.N = B;
             g.K = pcp;
-            g.splits = splits_for(M, B, pcp, ct);
+            g.splits = splits_within(M, B, pcp, ct, L.S);
             g.epi = EPI_PARTIAL;
             g.C = (double *)(ws + L.pc_off);
             g.ldc = B;
@@ -806,13 +857,13 @@ struct Bwd2Layout {
     int64_t Mp, Bp, Pcp;
     int S, T;
     size_t c_off, u_off, d_off, zr_off, zt_off, er_off, et_off, g_off, gt_off, pc_off, pr_off, total;
-    Bwd2Layout(int64_t M, int64_t Pc, int64_t B, int ct)
+    Bwd2Layout(int64_t M, int64_t Pc, int64_t B, int ct, bool few = true)
     {
         Mp = pad_up(M);
         Bp = pad_up(B);
         Pcp = pad_up(Pc);
         const size_t e = ct_bytes(ct), dsz = dsize_of(ct);
-        S = splits_for(M, B, Pcp, ct);
+        S = few ? splits_large(M, B, Pcp) : std::max(splits_large(M, B, Pcp), splits_for(M, B, Pcp, ct));
         T = (int)((M + coldot_bm(ct) - 1) / coldot_bm(ct));
         size_t o = 0;
         c_off = o;
@@ -866,7 +917,7 @@ zp_status zp_series_bwd2_workspace(int64_t M, int64_t P, int64_t B, int32_t prec
     if (prec < ZP_FP64 || prec > ZP_BF16X3) return set_error(ZP_ERR_PREC, "unknown prec");
     const int ct = ct_of(prec);
     const int64_t P1 = std::min<int64_t>(P, kPad);
-    *full_bytes = std::max({Bwd2Layout(M, P, B, ct).total, JvpLayout(M, P, B, ct).total, (size_t)256});
+    *full_bytes = std::max({Bwd2Layout(M, P, B, ct, false).total, JvpLayout(M, P, B, ct).total, (size_t)256});
     if (min_bytes) *min_bytes = std::max({Bwd2Layout(M, P1, B, ct).total, JvpLayout(M, P1, B, ct).total, (size_t)256});
     return ZP_OK;
 }
@@ -901,7 +952,7 @@ zp_status zp_series_bwd2(const int32_t *h_n, const int32_t *h_m, int64_t M, cons
         st = launch_zero_pad(d_out_c, CT_F64, 0, 0, M, B, 0, s);
         if (st != ZP_OK) return st;
     }
-    const Bwd2Layout L(M, Pc, B, ct);
+    const Bwd2Layout L(M, Pc, B, ct, Bwd2Layout(M, Pc, B, ct, false).total > ws_bytes);
     char *ws = (char *)d_ws;
     const int64_t Mp = L.Mp, Bp = L.Bp;
     bool rt_done = false;
@@ -983,7 +1034,7 @@ zp_status zp_series_bwd2(const int32_t *h_n, const int32_t *h_m, int64_t M, cons
             g.M = M;
             g.N = B;
             g.K = pcp;
-            g.splits = splits_for(M, B, pcp, ct);
+            g.splits = splits_within(M, B, pcp, ct, L.S);
             g.epi = EPI_PARTIAL;
             g.C = (double *)(ws + L.pc_off);
             g.ldc = B;

@@ -44,7 +44,8 @@ struct GemmDesc {
     int ct;
     Operand a, b;
     int64_t M, N, K; // output M x N (unpadded); K a multiple of kPad
-    int splits;      // split-K count (EPI_PARTIAL)
+    int splits;      // split-K count (EPI_PARTIAL); the last split may be shorter
+    int64_t kchunk;  // k per split (set by launch_gemm)
     int epi;
     double *C;
     int64_t ldc;
