@@ -1,7 +1,8 @@
 // FP64 Zernike series without a stored basis: the recurrence runs inside the
 // contraction, and its values go from the lane that forms them straight into
 // an FP64 MFMA operand (forward and forward-mode derivative) or weigh what an
-// MFMA returns to it (column dots of the backward).
+// MFMA returns to it (column dots of the backward); the coefficient gradient
+// passes them through a wave's own piece of LDS.
 //
 // MFMA 16x16x4 (FP64): lane l = x + 16 y (x < 16, y < 4) supplies A[x][y] and
 // B[y][x] and receives D[y + 4 t][x], t = 0..3.
@@ -14,8 +15,12 @@
 // Column dots (dot_kernel): D = modes x points, H = c g^T for two degrees at a
 // time: D[y + 4 t][x] is the cos (t even) or sin column of degree t / 2 on
 // chain y at point x, so lane (x, y) receives exactly the modes of the chain
-// that it walks itself, and weighs them with its own recurrence values.  Over a chain only the sums of H v^(i) are kept;
-// the powers, angles and chain-rule factors are applied once per chain.
+// that it walks itself, and weighs them with its own recurrence values.  Over
+// a chain only the sums of H v^(i) are kept; the powers, angles and chain-rule
+// factors are applied once per chain.
+// Coefficient gradient (grad_kernel): D = modes x sets, contracted over
+// points.  A lane walks whole chains at its own point and a wave collects 16
+// modes x 64 points in LDS, read back as A[mode][point].
 //
 // Arithmetic of the walk: as the basis kernel (chain_kernel.hip).
 #include <hip/hip_runtime.h>
@@ -751,6 +756,297 @@ template <bool SEC, bool HU, bool HC> void launch_dot_p(const DotArgs &g, int fp
         launch_dot_k<1, SEC, HU, HC>(g, kb, s);
 }
 
+// --------------------------------------------------- coefficient gradient --
+
+struct GradArgs {
+    const Chain *chains; // whole chains in emission order
+    const int32_t *row_chain;
+    const Coef *coefs;
+    const Emit *emits;
+    const double *r, *th;
+    int64_t P, M;
+    const double *wq;      // nullable: per-point weight of g
+    const double *tr, *tt; // DIR
+    const double *g;
+    uint32_t B;
+    int splits;
+    int64_t tiles, batches; // row tiles; 64-point batches per split (a multiple of four)
+    double *out;            // [split][M][B]
+    int norm;               // divide by the modes' norms (one split only)
+};
+
+// (2 (n + 1)) / (eps_m pi): one over the integral of Z^2 over the disc.
+__device__ __forceinline__ double inv_norm(int K, int alpha)
+{
+    const double inv_pi = 0.318309886183790671537767526745028724;
+    return (alpha == 0 ? 1.0 : 2.0) * (double)(2 * K + alpha + 1) * inv_pi;
+}
+
+constexpr int kLd = 66;         // LDS row stride: rows 4 banks apart, the fragment read is conflict-free
+constexpr int kStageSteps = 160; // recurrence steps of a tile kept in LDS
+
+// One row of a tile's program: steps to take on its chain before the row,
+// flags, and the low-anchor factor.
+struct Row {
+    int32_t hdr; // steps | sin << 10 | first of its chain << 11 | alpha << 12 | valid << 22
+    int32_t pad;
+    double a_lo;
+};
+
+// R row tiles of 16 modes (consecutive emissions) x FN tiles of 16 sets per
+// workgroup; its four waves take every fourth batch of 64 points of its split
+// and add their sums through LDS at the end.  A lane walks whole chains at its
+// own point: the rows of a tile then need not belong to chains of one length.  The rows' program and the
+// recurrence coefficients in the order the walk takes them are staged in LDS
+// once per workgroup (a tile whose chains need more than kStageSteps reads
+// the coefficients from memory).
+//
+// Bound by vector and MFMA cycles in turn and by the LDS round trip between
+// them, at two or three waves per SIMD; R = 2 is the tile that fits there
+// (one row tile: 388 against 347 us on n <= 64, 65536 points, 1 set; four:
+// 338).  Six workgroups per CU are launched, so that the uneven tiles even
+// out.  That case took 830 us with the basis stored.
+template <int R, int FN, bool DIR>
+__global__ __launch_bounds__(kThreads, DIR || FN > 1 ? 2 : 3) void grad_kernel(GradArgs g)
+{
+    constexpr int J = DIR ? 1 : 0;
+    __shared__ double buf[kSlices * 16 * (16 * FN > kLd ? 16 * FN : kLd)];
+    __shared__ Row prog[16 * R];
+    __shared__ Coef stage[kStageSteps + 2];
+    __shared__ int row_coef[16 * R]; // coefficient index of a row's first step
+    __shared__ int total_steps;
+    const int lane = threadIdx.x & 63, x = lane & 15, y = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int64_t lid = xcd_order(blockIdx.x, gridDim.x);
+    const int64_t tile = lid % g.tiles, rest = lid / g.tiles;
+    const int64_t split = rest % g.splits;
+    const uint32_t b0 = (uint32_t)(rest / g.splits) * (16 * FN);
+    const int e0 = (int)tile * (16 * R);
+    double *zl = buf + wave * (16 * kLd);
+
+    // the tile's program: row t is emission e0 + t
+    if ((int)threadIdx.x < 16 * R) {
+        const int e = e0 + (int)threadIdx.x;
+        Row rw{0, 0, 0.0};
+        int first = 0;
+        if (e < g.M) {
+            int ci = g.row_chain[e >> 4];
+            while (e >= g.chains[ci].emit_off + g.chains[ci].emit_cnt) ++ci;
+            const Chain ch = g.chains[ci];
+            const Emit em = g.emits[e];
+            const bool fresh = e == e0 || e == ch.emit_off;
+            const int before = fresh ? 0 : g.emits[e - 1].K; // degree reached by the row before
+            rw.hdr = (em.K - before) | (em.flags & 1) << 10 | (fresh ? 1 << 11 : 0) | ch.alpha << 12 | 1 << 22;
+            rw.a_lo = em.a_lo;
+            first = ch.coef_off + before;
+        }
+        prog[threadIdx.x] = rw;
+        row_coef[threadIdx.x] = first;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int n = 0;
+        for (int t = 0; t < 16 * R; ++t) n += prog[t].hdr & 1023;
+        total_steps = n;
+    }
+    __syncthreads();
+    const bool staged = total_steps <= kStageSteps;
+    if (staged && (int)threadIdx.x < 16 * R) { // each row's steps to its place in the stream
+        int at = 0;
+        for (int t = 0; t < (int)threadIdx.x; ++t) at += prog[t].hdr & 1023;
+        const int n = prog[threadIdx.x].hdr & 1023;
+        for (int k = 0; k < n; ++k) stage[at + k] = g.coefs[row_coef[threadIdx.x] + k];
+    }
+    __syncthreads();
+    // lane t keeps row t of the program; the walk reads it lane by lane
+    const Row mine = prog[lane < 16 * R ? lane : 0];
+    const int a_lo_lo = (int)__builtin_bit_cast(int64_t, mine.a_lo), a_lo_hi = (int)(__builtin_bit_cast(int64_t, mine.a_lo) >> 32);
+
+    d4 acc[R][FN];
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+#pragma unroll
+        for (int n = 0; n < FN; ++n) acc[i][n] = d4{0, 0, 0, 0};
+
+    uint32_t bo[FN]; // this lane's sets in a row, in bytes; those past the end are not stored
+#pragma unroll
+    for (int n = 0; n < FN; ++n) bo[n] = 8 * (b0 + 16 * n + x < g.B ? b0 + 16 * n + x : g.B - 1);
+    const int64_t nb = (g.P + 63) / 64;
+    const int64_t bt1 = std::min(nb, (split + 1) * g.batches);
+    // the batch's own point, loaded a batch ahead
+    double xr = 0, xt = 0, tr = 0, tt = 0;
+    auto load_point = [&](int64_t bt) {
+        const int64_t p = bt * 64 + lane, pl = p < g.P ? p : g.P - 1;
+        xr = g.r[pl];
+        xt = g.th[pl];
+        if constexpr (DIR) {
+            tr = g.tr ? g.tr[pl] : 0.0;
+            tt = g.tt ? g.tt[pl] : 0.0;
+        }
+    };
+    int64_t bt = split * g.batches + wave;
+    if (bt < bt1) load_point(bt);
+    for (; bt < bt1; bt += kSlices) {
+        const int64_t pb = bt * 64;
+        const double r = xr, tgr = tr, tgt = tt;
+        const Turn th(xt);
+        // B[y][x]: point pb + 4 k + y, set b0 + 16 n + x; rows past the last
+        // point repeat it and count as zero below
+        const uint32_t last = g.P - pb < 64 ? (uint32_t)(g.P - pb) - 1 : 63;
+        const char *gb = (const char *)(g.g + pb * g.B);
+        double gv[16][FN];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const uint32_t row = __umul24(std::min<uint32_t>(4 * k + y, last), 8 * g.B);
+#pragma unroll
+            for (int n = 0; n < FN; ++n) gv[k][n] = *(const double *)(gb + (row + bo[n]));
+        }
+        if (bt + kSlices < bt1) load_point(bt + kSlices);
+        const Anchor an(r);
+        int at = 0; // next step of the stream
+        Coef q = stage[0];
+        double wc = 0, wsn = 0, kc0 = 0, kc1 = 0, ks0 = 0, ks1 = 0;
+        Walk<J> w;
+        w.start();
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+#pragma unroll 2
+            for (int row = 0; row < 16; ++row) {
+                const int h = __builtin_amdgcn_readlane(mine.hdr, 16 * i + row);
+                double val = 0.0; // rows past the last mode
+                if (h) {
+                    if (h & 2048) { // a chain's first mode of this tile
+                        const int alpha = (h >> 12) & 1023;
+                        const double fa = (double)alpha;
+                        double cs, sn;
+                        th.angle(fa, cs, sn);
+                        const double w0 = ipow(r, alpha);
+                        wc = w0 * cs;
+                        wsn = w0 * sn;
+                        if constexpr (DIR) {
+                            const double w1 = alpha ? fa * ipow(r, alpha - 1) : 0.0;
+                            kc0 = __builtin_fma(tgr, w1 * cs, -(tgt * fa) * wsn);
+                            ks0 = __builtin_fma(tgr, w1 * sn, (tgt * fa) * wc);
+                            kc1 = tgr * an.s1 * wc;
+                            ks1 = tgr * an.s1 * wsn;
+                        }
+                        w.start();
+                    }
+                    const int n = h & 1023;
+                    if (staged) {
+                        for (int k = 0; k < n; ++k) {
+                            const Coef now_q = q;
+                            q = stage[++at];
+                            w.step(an.high ? now_q.cc_hi : now_q.cc_lo, an.high ? now_q.bs_hi : now_q.bs_lo, an.s);
+                        }
+                    } else {
+                        const Coef *cf = g.coefs + __builtin_amdgcn_readfirstlane(row_coef[16 * i + row]);
+                        for (int k = 0; k < n; ++k)
+                            w.step(an.high ? cf[k].cc_hi : cf[k].cc_lo, an.high ? cf[k].bs_hi : cf[k].bs_lo, an.s);
+                    }
+                    const int64_t bits = (int64_t)(uint32_t)__builtin_amdgcn_readlane(a_lo_lo, 16 * i + row) |
+                                         (int64_t)__builtin_amdgcn_readlane(a_lo_hi, 16 * i + row) << 32;
+                    const double a = an.high ? 1.0 : __builtin_bit_cast(double, bits);
+                    const double av = a * w.v[0];
+                    const bool is_sin = h & 1024;
+                    if constexpr (DIR) {
+                        const double av1 = a * w.v[J];
+                        val = is_sin ? __builtin_fma(ks0, av, ks1 * av1) : __builtin_fma(kc0, av, kc1 * av1);
+                    } else {
+                        val = (is_sin ? wsn : wc) * av;
+                    }
+                }
+                zl[row * kLd + lane] = val;
+            }
+            if (i == 0) { // the gradient's weights, and zeros past the last point
+                if (g.wq) {
+#pragma unroll
+                    for (int k = 0; k < 16; ++k) {
+                        const double wgt = g.wq[pb + std::min<uint32_t>(4 * k + y, last)];
+#pragma unroll
+                        for (int n = 0; n < FN; ++n) gv[k][n] *= wgt;
+                    }
+                }
+                if (last < 63) {
+#pragma unroll
+                    for (int k = 0; k < 16; ++k)
+#pragma unroll
+                        for (int n = 0; n < FN; ++n) gv[k][n] = 4 * k + y <= (int)last ? gv[k][n] : 0.0;
+                }
+            }
+            wave_lds_order();
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                const double a = zl[x * kLd + 4 * k + y];
+#pragma unroll
+                for (int n = 0; n < FN; ++n)
+                    acc[i][n] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, gv[k][n], acc[i][n], 0, 0, 0);
+            }
+            wave_lds_order();
+        }
+    }
+    constexpr int C = 16 * FN;
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        __syncthreads();
+#pragma unroll
+        for (int n = 0; n < FN; ++n)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) buf[wave * 16 * C + (y + 4 * t) * C + 16 * n + x] = acc[i][n][t];
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < FN; ++k) {
+            const int el = k * kThreads + (int)threadIdx.x;
+            const int64_t e = e0 + 16 * i + el / C;
+            const uint32_t b = b0 + el % C;
+            if (e >= g.M || b >= g.B) continue;
+            double v = (buf[el] + buf[16 * C + el]) + (buf[32 * C + el] + buf[48 * C + el]);
+            const Emit em = g.emits[e];
+            if (g.norm) {
+                int lo = g.row_chain[e >> 4]; // the chain of emission e: at or after that of its row's first
+                while (e >= g.chains[lo].emit_off + g.chains[lo].emit_cnt) ++lo;
+                v *= inv_norm(em.K, g.chains[lo].alpha);
+            }
+            g.out[(split * g.M + em.col) * g.B + b] = v;
+        }
+    }
+}
+
+template <int R, int FN, bool DIR> void launch_grad_t(const GradArgs &g, int64_t nsb, hipStream_t s)
+{
+    hipLaunchKernelGGL((grad_kernel<R, FN, DIR>), dim3((unsigned)(g.tiles * g.splits * nsb)), dim3(kThreads), 0, s, g);
+}
+
+template <int R, bool DIR> void launch_grad_n(const GradArgs &g, int fn, int64_t nsb, hipStream_t s)
+{
+    if (fn == 2)
+        launch_grad_t<R, 2, DIR>(g, nsb, s);
+    else
+        launch_grad_t<R, 1, DIR>(g, nsb, s);
+}
+
+// out[m][b] = sum over splits, in order; norm: times the inverse mode norms.
+__global__ __launch_bounds__(kThreads) void grad_reduce_kernel(const double *__restrict__ part, int S, int64_t M,
+                                                               int64_t B, const Chain *chains,
+                                                               const int32_t *row_chain, const Emit *emits, int norm,
+                                                               double *__restrict__ out)
+{
+    const int64_t b = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    const int64_t e = b / B; // emission, set b - e B
+    if (e >= M) return;
+    const Emit em = emits[e];
+    const int64_t o = em.col * B + (b - e * B);
+    double v = 0.0;
+#pragma unroll 4
+    for (int k = 0; k < S; ++k) v += part[k * M * B + o];
+    if (norm) {
+        int lo = row_chain[e >> 4];
+        while (e >= chains[lo].emit_off + chains[lo].emit_cnt) ++lo;
+        v *= inv_norm(em.K, chains[lo].alpha);
+    }
+    out[o] = v;
+}
+
 // Two workgroups of four waves per CU is what the larger tiles' registers
 // allow; a smaller point tile is taken where that would leave CUs idle.
 int64_t wanted_workgroups() { return 2 * (int64_t)std::max(1, device_cus()); }
@@ -834,6 +1130,44 @@ zp_status launch_fused_dot(const Plan &p, const double *r, const double *th, int
     zp_status st = hip_check(hipGetLastError(), "fused column-dot launch");
     if (st != ZP_OK || chunks == 1) return st;
     return launch_coldot_reduce(part, (int)chunks, P, out_r, out_t, s);
+}
+
+// Up to 32 sets the recurrence is repeated for no second block of sets; with
+// more, the basis stored once and the split-K GEMM win.  Basis + GEMM -> fused
+// (dL/dc alone): (n <= 64, 65536 points) 830 -> 335 us with 1 to 16 sets, 549
+// -> 459 with 32, 568 -> 857 with 64; (n <= 40, 16384 points) 87 -> 50 and 88
+// -> 65 us with 16 and 32 sets, 85 -> 106 with 64; (n <= 24, 65536 points, 32
+// sets) 153 -> 100 us.
+bool fused_grad_ok(int64_t M, int64_t P, int64_t B) { return B <= 32 && small_rows(M, B) && P < ((int64_t)1 << 40); }
+
+zp_status launch_fused_grad(const Plan &p, const double *r, const double *th, int64_t P, const double *wq,
+                            const double *tr, const double *tt, const double *g_up, int64_t B, bool norm,
+                            double *part, size_t part_bytes, double *out, hipStream_t s)
+{
+    const int64_t M = (int64_t)p.n.size();
+    constexpr int R = 2;
+    const int fn = B <= 16 ? 1 : 2;
+    const int64_t nsb = (B + 16 * fn - 1) / (16 * fn);
+    const int64_t tiles = (M + 16 * R - 1) / (16 * R);
+    const int64_t nb = (P + 63) / 64;
+    int64_t S = std::min((nb + kSlices - 1) / kSlices, std::max<int64_t>(1, 6 * (int64_t)device_cus() / (tiles * nsb)));
+    S = std::min(S, std::max<int64_t>(1, (int64_t)(part_bytes / (8 * (size_t)M * (size_t)B))));
+    const int64_t batches = ((nb + S - 1) / S + kSlices - 1) / kSlices * kSlices;
+    S = (nb + batches - 1) / batches;
+    if (tiles * S * nsb > INT32_MAX) return set_error(ZP_ERR_ARG, "too many modes for one launch");
+    GradArgs g{p.d_achains, p.d_row_chain, p.d_coefs, p.d_emits, r, th, P, M, wq, tr, tt, g_up, (uint32_t)B, (int)S, tiles,
+               batches, S > 1 ? part : out, norm && S == 1};
+    if (tr || tt)
+        launch_grad_n<R, true>(g, fn, nsb, s);
+    else
+        launch_grad_n<R, false>(g, fn, nsb, s);
+    zp_status st = hip_check(hipGetLastError(), "fused gradient launch");
+    if (st != ZP_OK || S == 1) return st;
+    const int64_t blocks = (M * B + kThreads - 1) / kThreads;
+    if (blocks > INT32_MAX) return set_error(ZP_ERR_ARG, "M * B too large for one launch");
+    hipLaunchKernelGGL(grad_reduce_kernel, dim3((unsigned)blocks), dim3(kThreads), 0, s, part, (int)S, M, B,
+                       p.d_achains, p.d_row_chain, p.d_emits, norm ? 1 : 0, out);
+    return hip_check(hipGetLastError(), "gradient reduce launch");
 }
 
 } // namespace zp

@@ -607,6 +607,9 @@ zp_status zp_series_bwd(const int32_t *h_n, const int32_t *h_m, int64_t M, const
         if (st != ZP_OK || !d_grad_c) return st;
         need_rt = false;
     }
+    if (d_grad_c && ct == CT_F64 && !need_rt && fused_grad_ok(M, P, B))
+        return launch_fused_grad(*plan, d_r, d_theta, P, nullptr, nullptr, nullptr, d_g, B, false, (double *)ws,
+                                 ws_bytes, d_grad_c, s);
     // c [Mp][Bp]: H's B operand, element (x = q, k = b), k contiguous.
     void *cbuf = ws + L.c_off;
     if (need_rt) {
@@ -945,7 +948,7 @@ zp_status zp_series_bwd2(const int32_t *h_n, const int32_t *h_m, int64_t M, cons
     const bool need_u = d_uc != nullptr;                  // terms with uc
     const bool need_dir = d_ur != nullptr || d_ut != nullptr; // terms with ur, ut
     const bool want_rt = d_out_r || d_out_t;
-    const bool run_c = d_out_c && need_dir;
+    bool run_c = d_out_c && need_dir;
     bool run_u = want_rt && need_u;   // column-dot of uc g^T with dZ/dr, dZ/dtheta
     bool run_e = want_rt && need_dir; // column-dot of c g^T with Er, Et
     if (d_out_c && !need_dir) {
@@ -962,6 +965,12 @@ zp_status zp_series_bwd2(const int32_t *h_n, const int32_t *h_m, int64_t M, cons
         if (st != ZP_OK) return st;
         run_u = run_e = false;
         rt_done = true;
+    }
+    if (run_c && ct == CT_F64 && fused_grad_ok(M, P, B)) {
+        st = launch_fused_grad(*plan, d_r, d_theta, P, nullptr, d_ur, d_ut, d_g, B, false, (double *)ws, ws_bytes,
+                               d_out_c, s);
+        if (st != ZP_OK) return st;
+        run_c = false;
     }
     if (run_e) {
         st = launch_convert(d_c, M, B, B, ct, ws + L.c_off, Bp, Mp, Mp * Bp, false, s);

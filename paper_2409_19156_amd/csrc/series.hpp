@@ -110,6 +110,15 @@ zp_status launch_fused_dot(const Plan &p, const double *r, const double *th, int
                            const double *u, const double *ur, const double *ut, bool second, int64_t B,
                            const double *g, double *part, double *out_r, double *out_t, hipStream_t s);
 
+// out[k][b] = sum_p Z_k(p) w[p] g[p][b] (w nullable: 1), or with the
+// directional derivative along (tr, tt) in place of Z if either is given;
+// norm: divided by the integral of Z_k^2.  part: workspace of part_bytes for
+// the partial sums of point ranges (any size).
+bool fused_grad_ok(int64_t M, int64_t P, int64_t B);
+zp_status launch_fused_grad(const Plan &p, const double *r, const double *th, int64_t P, const double *w,
+                            const double *tr, const double *tt, const double *g, int64_t B, bool norm, double *part,
+                            size_t part_bytes, double *out, hipStream_t s);
+
 // dst (compute type, [R_pad][C_pad] or transposed [C_pad][R_pad]) from a
 // row-major FP64 src [R][C] (leading dimension lds); zero padding.
 zp_status launch_convert(const double *src, int64_t R, int64_t C, int64_t lds, int ct, void *dst, int64_t ldd,
