@@ -259,7 +259,7 @@ zp_status zp_series3d_fwd(const int32_t *h_n, const int32_t *h_m, const int32_t 
     const size_t head = head_bytes(U, Q, B);
     hipStream_t s = (hipStream_t)stream;
     double *T = (double *)d_ws;
-    st = launch_fourier_mix(*p, d_c, B, d_phi, Q, false, T, s);
+    st = launch_fourier_mix(*p, d_c, B, d_phi, Q, T, s);
     if (st != ZP_OK) return st;
     return zp_series_fwd(p->un.data(), p->um.data(), U, d_r, d_theta, P, T, Q * B, prec, d_f, d_cache,
                          (char *)d_ws + head, ws_bytes - head, stream);
@@ -288,7 +288,7 @@ zp_status zp_series3d_bwd(const int32_t *h_n, const int32_t *h_m, const int32_t 
     hipStream_t s = (hipStream_t)stream;
     double *T = (double *)d_ws;
     double *gT = (double *)((char *)d_ws + head / 2);
-    st = launch_fourier_mix(*p, d_c, B, d_phi, Q, false, T, s);
+    st = launch_fourier_mix(*p, d_c, B, d_phi, Q, T, s);
     if (st != ZP_OK) return st;
     const bool need_gT = d_grad_c || d_grad_phi;
     st = zp_series_bwd(p->un.data(), p->um.data(), U, d_r, d_theta, P, T, Q * B, prec, d_g, d_cache,
@@ -299,7 +299,8 @@ zp_status zp_series3d_bwd(const int32_t *h_n, const int32_t *h_m, const int32_t 
         if (st != ZP_OK) return st;
     }
     if (d_grad_phi) {
-        st = launch_fourier_phi_grad(*p, gT, d_c, B, d_phi, Q, d_grad_phi, s);
+        // T [U][Q*B] is free again: partial sums
+        st = launch_fourier_phi_grad(*p, gT, d_c, B, d_phi, Q, T, U * B, d_grad_phi, s);
         if (st != ZP_OK) return st;
     }
     return ZP_OK;

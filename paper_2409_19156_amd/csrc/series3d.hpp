@@ -32,18 +32,18 @@ void dedup_modes(const int32_t *n, const int32_t *m, int64_t J, std::vector<int3
 zp_status get_plan3(const int32_t *n, const int32_t *m, const int32_t *l, int64_t J, std::shared_ptr<Plan3> *out);
 void clear_plans3();
 
-// T[u][q*B + b] = sum over modes j of pair u of c[j][b] F_{l_j}(phi_q)
-// (deriv: dF/dphi instead of F).  T is [U][Q*B], row-major.
-zp_status launch_fourier_mix(const Plan3 &p, const double *c, int64_t B, const double *phi, int64_t Q, bool deriv,
-                             double *T, hipStream_t s);
+// T[u][q*B + b] = sum over modes j of pair u of c[j][b] F_{l_j}(phi_q).  T is
+// [U][Q*B], row-major.
+zp_status launch_fourier_mix(const Plan3 &p, const double *c, int64_t B, const double *phi, int64_t Q, double *T,
+                             hipStream_t s);
 
 // grad_c[j][b] = sum_q F_{l_j}(phi_q) gT[owner_j][q*B + b].
 zp_status launch_fourier_unmix(const Plan3 &p, const double *gT, int64_t B, const double *phi, int64_t Q,
                                double *grad_c, hipStream_t s);
 
 // grad_phi[q] = sum_j sum_b dF_{l_j}/dphi(phi_q) c[j][b] gT[owner_j][q*B + b],
-// summed in a fixed order.
+// summed in a fixed order.  part: room for part_rows x Q partial sums.
 zp_status launch_fourier_phi_grad(const Plan3 &p, const double *gT, const double *c, int64_t B, const double *phi,
-                                  int64_t Q, double *grad_phi, hipStream_t s);
+                                  int64_t Q, double *part, int64_t part_rows, double *grad_phi, hipStream_t s);
 
 } // namespace zp
