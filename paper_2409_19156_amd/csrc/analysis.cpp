@@ -9,7 +9,9 @@
 // (r_p, theta_p, w_p) that integrates every product Z_k f exactly,
 //   c_k = (1 / N_k) sum_p w_p Z_k(p) f(p).
 // On the device this is the series' adjoint contraction dL/dc = Z g with
-// g = w * f, followed by the division by N_k.
+// g = w * f, the weights applied where the contraction reads f and the
+// division by N_k where its partial sums are added: as kernels of their own
+// these took 5 and 25 of 210 us (n <= 64, 4257 points, 64 sets).
 //
 // zp_analysis_grid builds such a rule for modes with n <= L: Gauss-Legendre
 // in t = r^2 (R_n^m R_n'^m r dr is a polynomial of degree (n + n')/2 <= L in
@@ -21,8 +23,6 @@
 
 namespace zp {
 zp_status check_modes_arg(const int32_t *n, const int32_t *m, int64_t M);
-zp_status launch_weight(const double *w, const double *f, int64_t P, int64_t B, double *wf, hipStream_t s);
-zp_status launch_mode_norm(const Plan &plan, int64_t B, double *c, hipStream_t s);
 } // namespace zp
 
 using namespace zp;
@@ -142,13 +142,10 @@ zp_status zp_series_analysis(const int32_t *h_n, const int32_t *h_m, int64_t M, 
     std::shared_ptr<Plan> plan;
     st = get_plan(h_n, h_m, M, &plan);
     if (st != ZP_OK) return st;
-    double *wf = (double *)d_ws;
-    st = launch_weight(d_w, d_f, P, B, wf, s);
-    if (st != ZP_OK) return st;
-    st = zp_series_bwd(h_n, h_m, M, d_r, d_theta, P, nullptr, B, prec, wf, nullptr, d_c, nullptr, nullptr,
-                       (char *)d_ws + head, ws_bytes - head, stream);
-    if (st != ZP_OK) return st;
-    return launch_mode_norm(*plan, B, d_c, s);
+    // the weights go with the samples' conversion, the norms with the
+    // reduction of the partial sums
+    return series_bwd_run(*plan, M, d_r, d_theta, P, nullptr, B, prec, d_f, d_w, true, nullptr, d_c, nullptr, nullptr,
+                          (char *)d_ws + head, ws_bytes - head, s);
 }
 
 } // extern "C"

@@ -975,11 +975,11 @@ template <int R, bool DIR> void launch_grad_n(const GradArgs &g, int fn, int64_t
         launch_grad_t<R, 1, DIR>(g, nsb, s);
 }
 
-// out[m][b] = sum over splits, in order; norm: times the inverse mode norms.
+// out[m][b] = (out +) sum over splits, in order; norm: times the inverse mode norms.
 __global__ __launch_bounds__(kThreads) void grad_reduce_kernel(const double *__restrict__ part, int S, int64_t M,
                                                                int64_t B, const Chain *chains,
                                                                const int32_t *row_chain, const Emit *emits, int norm,
-                                                               double *__restrict__ out)
+                                                               int accumulate, double *__restrict__ out)
 {
     const int64_t b = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     const int64_t e = b / B; // emission, set b - e B
@@ -987,8 +987,9 @@ __global__ __launch_bounds__(kThreads) void grad_reduce_kernel(const double *__r
     const Emit em = emits[e];
     const int64_t o = em.col * B + (b - e * B);
     double v = 0.0;
-#pragma unroll 4
+#pragma unroll 8
     for (int k = 0; k < S; ++k) v += part[k * M * B + o];
+    if (accumulate) v += out[o];
     if (norm) {
         int lo = row_chain[e >> 4];
         while (e >= chains[lo].emit_off + chains[lo].emit_cnt) ++lo;
@@ -1113,10 +1114,16 @@ zp_status launch_fused_grad(const Plan &p, const double *r, const double *th, in
         launch_grad_n<R, false>(g, fn, nsb, s);
     zp_status st = hip_check(hipGetLastError(), "fused gradient launch");
     if (st != ZP_OK || S == 1) return st;
+    return launch_grad_reduce(p, part, (int)S, M, B, norm, false, out, s);
+}
+
+zp_status launch_grad_reduce(const Plan &p, const double *part, int S, int64_t M, int64_t B, bool norm,
+                             bool accumulate, double *C, hipStream_t s)
+{
     const int64_t blocks = (M * B + kThreads - 1) / kThreads;
     if (blocks > INT32_MAX) return set_error(ZP_ERR_ARG, "M * B too large for one launch");
-    hipLaunchKernelGGL(grad_reduce_kernel, dim3((unsigned)blocks), dim3(kThreads), 0, s, part, (int)S, M, B,
-                       p.d_achains, p.d_row_chain, p.d_emits, norm ? 1 : 0, out);
+    hipLaunchKernelGGL(grad_reduce_kernel, dim3((unsigned)blocks), dim3(kThreads), 0, s, part, S, M, B, p.d_achains,
+                       p.d_row_chain, p.d_emits, norm ? 1 : 0, accumulate ? 1 : 0, C);
     return hip_check(hipGetLastError(), "gradient reduce launch");
 }
 

@@ -35,11 +35,18 @@
 // D[l/16+4t][l%16] for the FP64 shape.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "series.hpp"
 
 namespace zp {
+
+bool gemm_narrow(int64_t M, int64_t N, int splits)
+{
+    return ((M + 127) / 128) * ((N + 127) / 128) * (int64_t)splits < 4 * (int64_t)device_cus();
+}
+
 namespace {
 
 typedef double d4 __attribute__((ext_vector_type(4)));
@@ -583,8 +590,7 @@ template <int CT, int ALAY, int BLAY, int EPI>
 hipError_t launch_t(const GemmDesc &g, hipStream_t s)
 {
     if constexpr (CT == CT_F64 && EPI != EPI_STORE) {
-        const int64_t wide = ((g.M + 127) / 128) * ((g.N + 127) / 128) * (int64_t)g.splits;
-        if (wide < 4 * (int64_t)device_cus()) return launch_shape<CT, ALAY, BLAY, EPI, true>(g, s);
+        if (gemm_narrow(g.M, g.N, g.splits)) return launch_shape<CT, ALAY, BLAY, EPI, true>(g, s);
     }
     return launch_shape<CT, ALAY, BLAY, EPI, kNarrowDefault<CT, EPI>>(g, s);
 }
@@ -625,26 +631,8 @@ hipError_t launch_c(const GemmDesc &g, hipStream_t s)
 
 // ------------------------------------------------------------ helpers --
 
-__device__ __forceinline__ void put(void *dst, int ct, int64_t idx, int64_t sub, double v)
-{
-    if (ct == CT_F64) {
-        ((double *)dst)[idx] = v;
-    } else if (ct == CT_F32) {
-        ((float *)dst)[idx] = (float)v;
-    } else {
-        uint16_t *b = (uint16_t *)dst;
-        const uint16_t h = bf16_rne((float)v);
-        const double r1 = v - bf16_val(h);
-        const uint16_t m = bf16_rne((float)r1);
-        const double r2 = r1 - bf16_val(m);
-        b[idx] = h;
-        b[idx + sub] = m;
-        b[idx + 2 * sub] = bf16_rne((float)r2);
-    }
-}
-
-// put() for the two adjacent elements idx, idx + 1 (idx even, dst aligned):
-// one 16-, 8- or 2 x 3 x 2-byte store instead of two, the same values.
+// The two adjacent elements idx, idx + 1 (idx even, dst aligned) in the compute
+// type, in one 16-, 8- or 3 x 4-byte store.
 __device__ __forceinline__ void put2(void *dst, int ct, int64_t idx, int64_t sub, double v0, double v1)
 {
     if (ct == CT_F64) {
@@ -673,9 +661,11 @@ __device__ __forceinline__ void put2(void *dst, int ct, int64_t idx, int64_t sub
 }
 
 // Row conversion: dst[r][c] for r < gridDim.x (the padded rows), c < ldd
-// (even), two columns per lane; zero outside src's R x C.
+// (even), two columns per lane; zero outside src's R x C; rows times roww if
+// that is set.
 __global__ __launch_bounds__(256) void convert_rows_kernel(const double *__restrict__ src, int64_t R, int64_t C,
-                                                           int64_t lds, int ct, void *dst, int64_t ldd, int64_t sub)
+                                                           int64_t lds, int ct, void *dst, int64_t ldd, int64_t sub,
+                                                           const double *__restrict__ roww)
 {
     const int64_t r = blockIdx.x;
     const int64_t c = ((int64_t)blockIdx.y * 256 + threadIdx.x) * 2;
@@ -684,73 +674,16 @@ __global__ __launch_bounds__(256) void convert_rows_kernel(const double *__restr
     if (r < R) {
         if (c < C) v0 = src[r * lds + c];
         if (c + 1 < C) v1 = src[r * lds + c + 1];
+        if (roww) {
+            const double w = roww[r];
+            v0 *= w;
+            v1 *= w;
+        }
     }
     put2(dst, ct, r * ldd + c, sub, v0, v1);
 }
 
-// Transposing conversion through a 64 x 64 LDS tile: dst_t[c][r] = src[r][c]
-// (dst_t [gridDim.y * 64][ldt]).  Zero outside src's R x C; two elements per
-// lane on each store.
-__global__ __launch_bounds__(256) void convert_t64_kernel(const double *__restrict__ src, int64_t R, int64_t C,
-                                                          int64_t lds, int ct, void *dst_t, int64_t ldt,
-                                                          int64_t sub_t)
-{
-    __shared__ double tile[64][65];
-    const int64_t r0 = (int64_t)blockIdx.x * 64; // src rows = dst_t columns
-    const int64_t c0 = (int64_t)blockIdx.y * 64; // src cols = dst_t rows
-    const int t = threadIdx.x;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const int idx = i * 256 + t;
-        const int y = idx >> 5, x = (idx & 31) * 2;
-        const int64_t r = r0 + y, c = c0 + x;
-        const double v0 = (r < R && c < C) ? src[r * lds + c] : 0.0;
-        const double v1 = (r < R && c + 1 < C) ? src[r * lds + c + 1] : 0.0;
-        tile[y][x] = v0;
-        tile[y][x + 1] = v1;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const int idx = i * 256 + t;
-        const int cy = idx >> 5, rx = (idx & 31) * 2;
-        put2(dst_t, ct, (c0 + cy) * ldt + r0 + rx, sub_t, tile[rx][cy], tile[rx + 1][cy]);
-    }
-}
-
-// Direct conversion: dst[r][c] for r < rows_pad, c < ldd.
-__global__ void convert_kernel(const double *__restrict__ src, int64_t R, int64_t C, int64_t lds, int ct, void *dst,
-                               int64_t ldd, int64_t rows_pad, int64_t sub)
-{
-    const int64_t total = rows_pad * ldd;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t r = e / ldd, c = e % ldd;
-        const double v = (r < R && c < C) ? src[r * lds + c] : 0.0;
-        put(dst, ct, e, sub, v);
-    }
-}
-
-// Transposing conversion through a 32 x 32 LDS tile: dst[c][r] = src[r][c],
-// dst is [rows_pad][ldd] with rows indexed by c.
-__global__ __launch_bounds__(256) void convert_t_kernel(const double *__restrict__ src, int64_t R, int64_t C,
-                                                        int64_t lds, int ct, void *dst, int64_t ldd, int64_t sub)
-{
-    __shared__ double tile[32][33];
-    const int64_t r0 = (int64_t)blockIdx.x * 32; // src rows = dst columns
-    const int64_t c0 = (int64_t)blockIdx.y * 32; // src cols = dst rows
-    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-    for (int y = ty; y < 32; y += 8) {
-        const int64_t r = r0 + y, c = c0 + tx;
-        tile[y][tx] = (r < R && c < C) ? src[r * lds + c] : 0.0;
-    }
-    __syncthreads();
-    for (int y = ty; y < 32; y += 8) {
-        const int64_t c = c0 + y, r = r0 + tx; // dst row c, column r
-        put(dst, ct, c * ldd + r, sub, tile[tx][y]);
-    }
-}
-
-// FP64 value -> three bf16 planes, the same split as put()
+// FP64 value -> three bf16 planes, the same split as put2()
 __device__ __forceinline__ void split3d(double v, uint32_t &h, uint32_t &m, uint32_t &l)
 {
     h = bf16_rne((float)v);
@@ -780,7 +713,7 @@ __device__ __forceinline__ void put_frag8(uint16_t *dst, int64_t sub, int64_t of
 
 // One lane per (column x, group of 8 k): eight values gathered through perm
 // (consecutive lanes read consecutive columns), split into the three bf16
-// planes as put() does, and written as one 16-byte fragment row per plane.
+// planes as put2() does, and written as one 16-byte fragment row per plane.
 __global__ __launch_bounds__(256) void convert_gather_frag_kernel(const double *__restrict__ src,
                                                                   const int32_t *__restrict__ perm, int64_t R,
                                                                   int64_t C, int64_t lds, uint16_t *dst, int64_t xpad,
@@ -806,14 +739,15 @@ __global__ __launch_bounds__(256) void convert_gather_frag_kernel(const double *
 // B(k = point, j = set) (xpad_c / 16 column blocks).  Zero outside R x C.
 __global__ __launch_bounds__(256) void convert_g_bwd_kernel(const double *__restrict__ src, int64_t R, int64_t C,
                                                             int64_t lds, uint16_t *dst_c, int64_t subc,
-                                                            uint16_t *dst_s, int64_t subs, int64_t xpad_c)
+                                                            uint16_t *dst_s, int64_t subs, int64_t xpad_c,
+                                                            const double *__restrict__ roww)
 {
     __shared__ double tile[32][65];
     const int64_t r0 = (int64_t)blockIdx.x * 32, c0 = (int64_t)blockIdx.y * 64;
     const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
     for (int y = ty; y < 32; y += 4) {
         const int64_t r = r0 + y, c = c0 + tx;
-        tile[y][tx] = (r < R && c < C) ? src[r * lds + c] : 0.0;
+        tile[y][tx] = (r < R && c < C) ? (roww ? roww[r] * src[r * lds + c] : src[r * lds + c]) : 0.0;
     }
     __syncthreads();
     const int t = threadIdx.x;
@@ -833,44 +767,48 @@ __global__ __launch_bounds__(256) void convert_g_bwd_kernel(const double *__rest
 }
 
 // Zero the pad of a k-blocked bf16 operand [Mp/8][ld][8] (three planes, sub
-// apart): every mode e >= M and every point p >= P.
-__global__ void zero_kb8_kernel(uint16_t *dst, int64_t M, int64_t Mp, int64_t P, int64_t ld, int64_t sub)
+// apart): every mode e >= M and every point p >= P, looking from group g0 and
+// point p0 on: the caller leaves out the groups
+// and points that hold no pad (scanning the whole operand took 23 us per 8192
+// points of n <= 64 for 32 768 pad elements).
+__global__ __launch_bounds__(256) void zero_kb8_kernel(uint16_t *dst, int64_t M, int64_t P, int64_t ld, int64_t sub,
+                                                       int64_t g0, int64_t p0, int64_t blocks_per_row)
 {
-    const int64_t total = (Mp / 8) * ld;
-    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total; t += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t gq = t / ld, p = t % ld;
-        if (gq * 8 + 8 <= M && p < P) continue;
-        for (int q = 0; q < 8; ++q) {
-            if (gq * 8 + q < M && p < P) continue;
-            const int64_t idx = t * 8 + q;
-            dst[idx] = 0;
-            dst[idx + sub] = 0;
-            dst[idx + 2 * sub] = 0;
-        }
+    const int64_t gq = g0 + blockIdx.x / blocks_per_row;
+    const int64_t p = p0 + blockIdx.x % blocks_per_row * 256 + threadIdx.x;
+    if (p >= ld) return;
+    uint16_t *at = dst + (gq * ld + p) * 8;
+    if (gq * 8 >= M || p >= P) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) *(u4 *)(at + q * sub) = u4{0, 0, 0, 0};
+    } else {
+        for (int e = (int)(M - gq * 8); e < 8; ++e) at[e] = at[e + sub] = at[e + 2 * sub] = 0;
     }
 }
 
-__global__ void zero_kernel(void *dst, int ct, int64_t row0, int64_t rows, int64_t col0, int64_t cols, int64_t ld,
-                            int64_t sub)
+// Zero the pad of [rows_pad][ld] elements whose valid block is [rows][cols]: one row per grid row, starting at row0 (rows below `rows` are
+// zeroed from column `cols` on, the others whole).
+template <class T>
+__global__ __launch_bounds__(256) void zero_kernel(T *dst, int64_t rows, int64_t cols, int64_t ld, int64_t row0,
+                                                   int64_t rows_pad)
 {
-    const int64_t total = rows * cols;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t idx = (row0 + e / cols) * ld + col0 + e % cols;
-        put(dst, ct, idx, sub, 0.0);
+    for (int64_t r = row0 + blockIdx.y; r < rows_pad; r += gridDim.y) {
+        const int64_t c0 = r < rows ? cols : 0;
+        for (int64_t c = c0 + (int64_t)blockIdx.x * 256 + threadIdx.x; c < ld; c += (int64_t)gridDim.x * 256)
+            dst[r * ld + c] = T(0);
     }
 }
 
-__global__ void splitk_reduce_kernel(const double *__restrict__ part, int S, int64_t M, int64_t N, double *C,
-                                     int64_t ldc, int accumulate)
+// C = (C +) sum of the S partial sums, in order (M N contiguous elements).
+__global__ __launch_bounds__(256) void splitk_reduce_kernel(const double *__restrict__ part, int S, int64_t total,
+                                                            double *C, int accumulate)
 {
-    const int64_t total = M * N;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t i = e / N, j = e % N;
-        double s = 0.0;
-        for (int k = 0; k < S; ++k) s += part[(int64_t)k * M * ldc + i * ldc + j];
-        double *c = C + i * ldc + j;
-        *c = accumulate ? *c + s : s;
-    }
+    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (e >= total) return;
+    double s = 0.0;
+#pragma unroll 8
+    for (int k = 0; k < S; ++k) s += part[(int64_t)k * total + e];
+    C[e] = accumulate ? C[e] + s : s;
 }
 
 __global__ void coldot_reduce_kernel(const double *__restrict__ part, int T, int64_t P, double *out1, double *out2)
@@ -884,12 +822,6 @@ __global__ void coldot_reduce_kernel(const double *__restrict__ part, int T, int
     }
     if (out1) out1[p] = s1;
     if (out2) out2[p] = s2;
-}
-
-unsigned grid_for(int64_t total, int block)
-{
-    const int64_t g = (total + block - 1) / block;
-    return (unsigned)(g < 65536 * 4 ? (g < 1 ? 1 : g) : 65536 * 4);
 }
 
 } // namespace
@@ -919,25 +851,12 @@ zp_status launch_gemm(const GemmDesc &desc, hipStream_t s)
 }
 
 zp_status launch_convert(const double *src, int64_t R, int64_t C, int64_t lds, int ct, void *dst, int64_t ldd,
-                         int64_t rows_pad, int64_t sub, bool transpose, hipStream_t s)
+                         int64_t rows_pad, int64_t sub, const double *roww, hipStream_t s)
 {
-    if (!transpose) {
-        if (ldd % 2 == 0 && sub % 2 == 0 && rows_pad <= 0x7FFFFFFF && ((uintptr_t)dst & 15) == 0) {
-            const dim3 grid((unsigned)rows_pad, (unsigned)((ldd / 2 + 255) / 256));
-            hipLaunchKernelGGL(convert_rows_kernel, grid, dim3(256), 0, s, src, R, C, lds, ct, dst, ldd, sub);
-        } else {
-            hipLaunchKernelGGL(convert_kernel, dim3(grid_for(rows_pad * ldd, 256)), dim3(256), 0, s, src, R, C, lds,
-                               ct, dst, ldd, rows_pad, sub);
-        }
-    } else if (ldd % 64 == 0 && rows_pad % 64 == 0 && sub % 2 == 0) {
-        // dst is [rows_pad (>= C, padded)][ldd (>= R, padded)]
-        const dim3 grid((unsigned)(ldd / 64), (unsigned)(rows_pad / 64));
-        hipLaunchKernelGGL(convert_t64_kernel, grid, dim3(256), 0, s, src, R, C, lds, ct, dst, ldd, sub);
-    } else {
-        // both multiples of 32
-        const dim3 grid((unsigned)(ldd / 32), (unsigned)(rows_pad / 32));
-        hipLaunchKernelGGL(convert_t_kernel, grid, dim3(256), 0, s, src, R, C, lds, ct, dst, ldd, sub);
-    }
+    if (ldd % 2 || sub % 2 || rows_pad > 0x7FFFFFFF || ((uintptr_t)dst & 15))
+        return set_error(ZP_ERR_ARG, "internal: conversion target not padded or aligned");
+    const dim3 grid((unsigned)rows_pad, (unsigned)((ldd / 2 + 255) / 256));
+    hipLaunchKernelGGL(convert_rows_kernel, grid, dim3(256), 0, s, src, R, C, lds, ct, dst, ldd, sub, roww);
     return hip_check(hipGetLastError(), "convert launch");
 }
 
@@ -951,41 +870,51 @@ zp_status launch_convert_gather_frag(const double *src, const int32_t *perm, int
 }
 
 zp_status launch_convert_g_bwd(const double *src, int64_t R, int64_t C, int64_t lds, void *dst_c, int64_t subc,
-                               void *dst_s, int64_t subs, int64_t xpad_r, int64_t xpad_c, hipStream_t s)
+                               void *dst_s, int64_t subs, int64_t xpad_r, int64_t xpad_c, const double *roww,
+                               hipStream_t s)
 {
     const dim3 grid((unsigned)(xpad_r / 32), (unsigned)(xpad_c / 64));
     hipLaunchKernelGGL(convert_g_bwd_kernel, grid, dim3(256), 0, s, src, R, C, lds, (uint16_t *)dst_c, subc,
-                       (uint16_t *)dst_s, subs, xpad_c);
+                       (uint16_t *)dst_s, subs, xpad_c, roww);
     return hip_check(hipGetLastError(), "convert launch");
 }
 
 zp_status launch_zero_kb8(void *dst, int64_t M, int64_t Mp, int64_t P, int64_t ld, int64_t sub, hipStream_t s)
 {
-    hipLaunchKernelGGL(zero_kb8_kernel, dim3(grid_for((Mp / 8) * ld, 256)), dim3(256), 0, s, (uint16_t *)dst, M, Mp,
-                       P, ld, sub);
+    auto zero = [&](int64_t g0, int64_t p0) {
+        if (g0 >= Mp / 8 || p0 >= ld) return;
+        const int64_t per_row = (ld - p0 + 255) / 256;
+        hipLaunchKernelGGL(zero_kb8_kernel, dim3((unsigned)(per_row * (Mp / 8 - g0))), dim3(256), 0, s,
+                           (uint16_t *)dst, M, P, ld, sub, g0, p0, per_row);
+    };
+    zero(M / 8, 0);           // the groups with pad modes, every point
+    if (M >= 8) zero(0, P);   // the pad points (of all groups)
     return hip_check(hipGetLastError(), "zero-pad launch");
 }
 
 zp_status launch_zero_pad(void *dst, int ct, int64_t rows, int64_t cols, int64_t rows_pad, int64_t ld, int64_t sub,
                           hipStream_t s)
 {
-    if (rows_pad > rows) {
-        const int64_t n = (rows_pad - rows) * ld;
-        hipLaunchKernelGGL(zero_kernel, dim3(grid_for(n, 256)), dim3(256), 0, s, dst, ct, rows, rows_pad - rows,
-                           (int64_t)0, ld, ld, sub);
-    }
-    if (ld > cols && rows > 0) {
-        const int64_t n = rows * (ld - cols);
-        hipLaunchKernelGGL(zero_kernel, dim3(grid_for(n, 256)), dim3(256), 0, s, dst, ct, (int64_t)0, rows, cols,
-                           ld - cols, ld, sub);
-    }
+    (void)sub;
+    if (ct == CT_BF3) return set_error(ZP_ERR_ARG, "internal: zero pad of FP64 or FP32 planes only");
+    const bool sides = ld > cols && rows > 0;
+    const int64_t row0 = sides ? 0 : rows;
+    if (rows_pad <= row0 || ld <= 0) return ZP_OK;
+    const int64_t width = sides ? ld - cols : ld; // (the pad rows of a block with pad columns are strided over)
+    const dim3 grid((unsigned)std::min<int64_t>((width + 255) / 256, 4096), (unsigned)std::min<int64_t>(rows_pad - row0, 65535));
+    if (ct == CT_F64)
+        hipLaunchKernelGGL(zero_kernel<double>, grid, dim3(256), 0, s, (double *)dst, rows, cols, ld, row0, rows_pad);
+    else
+        hipLaunchKernelGGL(zero_kernel<float>, grid, dim3(256), 0, s, (float *)dst, rows, cols, ld, row0, rows_pad);
     return hip_check(hipGetLastError(), "zero-pad launch");
 }
 
-zp_status launch_splitk_reduce(const double *part, int S, int64_t M, int64_t N, double *C, int64_t ldc,
-                               bool accumulate, hipStream_t s)
+zp_status launch_splitk_reduce(const double *part, int S, int64_t M, int64_t N, double *C, bool accumulate,
+                               hipStream_t s)
 {
-    hipLaunchKernelGGL(splitk_reduce_kernel, dim3(grid_for(M * N, 256)), dim3(256), 0, s, part, S, M, N, C, ldc,
+    const int64_t blocks = (M * N + 255) / 256;
+    if (blocks > 0x7FFFFFFF) return set_error(ZP_ERR_ARG, "too many coefficients for one launch");
+    hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)blocks), dim3(256), 0, s, part, S, M * N, C,
                        accumulate ? 1 : 0);
     return hip_check(hipGetLastError(), "split-K reduce launch");
 }

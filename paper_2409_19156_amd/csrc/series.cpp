@@ -470,7 +470,7 @@ zp_status series_fwd_run(const Plan &pl, int64_t M, const double *d_r, const dou
     if (ct == CT_BF3) // B(k = e, j = b) = c[perm[e]][b], in MFMA fragment order
         st = launch_convert_gather_frag(d_c, plan->d_perm, M, B, B, cbuf, Bp, Mp, Bp * Mp, s);
     else // B(k = q, j = b) = c[q][b]
-        st = launch_convert(d_c, M, B, B, ct, cbuf, Bp, Mp, Mp * Bp, false, s);
+        st = launch_convert(d_c, M, B, B, ct, cbuf, Bp, Mp, Mp * Bp, nullptr, s);
     if (st != ZP_OK) return st;
 
     const CacheLayout CL(M, P, ct);
@@ -583,15 +583,30 @@ zp_status zp_series_bwd(const int32_t *h_n, const int32_t *h_m, int64_t M, const
     if (!d_ws || ((uintptr_t)d_ws & 255)) return set_error(ZP_ERR_ARG, "workspace must be non-null and 256-byte aligned");
     if (!d_grad_c && !d_grad_r && !d_grad_theta) return ZP_OK;
     if ((uintptr_t)d_cache & 255) return set_error(ZP_ERR_ARG, "cache must be 256-byte aligned");
+    if (chunk_for(M, P, B, ct_of(prec), false, true, d_cache != nullptr, ws_bytes) <= 0)
+        return set_error(ZP_ERR_WORKSPACE, "workspace smaller than the minimum (zp_series_workspace)");
+    std::shared_ptr<Plan> plan;
+    st = get_plan(h_n, h_m, M, &plan);
+    if (st != ZP_OK) return st;
+    return series_bwd_run(*plan, M, d_r, d_theta, P, d_c, B, prec, d_g, nullptr, false, d_cache, d_grad_c, d_grad_r,
+                          d_grad_theta, d_ws, ws_bytes, (hipStream_t)stream);
+}
+
+} // extern "C"
+
+namespace zp {
+
+zp_status series_bwd_run(const Plan &pl, int64_t M, const double *d_r, const double *d_theta, int64_t P,
+                         const double *d_c, int64_t B, int32_t prec, const double *d_g, const double *d_w, bool norm,
+                         const void *d_cache, double *d_grad_c, double *d_grad_r, double *d_grad_theta, void *d_ws,
+                         size_t ws_bytes, hipStream_t s)
+{
+    const Plan *plan = &pl;
+    zp_status st = ZP_OK;
     const int ct = ct_of(prec);
     const bool have_cache = d_cache != nullptr;
     const int64_t Pc = chunk_for(M, P, B, ct, false, true, have_cache, ws_bytes);
     if (Pc <= 0) return set_error(ZP_ERR_WORKSPACE, "workspace smaller than the minimum (zp_series_workspace)");
-    hipStream_t s = (hipStream_t)stream;
-    std::shared_ptr<Plan> plan;
-    st = get_plan(h_n, h_m, M, &plan);
-    if (st != ZP_OK) return st;
-
     // room for the partial sums of as many splits as are wanted, if it is there
     // with the basis in the workspace (so that a cache changes no sum)
     const bool few = WsLayout(M, Pc, B, ct, false, true, false, false).total > ws_bytes;
@@ -608,12 +623,12 @@ zp_status zp_series_bwd(const int32_t *h_n, const int32_t *h_m, int64_t M, const
         need_rt = false;
     }
     if (d_grad_c && ct == CT_F64 && !need_rt && fused_grad_ok(M, P, B))
-        return launch_fused_grad(*plan, d_r, d_theta, P, nullptr, nullptr, nullptr, d_g, B, false, (double *)ws,
-                                 ws_bytes, d_grad_c, s);
+        return launch_fused_grad(*plan, d_r, d_theta, P, d_w, nullptr, nullptr, d_g, B, norm, (double *)ws, ws_bytes,
+                                 d_grad_c, s);
     // c [Mp][Bp]: H's B operand, element (x = q, k = b), k contiguous.
     void *cbuf = ws + L.c_off;
     if (need_rt) {
-        st = launch_convert(d_c, M, B, B, ct, cbuf, Bp, Mp, Mp * Bp, false, s);
+        st = launch_convert(d_c, M, B, B, ct, cbuf, Bp, Mp, Mp * Bp, nullptr, s);
         if (st != ZP_OK) return st;
     }
     const CacheLayout CL(M, P, ct);
@@ -657,15 +672,21 @@ zp_status zp_series_bwd(const int32_t *h_n, const int32_t *h_m, int64_t M, const
         // g rows of this chunk: [pcp][Bp] (and MFMA fragment order for bf16's
         // grad_c operand).
         // In FP64, with B and the chunk already multiples of the pad, g itself
-        // has that layout and is read in place.
-        const bool g_in_place = ct == CT_F64 && B == Bp && pc == pcp && ((uintptr_t)d_g & 15) == 0;
+        // has that layout and is read in place (multiples of 64 sets do for a
+        // split-K of narrow tiles alone).
+        const int splits = splits_within(M, B, pcp, ct, L.S);
+        const bool cols_fit = B == Bp || (B % 64 == 0 && !need_rt && gemm_narrow(M, B, splits));
+        const bool g_in_place = ct == CT_F64 && cols_fit && pc == pcp && !d_w && ((uintptr_t)d_g & 15) == 0;
+        const int64_t ldg = g_in_place ? B : Bp;
         const void *gbuf = g_in_place ? (const void *)(d_g + p0 * B) : (const void *)(ws + L.g_off);
         if (ct == CT_BF3) { // both contractions' operands from one read of g
             st = launch_convert_g_bwd(d_g + p0 * B, pc, B, B, ws + L.g_off, pcp * Bp,
-                                      d_grad_c ? ws + L.gt_off : nullptr, Bp * pcp, pcp, Bp, s);
+                                      d_grad_c ? ws + L.gt_off : nullptr, Bp * pcp, pcp, Bp, d_w ? d_w + p0 : nullptr,
+                                      s);
             if (st != ZP_OK) return st;
         } else if (!g_in_place) {
-            st = launch_convert(d_g + p0 * B, pc, B, B, ct, ws + L.g_off, Bp, pcp, pcp * Bp, false, s);
+            st = launch_convert(d_g + p0 * B, pc, B, B, ct, ws + L.g_off, Bp, pcp, pcp * Bp, d_w ? d_w + p0 : nullptr,
+                                s);
             if (st != ZP_OK) return st;
         }
         st = side.start(); // both contractions' inputs are queued on s
@@ -677,17 +698,20 @@ zp_status zp_series_bwd(const int32_t *h_n, const int32_t *h_m, int64_t M, const
             if (ct == CT_BF3)
                 g.b = Operand{ws + L.gt_off, Bp / 16, Bp * pcp, LAY_FRAG}; // B(k=p, j=b) = g[p][b]
             else
-                g.b = Operand{gbuf, Bp, pcp * Bp, LAY_XC}; // B(k=p, j=b) = g[p][b]
+                g.b = Operand{gbuf, ldg, pcp * ldg, LAY_XC}; // B(k=p, j=b) = g[p][b]
             g.M = M;
             g.N = B;
             g.K = pcp;
-            g.splits = splits_within(M, B, pcp, ct, L.S);
+            g.splits = splits;
             g.epi = EPI_PARTIAL;
             g.C = (double *)(ws + L.pc_off);
             g.ldc = B;
             st = launch_gemm(g, s);
             if (st != ZP_OK) return st;
-            st = launch_splitk_reduce(g.C, g.splits, M, B, d_grad_c, B, p0 > 0, s);
+            if (norm) // with the last chunk
+                st = launch_grad_reduce(*plan, g.C, g.splits, M, B, p0 + pc >= P, p0 > 0, d_grad_c, s);
+            else
+                st = launch_splitk_reduce(g.C, g.splits, M, B, d_grad_c, p0 > 0, s);
             if (st != ZP_OK) return st;
         }
         if (need_rt) {
@@ -719,7 +743,7 @@ zp_status zp_series_bwd(const int32_t *h_n, const int32_t *h_m, int64_t M, const
     return side.finish();
 }
 
-} // extern "C"
+} // namespace zp
 
 extern "C" zp_status zp_series_jvp(const int32_t *h_n, const int32_t *h_m, int64_t M, const double *d_r,
                                    const double *d_theta, int64_t P, const double *d_c, int64_t B, int32_t prec,
@@ -768,7 +792,7 @@ extern "C" zp_status zp_series_jvp(const int32_t *h_n, const int32_t *h_m, int64
             st = launch_convert_gather_frag(src, plan->d_perm, M, B, B, cbuf + esz * (size_t)(blk * Mp) * (size_t)Bp,
                                             Bp, Mp, Bp * K, s);
         else // [K][Bp]
-            st = launch_convert(src, M, B, B, ct, cbuf + esz * (size_t)(blk * Mp) * (size_t)Bp, Bp, Mp, 0, false, s);
+            st = launch_convert(src, M, B, B, ct, cbuf + esz * (size_t)(blk * Mp) * (size_t)Bp, Bp, Mp, 0, nullptr, s);
         if (st != ZP_OK) return st;
         ++blk;
     }
@@ -973,11 +997,11 @@ zp_status zp_series_bwd2(const int32_t *h_n, const int32_t *h_m, int64_t M, cons
         run_c = false;
     }
     if (run_e) {
-        st = launch_convert(d_c, M, B, B, ct, ws + L.c_off, Bp, Mp, Mp * Bp, false, s);
+        st = launch_convert(d_c, M, B, B, ct, ws + L.c_off, Bp, Mp, Mp * Bp, nullptr, s);
         if (st != ZP_OK) return st;
     }
     if (run_u) {
-        st = launch_convert(d_uc, M, B, B, ct, ws + L.u_off, Bp, Mp, Mp * Bp, false, s);
+        st = launch_convert(d_uc, M, B, B, ct, ws + L.u_off, Bp, Mp, Mp * Bp, nullptr, s);
         if (st != ZP_OK) return st;
     }
     const int zfmt = ct == CT_F64 ? F64 : F32; // D as the split-K contraction reads it
@@ -1022,14 +1046,17 @@ zp_status zp_series_bwd2(const int32_t *h_n, const int32_t *h_m, int64_t M, cons
         if (st != ZP_OK) return st;
         // the chunk's g: [pcp][Bp] (and MFMA fragment order for the bf16 dL/dc
         // operand); read in place in FP64 when it already has that layout
-        const bool g_in_place = ct == CT_F64 && B == Bp && pc == pcp && ((uintptr_t)d_g & 15) == 0;
+        const int splits = splits_within(M, B, pcp, ct, L.S);
+        const bool cols_fit = B == Bp || (B % 64 == 0 && !run_u && !run_e && gemm_narrow(M, B, splits));
+        const bool g_in_place = ct == CT_F64 && cols_fit && pc == pcp && ((uintptr_t)d_g & 15) == 0;
+        const int64_t ldg = g_in_place ? B : Bp;
         const void *gbuf = g_in_place ? (const void *)(d_g + p0 * B) : (const void *)(ws + L.g_off);
         if (run_c && ct == CT_BF3) { // both layouts from one read of g
             st = launch_convert_g_bwd(d_g + p0 * B, pc, B, B, ws + L.g_off, pcp * Bp, ws + L.gt_off, Bp * pcp, pcp,
-                                      Bp, s);
+                                      Bp, nullptr, s);
             if (st != ZP_OK) return st;
         } else if (!g_in_place) {
-            st = launch_convert(d_g + p0 * B, pc, B, B, ct, ws + L.g_off, Bp, pcp, pcp * Bp, false, s);
+            st = launch_convert(d_g + p0 * B, pc, B, B, ct, ws + L.g_off, Bp, pcp, pcp * Bp, nullptr, s);
             if (st != ZP_OK) return st;
         }
         if (run_c) {
@@ -1039,17 +1066,17 @@ zp_status zp_series_bwd2(const int32_t *h_n, const int32_t *h_m, int64_t M, cons
             if (ct == CT_BF3)
                 g.b = Operand{ws + L.gt_off, Bp / 16, Bp * pcp, LAY_FRAG};
             else
-                g.b = Operand{gbuf, Bp, pcp * Bp, LAY_XC};
+                g.b = Operand{gbuf, ldg, pcp * ldg, LAY_XC};
             g.M = M;
             g.N = B;
             g.K = pcp;
-            g.splits = splits_within(M, B, pcp, ct, L.S);
+            g.splits = splits;
             g.epi = EPI_PARTIAL;
             g.C = (double *)(ws + L.pc_off);
             g.ldc = B;
             st = launch_gemm(g, s);
             if (st != ZP_OK) return st;
-            st = launch_splitk_reduce(g.C, g.splits, M, B, d_out_c, B, p0 > 0, s);
+            st = launch_splitk_reduce(g.C, g.splits, M, B, d_out_c, p0 > 0, s);
             if (st != ZP_OK) return st;
         }
         if (run_u || run_e) {

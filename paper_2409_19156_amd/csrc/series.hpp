@@ -119,10 +119,10 @@ zp_status launch_fused_grad(const Plan &p, const double *r, const double *th, in
                             const double *tr, const double *tt, const double *g, int64_t B, bool norm, double *part,
                             size_t part_bytes, double *out, hipStream_t s);
 
-// dst (compute type, [R_pad][C_pad] or transposed [C_pad][R_pad]) from a
-// row-major FP64 src [R][C] (leading dimension lds); zero padding.
+// dst (compute type, [rows_pad][ldd]) from a row-major FP64 src [R][C]
+// (leading dimension lds), row r times roww[r] (roww nullable); zero padding.
 zp_status launch_convert(const double *src, int64_t R, int64_t C, int64_t lds, int ct, void *dst, int64_t ldd,
-                         int64_t rows_pad, int64_t sub, bool transpose, hipStream_t s);
+                         int64_t rows_pad, int64_t sub, const double *roww, hipStream_t s);
 
 // bf16 x 3 operand in MFMA fragment order for B(k = e, j = x) = src[perm[e]][x]:
 // per k step of 32 and block of 16 columns, 64 lanes x 8 bf16 contiguous (lane
@@ -135,20 +135,36 @@ zp_status launch_convert_gather_frag(const double *src, const int32_t *perm, int
 // operands from one read: [xpad_r][xpad_c] k-contiguous into dst_c (the
 // column-dot's B(k = set, j = point)) and, if dst_s is set, MFMA fragment
 // order into dst_s (the split-K's B(k = point, j = set)); xpad_r, xpad_c are
-// the padded point and set counts (multiples of 32 and 64).
+// the padded point and set counts (multiples of 32 and 64).  roww as above.
 zp_status launch_convert_g_bwd(const double *src, int64_t R, int64_t C, int64_t lds, void *dst_c, int64_t subc,
-                               void *dst_s, int64_t subs, int64_t xpad_r, int64_t xpad_c, hipStream_t s);
+                               void *dst_s, int64_t subs, int64_t xpad_r, int64_t xpad_c, const double *roww,
+                               hipStream_t s);
 // Zero the pad (modes >= M, points >= P) of a k-blocked bf16 operand.
 zp_status launch_zero_kb8(void *dst, int64_t M, int64_t Mp, int64_t P, int64_t ld, int64_t sub, hipStream_t s);
 
-// Zero the pad region of a [rows_pad][ld] compute-type plane set whose
-// valid block is [rows][cols].
+// Zero the pad region of a [rows_pad][ld] plane (FP64 or FP32) whose valid
+// block is [rows][cols].
 zp_status launch_zero_pad(void *dst, int ct, int64_t rows, int64_t cols, int64_t rows_pad, int64_t ld, int64_t sub,
                           hipStream_t s);
 
-// C[i*ldc + j] (=|+=) sum_s part[s][i][j] for s = 0..S-1, fixed order.
-zp_status launch_splitk_reduce(const double *part, int S, int64_t M, int64_t N, double *C, int64_t ldc,
-                               bool accumulate, hipStream_t s);
+// C[i][j] (=|+=) sum_s part[s][i][j] for s = 0..S-1, fixed order.
+zp_status launch_splitk_reduce(const double *part, int S, int64_t M, int64_t N, double *C, bool accumulate,
+                               hipStream_t s);
+// The same for coefficients C [M][B], divided by the integrals of Z_k^2 (after
+// the addition) if norm is set.
+zp_status launch_grad_reduce(const Plan &p, const double *part, int S, int64_t M, int64_t B, bool norm,
+                             bool accumulate, double *C, hipStream_t s);
+
+// Whether an FP64 split-K or column-dot of these sizes takes the narrow tiles
+// (64 columns): its B operand then needs 64, not 128, columns of padding.
+bool gemm_narrow(int64_t M, int64_t N, int splits);
+
+// zp_series_bwd for checked arguments; w: nullable weights of the rows of g
+// (dL/dc only), norm: dL/dc divided by the integrals of Z_k^2.
+zp_status series_bwd_run(const Plan &plan, int64_t M, const double *d_r, const double *d_theta, int64_t P,
+                         const double *d_c, int64_t B, int32_t prec, const double *d_g, const double *d_w, bool norm,
+                         const void *d_cache, double *d_grad_c, double *d_grad_r, double *d_grad_theta, void *d_ws,
+                         size_t ws_bytes, hipStream_t s);
 
 // out1[p] = sum_t part[t][0][p], out2[p] = sum_t part[t][1][p] (either nullable).
 zp_status launch_coldot_reduce(const double *part, int T, int64_t P, double *out1, double *out2, hipStream_t s);
