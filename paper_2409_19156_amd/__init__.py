@@ -8,8 +8,13 @@ a GPU these functions raise.
 """
 from __future__ import annotations
 
+import contextlib
+import ctypes
+import os
+
 import numpy as np
 import torch
+from torch.autograd import forward_ad
 
 from . import _lib
 from ._lib import ZpError
@@ -42,7 +47,15 @@ def _points(x: torch.Tensor, name: str) -> torch.Tensor:
 
 
 def _stream(dev: torch.device) -> int:
-    return torch.cuda.current_stream(dev).cuda_stream
+    return torch._C._cuda_getCurrentRawStream(dev.index)
+
+
+_HERE = contextlib.nullcontext()
+
+
+def _on(dev: torch.device):
+    """Context with ``dev`` current (nothing to do where it is already)."""
+    return _HERE if torch._C._cuda_getDevice() == dev.index else torch.cuda.device(dev)
 
 
 def basis_polar(n, m, r: torch.Tensor, theta: torch.Tensor, mask: int = Z,
@@ -63,7 +76,7 @@ def basis_polar(n, m, r: torch.Tensor, theta: torch.Tensor, mask: int = Z,
         out = torch.empty(shape, dtype=torch.float64, device=r.device)
     elif out.shape != shape or out.dtype != torch.float64 or not out.is_contiguous():
         raise ValueError("out must be a contiguous float64 tensor [popcount(mask), M, NR * NT]")
-    with torch.cuda.device(r.device):
+    with _on(r.device):
         st = lib.zp_basis_polar(nh.ctypes.data, mh.ctypes.data, M, r.data_ptr(), NR, theta.data_ptr(), NT,
                                 int(mask), out.data_ptr(), _stream(r.device))
     _lib.check(st, "zp_basis_polar")
@@ -76,7 +89,7 @@ def stream_fill(out: torch.Tensor, value: float = 0.0, nontemporal: bool = True)
     lib = _lib.load()
     if not isinstance(out, torch.Tensor) or not out.is_cuda or out.dtype != torch.float64 or not out.is_contiguous():
         raise TypeError("out must be a contiguous float64 GPU tensor")
-    with torch.cuda.device(out.device):
+    with _on(out.device):
         st = lib.zp_stream_fill(out.data_ptr(), out.numel(), float(value), 1 if nontemporal else 0, _stream(out.device))
     _lib.check(st, "zp_stream_fill")
     return out
@@ -95,7 +108,7 @@ def radial(n, m, r: torch.Tensor, max_dr: int = 0, out: torch.Tensor | None = No
         out = torch.empty((max_dr + 1, M, P), dtype=torch.float64, device=r.device)
     elif out.shape != (max_dr + 1, M, P) or out.dtype != torch.float64 or not out.is_contiguous():
         raise ValueError("out must be a contiguous float64 tensor [max_dr+1, M, P]")
-    with torch.cuda.device(r.device):
+    with _on(r.device):
         st = lib.zp_radial(nh.ctypes.data, mh.ctypes.data, M, r.data_ptr(), P, int(max_dr), out.data_ptr(),
                            _stream(r.device))
     _lib.check(st, "zp_radial")
@@ -111,7 +124,7 @@ def radial_direct(n, m, r: torch.Tensor, max_dr: int = 0) -> torch.Tensor:
     r = _points(r, "r")
     M, P = nh.size, r.numel()
     out = torch.empty((max_dr + 1, M, P), dtype=torch.float64, device=r.device)
-    with torch.cuda.device(r.device):
+    with _on(r.device):
         st = lib.zp_radial_direct(nh.ctypes.data, mh.ctypes.data, M, r.data_ptr(), P, int(max_dr), out.data_ptr(),
                                   _stream(r.device))
     _lib.check(st, "zp_radial_direct")
@@ -127,7 +140,7 @@ def radial_zernike_recursion(n, m, r: torch.Tensor, max_dr: int = 0) -> torch.Te
     r = _points(r, "r")
     M, P = nh.size, r.numel()
     out = torch.empty((max_dr + 1, M, P), dtype=torch.float64, device=r.device)
-    with torch.cuda.device(r.device):
+    with _on(r.device):
         st = lib.zp_radial_zernike_recursion(nh.ctypes.data, mh.ctypes.data, M, r.data_ptr(), P, int(max_dr),
                                              out.data_ptr(), _stream(r.device))
     _lib.check(st, "zp_radial_zernike_recursion")
@@ -150,7 +163,7 @@ def basis(n, m, r: torch.Tensor, theta: torch.Tensor, mask: int = Z, out: torch.
         out = torch.empty(shape, dtype=torch.float64, device=r.device)
     elif out.shape != shape or out.dtype != torch.float64 or not out.is_contiguous():
         raise ValueError("out must be a contiguous float64 tensor [popcount(mask), M, P]")
-    with torch.cuda.device(r.device):
+    with _on(r.device):
         st = lib.zp_basis(nh.ctypes.data, mh.ctypes.data, M, r.data_ptr(), theta.data_ptr(), P, int(mask),
                           out.data_ptr(), _stream(r.device))
     _lib.check(st, "zp_basis")
@@ -169,8 +182,6 @@ def _prec_code(prec) -> int:
 
 def series_sizes(M: int, P: int, B: int, prec="fp64"):
     """(workspace bytes for one pass, minimum workspace bytes, basis-cache bytes)."""
-    import ctypes
-
     lib = _lib.load()
     full = ctypes.c_size_t()
     mn = ctypes.c_size_t()
@@ -182,8 +193,6 @@ def series_sizes(M: int, P: int, B: int, prec="fp64"):
 
 
 def _budget(mem_budget):
-    import os
-
     if mem_budget is not None:
         return int(mem_budget)
     return int(os.environ.get("ZP_MEM_BUDGET_BYTES", str(32 << 30)))
@@ -198,10 +207,16 @@ def _keeps_basis(B: int, prec) -> bool:
     return _prec_code(prec) != PREC["fp64"] or B > _FUSED_SETS
 
 
+def _buffer(sizes, what: str, args, budget, device):
+    """Workspace tensor for the library's size query ``sizes`` within ``budget``."""
+    full, mn = ctypes.c_size_t(), ctypes.c_size_t()
+    _lib.check(sizes(*args, ctypes.byref(full), ctypes.byref(mn)), what)
+    nbytes = full.value if full.value <= budget else max(mn.value, budget)
+    return torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
+
+
 def _workspace(M, P, B, prec, budget, device):
-    full, mn, _ = series_sizes(M, P, B, prec)
-    nbytes = full if full <= budget else max(mn, budget)
-    return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    return _buffer(_lib.load().zp_series_workspace, "zp_series_workspace", (M, P, B, _prec_code(prec)), budget, device)
 
 
 def _coef(c: torch.Tensor, M: int) -> torch.Tensor:
@@ -227,7 +242,7 @@ def series_forward(n, m, r, theta, c, prec="fp64", cache: torch.Tensor | None = 
         return f.zero_()
     if ws is None:
         ws = _workspace(M, P, B, prec, _budget(mem_budget), r.device)
-    with torch.cuda.device(r.device):
+    with _on(r.device):
         st = lib.zp_series_fwd(nh.ctypes.data, mh.ctypes.data, M, r.data_ptr(), theta.data_ptr(), P, c.data_ptr(), B,
                                _prec_code(prec), f.data_ptr(), cache.data_ptr() if cache is not None else None,
                                ws.data_ptr(), ws.numel(), _stream(r.device))
@@ -257,7 +272,7 @@ def series_backward(n, m, r, theta, c, g, prec="fp64", cache: torch.Tensor | Non
     if ws is None:
         ws = _workspace(M, P, B, prec, _budget(mem_budget), dev)
     ptr = (lambda t: t.data_ptr() if t is not None else None)
-    with torch.cuda.device(dev):
+    with _on(dev):
         st = lib.zp_series_bwd(nh.ctypes.data, mh.ctypes.data, M, r.data_ptr(), theta.data_ptr(), P, c.data_ptr(), B,
                                _prec_code(prec), g.data_ptr(), ptr(cache), ptr(gc), ptr(gr), ptr(gt), ws.data_ptr(),
                                ws.numel(), _stream(dev))
@@ -289,7 +304,7 @@ def series_jvp(n, m, r, theta, c, tc=None, tr=None, ttheta=None, prec="fp64", ws
     if ws is None:
         ws = _workspace(M, P, B, prec, _budget(mem_budget), r.device)
     ptr = (lambda t: t.data_ptr() if t is not None else None)
-    with torch.cuda.device(r.device):
+    with _on(r.device):
         st = lib.zp_series_jvp(nh.ctypes.data, mh.ctypes.data, M, r.data_ptr(), theta.data_ptr(), P, c.data_ptr(), B,
                                _prec_code(prec), ptr(tc), ptr(tr), ptr(ttheta), tf.data_ptr(), ws.data_ptr(),
                                ws.numel(), _stream(r.device))
@@ -304,8 +319,6 @@ def series_backward2(n, m, r, theta, c, g, uc=None, ur=None, ut=None, prec="fp64
     derivatives of <uc, dL/dc> + <ur, dL/dr> + <ut, dL/dtheta> with respect to
     (g, c, r, theta); entries not in ``need`` are None, missing cotangents
     count as zero."""
-    import ctypes
-
     lib = _lib.load()
     nh, mh = modes_i32(n, m)
     r, theta = _points(r, "r"), _points(theta, "theta")
@@ -325,14 +338,10 @@ def series_backward2(n, m, r, theta, c, g, uc=None, ur=None, ut=None, prec="fp64
     if M == 0 or P == 0 or B == 0:
         return tuple(None if x is None else x.zero_() for x in outs)
     if ws is None:
-        full, mn = ctypes.c_size_t(), ctypes.c_size_t()
-        _lib.check(lib.zp_series_bwd2_workspace(M, P, B, _prec_code(prec), ctypes.byref(full), ctypes.byref(mn)),
-                   "zp_series_bwd2_workspace")
-        budget = _budget(mem_budget)
-        nbytes = full.value if full.value <= budget else max(mn.value, budget)
-        ws = torch.empty(nbytes, dtype=torch.uint8, device=dev)
+        ws = _buffer(lib.zp_series_bwd2_workspace, "zp_series_bwd2_workspace", (M, P, B, _prec_code(prec)),
+                     _budget(mem_budget), dev)
     ptr = (lambda t: t.data_ptr() if t is not None else None)
-    with torch.cuda.device(dev):
+    with _on(dev):
         st = lib.zp_series_bwd2(nh.ctypes.data, mh.ctypes.data, M, r.data_ptr(), theta.data_ptr(), P, c.data_ptr(), B,
                                 _prec_code(prec), g.data_ptr(), ptr(uc), ptr(ur), ptr(ut), *(ptr(x) for x in outs),
                                 ws.data_ptr(), ws.numel(), _stream(dev))
@@ -378,10 +387,11 @@ class ZernikeSeries(torch.autograd.Function):
         nh, mh = modes_i32(n, m)
         M, P, B = nh.size, r.numel(), c.shape[1]
         budget = _budget(mem_budget)
-        _, _, cache_bytes = series_sizes(M, P, B, prec)
         cache = None
-        if M and P and B and cache_bytes <= budget and _keeps_basis(B, prec):
-            cache = torch.empty(cache_bytes, dtype=torch.uint8, device=r.device)
+        if M and P and B and _keeps_basis(B, prec):
+            _, _, cache_bytes = series_sizes(M, P, B, prec)
+            if cache_bytes <= budget:
+                cache = torch.empty(cache_bytes, dtype=torch.uint8, device=r.device)
         f = series_forward(nh, mh, r, theta, c, prec, cache=cache, mem_budget=budget)
         ctx.modes = (nh, mh)
         ctx.prec = prec
@@ -395,8 +405,13 @@ class ZernikeSeries(torch.autograd.Function):
     def backward(ctx, g):
         c, r, theta = ctx.saved_tensors
         need = tuple(bool(x) for x in ctx.needs_input_grad[:3])
-        gc, gr, gt = _SeriesBackward.apply(c, r, theta, g.contiguous(), ctx.modes, ctx.prec, ctx.cache, ctx.budget,
-                                           need)
+        args = (c, r, theta, g.contiguous(), ctx.modes, ctx.prec, ctx.cache, ctx.budget, need)
+        if torch.is_grad_enabled() or forward_ad._current_level >= 0:
+            gc, gr, gt = _SeriesBackward.apply(*args)
+        else:  # nobody differentiates the gradients: no graph node for them
+            nh, mh = ctx.modes
+            gc, gr, gt = series_backward(nh, mh, c=c, r=r, theta=theta, g=args[3], prec=ctx.prec, cache=ctx.cache,
+                                         need=need, mem_budget=ctx.budget)
         if gr is not None:
             gr = gr.view_as(r)
         if gt is not None:
@@ -438,8 +453,6 @@ def series_analysis(n, m, r, theta, w, f, prec="fp64", ws: torch.Tensor | None =
                     mem_budget=None) -> torch.Tensor:
     """Coefficients c[k, b] = (1/N_k) sum_p w_p Z_k(r_p, theta_p) f[p, b] from
     samples f [P, B] with quadrature weights w [P] (N_k = integral of Z_k^2)."""
-    import ctypes
-
     lib = _lib.load()
     nh, mh = modes_i32(n, m)
     r, theta, w = _points(r, "r"), _points(theta, "theta"), _points(w, "w")
@@ -452,13 +465,9 @@ def series_analysis(n, m, r, theta, w, f, prec="fp64", ws: torch.Tensor | None =
     if M == 0 or B == 0:
         return c
     if ws is None:
-        full, mn = ctypes.c_size_t(), ctypes.c_size_t()
-        _lib.check(lib.zp_series_analysis_workspace(M, P, B, _prec_code(prec), ctypes.byref(full), ctypes.byref(mn)),
-                   "zp_series_analysis_workspace")
-        budget = _budget(mem_budget)
-        nbytes = full.value if full.value <= budget else max(mn.value, budget)
-        ws = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=r.device)
-    with torch.cuda.device(r.device):
+        ws = _buffer(lib.zp_series_analysis_workspace, "zp_series_analysis_workspace", (M, P, B, _prec_code(prec)),
+                     _budget(mem_budget), r.device)
+    with _on(r.device):
         st = lib.zp_series_analysis(nh.ctypes.data, mh.ctypes.data, M, r.data_ptr(), theta.data_ptr(), w.data_ptr(),
                                     P, f.data_ptr(), B, _prec_code(prec), c.data_ptr(), ws.data_ptr(), ws.numel(),
                                     _stream(r.device))
@@ -484,8 +493,6 @@ def modes3_i32(n, m, l):
 def series3d_sizes(n, m, l, P: int, Q: int, B: int, prec="fp64"):
     """(workspace bytes for one pass, minimum workspace bytes, basis-cache bytes)
     of the three-dimensional series."""
-    import ctypes
-
     lib = _lib.load()
     nh, mh, lh = modes3_i32(n, m, l)
     full, mn, cb = ctypes.c_size_t(), ctypes.c_size_t(), ctypes.c_size_t()
@@ -498,9 +505,8 @@ def series3d_sizes(n, m, l, P: int, Q: int, B: int, prec="fp64"):
 
 
 def _workspace3(nh, mh, lh, P, Q, B, prec, budget, device):
-    full, mn, _ = series3d_sizes(nh, mh, lh, P, Q, B, prec)
-    nbytes = full if full <= budget else max(mn, budget)
-    return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    return _buffer(_lib.load().zp_series3d_workspace, "zp_series3d_workspace",
+                   (nh.ctypes.data, mh.ctypes.data, lh.ctypes.data, nh.size, P, Q, B, _prec_code(prec)), budget, device)
 
 
 def series3d_forward(n, m, l, r, theta, phi, c, prec="fp64", cache: torch.Tensor | None = None,
@@ -519,7 +525,7 @@ def series3d_forward(n, m, l, r, theta, phi, c, prec="fp64", cache: torch.Tensor
         return f.zero_()
     if ws is None:
         ws = _workspace3(nh, mh, lh, P, Q, B, prec, _budget(mem_budget), r.device)
-    with torch.cuda.device(r.device):
+    with _on(r.device):
         st = lib.zp_series3d_fwd(nh.ctypes.data, mh.ctypes.data, lh.ctypes.data, J, r.data_ptr(), theta.data_ptr(), P,
                                  phi.data_ptr(), Q, c.data_ptr(), B, _prec_code(prec), f.data_ptr(),
                                  cache.data_ptr() if cache is not None else None, ws.data_ptr(), ws.numel(),
@@ -549,7 +555,7 @@ def series3d_backward(n, m, l, r, theta, phi, c, g, prec="fp64", cache: torch.Te
     if ws is None:
         ws = _workspace3(nh, mh, lh, P, Q, B, prec, _budget(mem_budget), dev)
     ptr = (lambda t: t.data_ptr() if t is not None else None)
-    with torch.cuda.device(dev):
+    with _on(dev):
         st = lib.zp_series3d_bwd(nh.ctypes.data, mh.ctypes.data, lh.ctypes.data, J, r.data_ptr(), theta.data_ptr(), P,
                                  phi.data_ptr(), Q, c.data_ptr(), B, _prec_code(prec), g.data_ptr(), ptr(cache),
                                  *(ptr(x) for x in outs), ws.data_ptr(), ws.numel(), _stream(dev))
@@ -569,9 +575,9 @@ class ZernikeSeries3D(torch.autograd.Function):
         J, P, Q, B = nh.size, r.numel(), phi.numel(), c.shape[1]
         budget = _budget(mem_budget)
         cache = None
-        if J and P and Q and B:
+        if J and P and Q and B and _keeps_basis(Q * B, prec):
             _, _, cache_bytes = series3d_sizes(nh, mh, lh, P, Q, B, prec)
-            if cache_bytes <= budget and _keeps_basis(Q * B, prec):
+            if cache_bytes <= budget:
                 cache = torch.empty(cache_bytes, dtype=torch.uint8, device=r.device)
         f = series3d_forward(nh, mh, lh, r, theta, phi, c, prec, cache=cache, mem_budget=budget)
         ctx.modes = (nh, mh, lh)

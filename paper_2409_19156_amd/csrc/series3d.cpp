@@ -108,6 +108,19 @@ zp_status upload3(Plan3 &p)
 
 } // namespace
 
+// A cached list equal to this one, on any device (null: none).  Its modes have
+// been checked and its distinct pairs are known.
+static std::shared_ptr<Plan3> find_plan3(const int32_t *n, const int32_t *m, const int32_t *l, int64_t J)
+{
+    if (J <= 0 || !n || !m || !l) return nullptr;
+    std::lock_guard<std::mutex> lock(g_mu3);
+    for (const auto &p : g_cache3)
+        if ((int64_t)p->n.size() == J && std::equal(p->n.begin(), p->n.end(), n) &&
+            std::equal(p->m.begin(), p->m.end(), m) && std::equal(p->l.begin(), p->l.end(), l))
+            return p;
+    return nullptr;
+}
+
 // As get_plan: the lookup under the lock, a missing plan built without it,
 // and plans pushed out of the cache released after the lock is dropped.
 zp_status get_plan3(const int32_t *n, const int32_t *m, const int32_t *l, int64_t J, std::shared_ptr<Plan3> *out)
@@ -171,25 +184,31 @@ namespace {
 
 size_t al(size_t x) { return (x + 255) / 256 * 256; }
 
+// known: the list's cached plan, if there is one (18 513 modes: a comparison
+// takes about 10 us, checking and deduplicating the list again about 150).
 zp_status checks3(const int32_t *n, const int32_t *m, const int32_t *l, int64_t J, int64_t P, int64_t Q, int64_t B,
-                  int32_t prec)
+                  int32_t prec, std::shared_ptr<Plan3> *known)
 {
-    zp_status st = check_modes_arg(n, m, J);
-    if (st != ZP_OK) return st;
-    if (J > 0 && !l) return set_error(ZP_ERR_ARG, "null l array");
-    for (int64_t j = 0; j < J; ++j)
-        if (l[j] < -ZP_L_MAX || l[j] > ZP_L_MAX) {
-            char buf[96];
-            snprintf(buf, sizeof buf, "mode %lld: |l| = %d exceeds ZP_L_MAX", (long long)j, l[j]);
-            return set_error(ZP_ERR_MODE, buf);
-        }
+    *known = find_plan3(n, m, l, J);
+    if (!*known) {
+        zp_status st = check_modes_arg(n, m, J);
+        if (st != ZP_OK) return st;
+        if (J > 0 && !l) return set_error(ZP_ERR_ARG, "null l array");
+        for (int64_t j = 0; j < J; ++j)
+            if (l[j] < -ZP_L_MAX || l[j] > ZP_L_MAX) {
+                char buf[96];
+                snprintf(buf, sizeof buf, "mode %lld: |l| = %d exceeds ZP_L_MAX", (long long)j, l[j]);
+                return set_error(ZP_ERR_MODE, buf);
+            }
+    }
     if (P < 0 || Q < 0 || B < 0) return set_error(ZP_ERR_ARG, "negative P, Q or B");
     if (prec < ZP_FP64 || prec > ZP_BF16X3) return set_error(ZP_ERR_PREC, "prec must be ZP_FP64, ZP_FP32 or ZP_BF16X3");
     return ZP_OK;
 }
 
-int64_t distinct_pairs(const int32_t *n, const int32_t *m, int64_t J)
+int64_t distinct_pairs(const int32_t *n, const int32_t *m, int64_t J, const std::shared_ptr<Plan3> &known)
 {
+    if (known) return (int64_t)known->un.size();
     std::vector<int32_t> un, um, owner;
     dedup_modes(n, m, J, un, um, owner);
     return (int64_t)un.size();
@@ -201,14 +220,26 @@ size_t head_bytes(int64_t U, int64_t Q, int64_t B) { return 2 * al(8 * (size_t)U
 // Host-side check that ws_bytes covers the head and the planar series'
 // minimum, before any device work.
 zp_status check_ws3(const int32_t *n, const int32_t *m, int64_t J, int64_t P, int64_t Q, int64_t B, int32_t prec,
-                    size_t ws_bytes)
+                    size_t ws_bytes, const std::shared_ptr<Plan3> &known)
 {
-    const int64_t U = distinct_pairs(n, m, J);
+    const int64_t U = distinct_pairs(n, m, J, known);
     size_t f = 0, mn = 0;
     zp_status st = zp_series_workspace(U, P, Q * B, prec, &f, &mn);
     if (st != ZP_OK) return st;
     if (ws_bytes < head_bytes(U, Q, B) + mn)
         return set_error(ZP_ERR_WORKSPACE, "workspace smaller than the minimum (zp_series3d_workspace)");
+    return ZP_OK;
+}
+
+// The list's plan on the current device.
+zp_status plan3_here(const int32_t *n, const int32_t *m, const int32_t *l, int64_t J,
+                     const std::shared_ptr<Plan3> &known, std::shared_ptr<Plan3> *out)
+{
+    int dev = 0;
+    zp_status st = hip_check(hipGetDevice(&dev), "hipGetDevice");
+    if (st != ZP_OK) return st;
+    if (!known || known->device != dev) return get_plan3(n, m, l, J, out);
+    *out = known;
     return ZP_OK;
 }
 
@@ -219,10 +250,11 @@ extern "C" {
 zp_status zp_series3d_workspace(const int32_t *h_n, const int32_t *h_m, const int32_t *h_l, int64_t J, int64_t P,
                                 int64_t Q, int64_t B, int32_t prec, size_t *full_bytes, size_t *min_bytes)
 {
-    zp_status st = checks3(h_n, h_m, h_l, J, P, Q, B, prec);
+    std::shared_ptr<Plan3> known;
+    zp_status st = checks3(h_n, h_m, h_l, J, P, Q, B, prec, &known);
     if (st != ZP_OK) return st;
     if (!full_bytes) return set_error(ZP_ERR_ARG, "null full_bytes");
-    const int64_t U = distinct_pairs(h_n, h_m, J);
+    const int64_t U = distinct_pairs(h_n, h_m, J, known);
     size_t f = 0, mn = 0;
     st = zp_series_workspace(U, P, Q * B, prec, &f, &mn);
     if (st != ZP_OK) return st;
@@ -234,9 +266,10 @@ zp_status zp_series3d_workspace(const int32_t *h_n, const int32_t *h_m, const in
 zp_status zp_series3d_cache_bytes(const int32_t *h_n, const int32_t *h_m, const int32_t *h_l, int64_t J, int64_t P,
                                   int32_t prec, size_t *bytes)
 {
-    zp_status st = checks3(h_n, h_m, h_l, J, P, 0, 0, prec);
+    std::shared_ptr<Plan3> known;
+    zp_status st = checks3(h_n, h_m, h_l, J, P, 0, 0, prec, &known);
     if (st != ZP_OK) return st;
-    return zp_series_cache_bytes(distinct_pairs(h_n, h_m, J), P, prec, bytes);
+    return zp_series_cache_bytes(distinct_pairs(h_n, h_m, J, known), P, prec, bytes);
 }
 
 zp_status zp_series3d_fwd(const int32_t *h_n, const int32_t *h_m, const int32_t *h_l, int64_t J, const double *d_r,
@@ -244,16 +277,17 @@ zp_status zp_series3d_fwd(const int32_t *h_n, const int32_t *h_m, const int32_t 
                           int64_t B, int32_t prec, double *d_f, void *d_cache, void *d_ws, size_t ws_bytes,
                           void *stream)
 {
-    zp_status st = checks3(h_n, h_m, h_l, J, P, Q, B, prec);
+    std::shared_ptr<Plan3> known;
+    zp_status st = checks3(h_n, h_m, h_l, J, P, Q, B, prec, &known);
     if (st != ZP_OK) return st;
     if (J == 0 || P == 0 || Q == 0 || B == 0) return ZP_OK;
     if (!d_r || !d_theta || !d_phi || !d_c || !d_f) return set_error(ZP_ERR_ARG, "null pointer");
     if (!d_ws || ((uintptr_t)d_ws & 255)) return set_error(ZP_ERR_ARG, "workspace must be non-null and 256-byte aligned");
     if ((uintptr_t)d_cache & 255) return set_error(ZP_ERR_ARG, "cache must be 256-byte aligned");
-    st = check_ws3(h_n, h_m, J, P, Q, B, prec, ws_bytes);
+    st = check_ws3(h_n, h_m, J, P, Q, B, prec, ws_bytes, known);
     if (st != ZP_OK) return st;
     std::shared_ptr<Plan3> p;
-    st = get_plan3(h_n, h_m, h_l, J, &p);
+    st = plan3_here(h_n, h_m, h_l, J, known, &p);
     if (st != ZP_OK) return st;
     const int64_t U = (int64_t)p->un.size();
     const size_t head = head_bytes(U, Q, B);
@@ -271,17 +305,18 @@ zp_status zp_series3d_bwd(const int32_t *h_n, const int32_t *h_m, const int32_t 
                           double *d_grad_r, double *d_grad_theta, double *d_grad_phi, void *d_ws, size_t ws_bytes,
                           void *stream)
 {
-    zp_status st = checks3(h_n, h_m, h_l, J, P, Q, B, prec);
+    std::shared_ptr<Plan3> known;
+    zp_status st = checks3(h_n, h_m, h_l, J, P, Q, B, prec, &known);
     if (st != ZP_OK) return st;
     if (J == 0 || P == 0 || Q == 0 || B == 0) return ZP_OK;
     if (!d_r || !d_theta || !d_phi || !d_c || !d_g) return set_error(ZP_ERR_ARG, "null pointer");
     if (!d_grad_c && !d_grad_r && !d_grad_theta && !d_grad_phi) return ZP_OK;
     if (!d_ws || ((uintptr_t)d_ws & 255)) return set_error(ZP_ERR_ARG, "workspace must be non-null and 256-byte aligned");
     if ((uintptr_t)d_cache & 255) return set_error(ZP_ERR_ARG, "cache must be 256-byte aligned");
-    st = check_ws3(h_n, h_m, J, P, Q, B, prec, ws_bytes);
+    st = check_ws3(h_n, h_m, J, P, Q, B, prec, ws_bytes, known);
     if (st != ZP_OK) return st;
     std::shared_ptr<Plan3> p;
-    st = get_plan3(h_n, h_m, h_l, J, &p);
+    st = plan3_here(h_n, h_m, h_l, J, known, &p);
     if (st != ZP_OK) return st;
     const int64_t U = (int64_t)p->un.size();
     const size_t head = head_bytes(U, Q, B);
