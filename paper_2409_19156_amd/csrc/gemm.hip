@@ -253,19 +253,28 @@ template <> struct Cfg<CT_BF3> {
 // tiles cost little there (the FP32 forward, narrow, measured 6% slower).  The
 // FP64 split-K and column-dot take it on small problems (below), where twice
 // the workgroups fill the chip better.
-template <int CT, int EPI> constexpr bool kNarrowDefault = CT == CT_F32 && EPI != EPI_STORE;
+//
+// Small shape (forward only): 32 x 16 wave tiles, a 64 x 64 workgroup tile, for
+// bf16 128 x 32 (its A tile has to give every thread a 16-byte load).  A
+// workgroup sums over all modes, so with fewer 128 x 128 tiles than CUs the
+// launch takes one such tile's time whatever its size; a quarter of the tile
+// takes less than half of that and four times the CUs.  An element's sum does
+// not depend on the shape.
+enum Shape : int { WIDE = 0, NARROW = 1, SMALL = 2 };
+template <int CT, int EPI> constexpr int kShape = CT == CT_F32 && EPI != EPI_STORE ? NARROW : WIDE;
 
-template <int CT, int EPI, bool NARROW_ = kNarrowDefault<CT, EPI>> struct CfgE : Cfg<CT> {
-    static constexpr bool NARROW = NARROW_;
-    static constexpr int BN = NARROW ? 64 : Cfg<CT>::BN;
-    static constexpr int WN = NARROW ? 16 : Cfg<CT>::WN;
-    static constexpr bool W4 = CT == CT_F64 || NARROW; // compiled for four waves per SIMD
+template <int CT, int EPI, int SHAPE = kShape<CT, EPI>> struct CfgE : Cfg<CT> {
+    static constexpr int BM = SHAPE == SMALL && CT != CT_BF3 ? 64 : Cfg<CT>::BM;
+    static constexpr int BN = SHAPE == NARROW ? 64 : SHAPE == SMALL ? (CT == CT_BF3 ? 32 : 64) : Cfg<CT>::BN;
+    static constexpr int WM = SHAPE == SMALL ? 32 : Cfg<CT>::WM;
+    static constexpr int WN = SHAPE == WIDE ? Cfg<CT>::WN : 16;
+    static constexpr bool W4 = CT == CT_F64 || SHAPE != WIDE; // compiled for four waves per SIMD
 };
 
-template <int CT, int ALAY, int BLAY, int EPI, int NSET, bool NARROW>
+template <int CT, int ALAY, int BLAY, int EPI, int NSET, int SHAPE>
 __device__ __forceinline__ void gemm_body(const GemmDesc &g)
 {
-    using C = CfgE<CT, EPI, NARROW>;
+    using C = CfgE<CT, EPI, SHAPE>;
     constexpr int BM = C::BM, BN = C::BN, BK = C::BK, WM = C::WM, WN = C::WN;
     using TR = CTr<CT>;
     using T = typename TR::T;
@@ -274,7 +283,7 @@ __device__ __forceinline__ void gemm_body(const GemmDesc &g)
     constexpr bool BFRAG = BLAY == LAY_FRAG;
     static_assert(!BFRAG || CT == CT_BF3, "fragment-order operands are bf16");
     using TA = Tile<CT, BM, BK, ALAY>;
-    using TB = Tile<CT, BN, BK, BFRAG ? LAY_KC : BLAY>;
+    using TB = Tile<CT, BFRAG ? 128 : BN, BK, BFRAG ? LAY_KC : BLAY>; // (BFRAG: not used)
     constexpr int NP = TR::NP;
     constexpr int FM = WM / 16, FN = WN / 16;
     constexpr bool MIXED = CT != CT_F64;
@@ -550,7 +559,7 @@ __device__ __forceinline__ void gemm_body(const GemmDesc &g)
 template <int CT, int ALAY, int BLAY, int EPI>
 __global__ __launch_bounds__(kThreads) void gemm_kernel(GemmDesc g)
 {
-    gemm_body<CT, ALAY, BLAY, EPI, 2, kNarrowDefault<CT, EPI>>(g);
+    gemm_body<CT, ALAY, BLAY, EPI, 2, WIDE>(g);
 }
 
 // The same kernel compiled for four waves per SIMD (at most 128 registers,
@@ -563,20 +572,51 @@ __global__ __launch_bounds__(kThreads) void gemm_kernel(GemmDesc g)
 // and 9% faster than 64 x 32 wave tiles at one workgroup per CU.  The FP32
 // forward and the bf16 instances need 170-220 registers and keep one
 // workgroup per CU.
-template <int CT, int ALAY, int BLAY, int EPI, bool NARROW>
+template <int CT, int ALAY, int BLAY, int EPI, int SHAPE>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void gemm_kernel_w4(GemmDesc g)
 {
-    gemm_body<CT, ALAY, BLAY, EPI, 1, NARROW>(g);
+    gemm_body<CT, ALAY, BLAY, EPI, 1, SHAPE>(g);
 }
 
-template <int CT, int ALAY, int BLAY, int EPI, bool NARROW>
+// The forward's tile shape: the one whose last round of workgroups ends first.
+// A CU takes its workgroups' tiles at a rate that hardly depends on how many it
+// holds, so a launch takes ceil(tiles / CUs) tiles' time.  In quarters of a
+// wide tile a small one costs 1.1 (FP32, FP64) or, for bf16, whose A fragments
+// it reads for 32 columns instead of 128, 2.  FP64 with at most one wide tile
+// per CU gains from the small tiles' occupancy what they cost.  Measured, wide
+// -> small, modes x points x sets, us per forward (basis included):
+//   FP32   861 x 16 384 x  64 (128 ->    256 tiles)   101 ->  55
+//   FP32  2145 x  2 048 x 300 ( 48 ->    160 tiles)    194 ->  79
+//   FP32   861 x 40 000 x 128 (313 ->  1 250 tiles)    203 -> 155
+//   FP32   861 x 65 536 x 128 (512 ->  2 048 tiles)    253 -> 252  stays wide
+//   FP32  2145 x  8 192 x 1024 (512 -> 2 048 tiles)    397 -> 417  stays wide
+//   FP64   861 x 16 384 x 256 (256 ->  1 024 tiles)    159 -> 153
+//   FP64   861 x 65 536 x 256 (1 024 -> 4 096 tiles)   568 -> 628  stays wide
+//   FP64  5151 x  4 096 x 256 ( 64 ->    256 tiles)    741 -> 253
+//   bf16  2145 x  8 192 x  64 ( 64 ->    128 tiles)    137 -> 108
+//   bf16   861 x 16 384 x 256 (256 ->  1 024 tiles)     96 -> 118  stays wide
+template <int CT> bool small_tiles(int64_t M, int64_t N)
+{
+    using W = CfgE<CT, EPI_STORE, WIDE>;
+    using S = CfgE<CT, EPI_STORE, SMALL>;
+    if (N > (int64_t)65535 * S::BN) return false; // grid.y
+    const int64_t cus = device_cus();
+    auto rounds = [&](int64_t bm, int64_t bn) {
+        return (((M + bm - 1) / bm) * ((N + bn - 1) / bn) + cus - 1) / cus;
+    };
+    const int64_t wide = rounds(W::BM, W::BN), small = rounds(S::BM, S::BN);
+    if (CT == CT_F64 && wide == 1) return true;
+    return (CT == CT_BF3 ? 20 : 11) * small < 40 * wide;
+}
+
+template <int CT, int ALAY, int BLAY, int EPI, int SHAPE>
 hipError_t launch_shape(const GemmDesc &g, hipStream_t s)
 {
-    using C = CfgE<CT, EPI, NARROW>;
+    using C = CfgE<CT, EPI, SHAPE>;
     const dim3 grid((unsigned)((g.M + C::BM - 1) / C::BM), (unsigned)((g.N + C::BN - 1) / C::BN),
                     (unsigned)g.splits);
     if constexpr (C::W4)
-        hipLaunchKernelGGL((gemm_kernel_w4<CT, ALAY, BLAY, EPI, NARROW>), grid, dim3(kThreads), 0, s, g);
+        hipLaunchKernelGGL((gemm_kernel_w4<CT, ALAY, BLAY, EPI, SHAPE>), grid, dim3(kThreads), 0, s, g);
     else
         hipLaunchKernelGGL((gemm_kernel<CT, ALAY, BLAY, EPI>), grid, dim3(kThreads), 0, s, g);
     return hipGetLastError();
@@ -590,9 +630,12 @@ template <int CT, int ALAY, int BLAY, int EPI>
 hipError_t launch_t(const GemmDesc &g, hipStream_t s)
 {
     if constexpr (CT == CT_F64 && EPI != EPI_STORE) {
-        if (gemm_narrow(g.M, g.N, g.splits)) return launch_shape<CT, ALAY, BLAY, EPI, true>(g, s);
+        if (gemm_narrow(g.M, g.N, g.splits)) return launch_shape<CT, ALAY, BLAY, EPI, NARROW>(g, s);
     }
-    return launch_shape<CT, ALAY, BLAY, EPI, kNarrowDefault<CT, EPI>>(g, s);
+    if constexpr (EPI == EPI_STORE) {
+        if (small_tiles<CT>(g.M, g.N)) return launch_shape<CT, ALAY, BLAY, EPI, SMALL>(g, s);
+    }
+    return launch_shape<CT, ALAY, BLAY, EPI, kShape<CT, EPI>>(g, s);
 }
 
 // The operand-layout combinations the series uses (anything else is an
