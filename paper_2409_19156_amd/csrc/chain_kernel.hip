@@ -31,6 +31,7 @@
 
 #include <climits>
 
+#include "bf16.hpp"
 #include "zp_internal.hpp"
 
 namespace zp {
@@ -39,29 +40,7 @@ namespace {
 constexpr int kBlock = 256;     // points per workgroup (4 waves)
 constexpr int kTabChunk = 256;  // recurrence steps staged in LDS at a time
 
-__device__ __forceinline__ uint16_t bf16_rne(float f)
-{
-    uint32_t u = __float_as_uint(f);
-    u += 0x7FFFu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
-}
-
-__device__ __forceinline__ double bf16_to_double(uint16_t h)
-{
-    return (double)__uint_as_float((uint32_t)h << 16);
-}
-
 typedef uint32_t u4 __attribute__((ext_vector_type(4)));
-
-// v ~ hi + mid + lo as three bf16 values; the residuals are exact in FP64.
-__device__ __forceinline__ void split3(double v, uint16_t &h, uint16_t &m, uint16_t &l)
-{
-    h = bf16_rne((float)v);
-    const double r1 = v - bf16_to_double(h);
-    m = bf16_rne((float)r1);
-    const double r2 = r1 - bf16_to_double(m);
-    l = bf16_rne((float)r2);
-}
 
 __device__ __forceinline__ void store_fmt(void *base, int fmt, int64_t sub, int64_t idx, double v)
 {
@@ -74,11 +53,10 @@ __device__ __forceinline__ void store_fmt(void *base, int fmt, int64_t sub, int6
         break;
     default: { // B16X3
         uint16_t *b = (uint16_t *)base + idx;
-        uint16_t h, md, l;
-        split3(v, h, md, l);
-        __builtin_nontemporal_store(h, b);
-        __builtin_nontemporal_store(md, b + sub);
-        __builtin_nontemporal_store(l, b + 2 * sub);
+        uint32_t w[3];
+        split3_pair(v, v, w);
+#pragma unroll
+        for (int q = 0; q < 3; ++q) __builtin_nontemporal_store((uint16_t)w[q], b + q * sub);
         break;
     }
     }
@@ -90,21 +68,26 @@ __device__ __forceinline__ void store_plane(const Planes &o, int q, int64_t idx,
 }
 
 // One k-blocked bf16 group register (8 emissions x 16 bits per plane); see
-// the kernel for how groups are formed.
+// the kernel for how groups are formed.  An even emission waits in `even` for
+// its neighbour, so that both are split and pushed at once.
 template <int NW>
-__device__ __forceinline__ void kb_push(uint32_t (&w)[NW][4], double val, uint16_t *kb, int64_t kb_sub, int eidx,
-                                        bool full_group)
+__device__ __forceinline__ void kb_push(uint32_t (&w)[NW][4], double &even, double val, uint16_t *kb, int64_t kb_sub,
+                                        int eidx, bool full_group)
 {
-    uint16_t hv[3];
-    split3(val, hv[0], hv[1], hv[2]);
+    uint32_t pair[3];
     if (full_group) {
+        if (!(eidx & 1)) {
+            even = val;
+            return;
+        }
+        split3_pair(even, val, pair);
 #pragma unroll
         for (int q = 0; q < 3; ++q) {
             uint32_t *x4 = w[q < NW ? q : 0];
-            x4[0] = __builtin_amdgcn_alignbit(x4[1], x4[0], 16);
-            x4[1] = __builtin_amdgcn_alignbit(x4[2], x4[1], 16);
-            x4[2] = __builtin_amdgcn_alignbit(x4[3], x4[2], 16);
-            x4[3] = (x4[3] >> 16) | ((uint32_t)hv[q] << 16);
+            x4[0] = x4[1];
+            x4[1] = x4[2];
+            x4[2] = x4[3];
+            x4[3] = pair[q];
         }
         if ((eidx & 7) == 7) {
 #pragma unroll
@@ -118,8 +101,9 @@ __device__ __forceinline__ void kb_push(uint32_t (&w)[NW][4], double val, uint16
         // groups shared with another chain piece: the two workgroups write
         // different bytes of the same 16-byte blocks; plain stores let L2
         // merge them before the lines go to memory
+        split3_pair(val, val, pair);
 #pragma unroll
-        for (int q = 0; q < 3; ++q) kb[q * kb_sub + (eidx & 7)] = hv[q];
+        for (int q = 0; q < 3; ++q) kb[q * kb_sub + (eidx & 7)] = (uint16_t)pair[q];
     }
 }
 
@@ -224,10 +208,11 @@ __global__ __launch_bounds__(kBlock) void chain_kernel(const Chain *__restrict__
     int nextK = e < e_end ? emits[e].K : INT_MAX;
 
     // Staging for the k-blocked bf16 copy of Z: a 128-bit shift register per
-    // plane collects the eight emissions of a group that lies wholly on this
+    // plane collects the eight emissions, two at a time, of a group that lies wholly on this
     // chain piece; groups that straddle a boundary are stored element-wise.
     uint32_t kbw[3][4] = {};
     uint32_t kbd[DIR ? 3 : 1][4] = {};
+    double kbw_even = 0.0, kbd_even = 0.0;
 
     auto emit_all = [&](int k) {
         while (nextK == k) {
@@ -310,8 +295,9 @@ __global__ __launch_bounds__(kBlock) void chain_kernel(const Chain *__restrict__
                 const int g8 = eidx & ~7;
                 const bool full = g8 >= ch.emit_off && g8 + 8 <= e_end;
                 const int64_t off = ((int64_t)(eidx >> 3) * out.kb_ld + p0) * 8;
-                if (out.kb) kb_push(kbw, val[0][0], (uint16_t *)out.kb + off, out.kb_sub, eidx, full);
-                if (DIR && out.kb_dir) kb_push(kbd, vdir[0], (uint16_t *)out.kb_dir + off, out.kb_sub, eidx, full);
+                if (out.kb) kb_push(kbw, kbw_even, val[0][0], (uint16_t *)out.kb + off, out.kb_sub, eidx, full);
+                if (DIR && out.kb_dir)
+                    kb_push(kbd, kbd_even, vdir[0], (uint16_t *)out.kb_dir + off, out.kb_sub, eidx, full);
             }
         }
     };

@@ -38,6 +38,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "bf16.hpp"
 #include "series.hpp"
 
 namespace zp {
@@ -81,25 +82,6 @@ template <> struct CTr<CT_BF3> {
     using T = uint16_t;
     static constexpr int NP = 3;
 };
-
-__device__ __forceinline__ uint16_t bf16_rne(float f)
-{
-    uint32_t u = __float_as_uint(f);
-    u += 0x7FFFu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
-}
-
-__device__ __forceinline__ double bf16_val(uint16_t h) { return (double)__uint_as_float((uint32_t)h << 16); }
-
-// x = hi + mid + lo as three bf16 values (the residuals are exact in FP32).
-__device__ __forceinline__ void split3f(float x, uint32_t &h, uint32_t &m, uint32_t &l)
-{
-    h = bf16_rne(x);
-    const float r1 = x - __uint_as_float(h << 16);
-    m = bf16_rne(r1);
-    const float r2 = r1 - __uint_as_float(m << 16);
-    l = bf16_rne(r2);
-}
 
 // LDS geometry and global->LDS copy of one operand tile (X rows of the output
 // index by BK).  LDS holds the tile either as [X][BK] rows (k contiguous: the
@@ -193,13 +175,12 @@ template <int CT, int X, int BK, int LAY> struct Tile {
                 u4 hp, mp, lp;
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    uint32_t h0, m0, l0, h1, m1, l1;
-                    const uint32_t w0 = reg[v][q >> 1][(q & 1) * 2], w1 = reg[v][q >> 1][(q & 1) * 2 + 1];
-                    split3f(__uint_as_float(w0), h0, m0, l0);
-                    split3f(__uint_as_float(w1), h1, m1, l1);
-                    hp[q] = h0 | (h1 << 16);
-                    mp[q] = m0 | (m1 << 16);
-                    lp[q] = l0 | (l1 << 16);
+                    uint32_t w[3];
+                    split3_pair(__uint_as_float(reg[v][q >> 1][(q & 1) * 2]),
+                                __uint_as_float(reg[v][q >> 1][(q & 1) * 2 + 1]), w);
+                    hp[q] = w[0];
+                    mp[q] = w[1];
+                    lp[q] = w[2];
                 }
                 *(u4 *)(lds + at(gr, gc)) = hp;
                 *(u4 *)(lds + ELEMS + at(gr, gc)) = mp;
@@ -685,21 +666,12 @@ __device__ __forceinline__ void put2(void *dst, int ct, int64_t idx, int64_t sub
         typedef float ff2 __attribute__((ext_vector_type(2)));
         *(ff2 *)((float *)dst + idx) = ff2{(float)v0, (float)v1};
     } else {
-        uint16_t h[2], m[2], l[2];
-        const double v[2] = {v0, v1};
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            h[u] = bf16_rne((float)v[u]);
-            const double r1 = v[u] - bf16_val(h[u]);
-            m[u] = bf16_rne((float)r1);
-            const double r2 = r1 - bf16_val(m[u]);
-            l[u] = bf16_rne((float)r2);
-        }
+        uint32_t w[3];
+        split3_pair(v0, v1, w);
         uint32_t *b = (uint32_t *)((uint16_t *)dst + idx);
         const int64_t sub2 = sub / 2; // planes sub elements apart (sub even)
-        b[0] = h[0] | ((uint32_t)h[1] << 16);
-        b[sub2] = m[0] | ((uint32_t)m[1] << 16);
-        b[2 * sub2] = l[0] | ((uint32_t)l[1] << 16);
+#pragma unroll
+        for (int q = 0; q < 3; ++q) b[q * sub2] = w[q];
     }
 }
 
@@ -726,29 +698,17 @@ __global__ __launch_bounds__(256) void convert_rows_kernel(const double *__restr
     put2(dst, ct, r * ldd + c, sub, v0, v1);
 }
 
-// FP64 value -> three bf16 planes, the same split as put2()
-__device__ __forceinline__ void split3d(double v, uint32_t &h, uint32_t &m, uint32_t &l)
-{
-    h = bf16_rne((float)v);
-    const double r1 = v - bf16_val((uint16_t)h);
-    m = bf16_rne((float)r1);
-    const double r2 = r1 - bf16_val((uint16_t)m);
-    l = bf16_rne((float)r2);
-}
-
 // Eight values (k = 8 kg .. 8 kg + 7 of one column) -> one 16-byte fragment
 // row per plane at element offset off.
 __device__ __forceinline__ void put_frag8(uint16_t *dst, int64_t sub, int64_t off, const double (&v)[8])
 {
-    u4 w[3] = {};
+    u4 w[3];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        uint32_t h, m, l;
-        split3d(v[e], h, m, l);
-        const int q = e >> 1, sh = (e & 1) * 16;
-        w[0][q] |= h << sh;
-        w[1][q] |= m << sh;
-        w[2][q] |= l << sh;
+    for (int q = 0; q < 4; ++q) {
+        uint32_t pair[3];
+        split3_pair(v[2 * q], v[2 * q + 1], pair);
+#pragma unroll
+        for (int p = 0; p < 3; ++p) w[p][q] = pair[p];
     }
 #pragma unroll
     for (int p = 0; p < 3; ++p) *(u4 *)(dst + p * sub + off) = w[p];
