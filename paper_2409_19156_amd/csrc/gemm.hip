@@ -492,6 +492,13 @@ __device__ __forceinline__ void gemm_body(const GemmDesc &g)
         // lanes of a column are summed with two exchanges, and the wave rows
         // that share the column are added in a fixed order through LDS.
         constexpr int WROWS = BM / WM;
+        // The plane values of AB row blocks are loaded before the first of
+        // their products, so that a column waits for memory FM / AB times and
+        // not 16 (rows past M read row M - 1 and are left out of the sums).
+        // FP64 has registers for one block without spills.  Column-dot: bf16
+        // 2 230 -> 1 980 us, FP64 1 174 -> 1 134 us (n <= 64, 65 536 and 16 384
+        // points, 1024 sets), 154 -> 138 us (n <= 40, 16 384 points, 256 sets).
+        constexpr int AB = CT == CT_F64 ? 1 : FM;
         __shared__ double red[2][WROWS][BN];
         const int wrow = wave % (BM / WM);
         using DT = typename std::conditional<CT == CT_F64, double, float>::type;
@@ -503,17 +510,29 @@ __device__ __forceinline__ void gemm_body(const GemmDesc &g)
             double s1 = 0.0, s2 = 0.0;
             if (j < g.N) {
 #pragma unroll
-                for (int a = 0; a < FM; ++a)
+                for (int a0 = 0; a0 < FM; a0 += AB) {
+                    DT d1[AB][4], d2[AB][4];
 #pragma unroll
-                    for (int t = 0; t < 4; ++t) {
-                        const int64_t i = i0 + wm0 + a * 16 + row_of(t);
-                        if (i < g.M) {
-                            const int64_t o = i * g.ldd + j;
-                            const double h = value(a, b, t);
-                            s1 = __builtin_fma(h, (double)D1[o], s1);
-                            s2 = __builtin_fma(h, (double)D2[o], s2);
+                    for (int a = 0; a < AB; ++a)
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) {
+                            const int64_t i = i0 + wm0 + (a0 + a) * 16 + row_of(t);
+                            const int64_t o = (i < g.M ? i : g.M - 1) * g.ldd + j;
+                            d1[a][t] = D1[o];
+                            d2[a][t] = D2[o];
                         }
-                    }
+#pragma unroll
+                    for (int a = 0; a < AB; ++a)
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) {
+                            const int64_t i = i0 + wm0 + (a0 + a) * 16 + row_of(t);
+                            const double h = value(a0 + a, b, t);
+                            if (i < g.M) {
+                                s1 = __builtin_fma(h, (double)d1[a][t], s1);
+                                s2 = __builtin_fma(h, (double)d2[a][t], s2);
+                            }
+                        }
+                }
             }
             s1 += __shfl_xor(s1, 16);
             s2 += __shfl_xor(s2, 16);
