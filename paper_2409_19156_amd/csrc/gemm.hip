@@ -341,9 +341,9 @@ __device__ __forceinline__ void gemm_body(const GemmDesc &g)
     const T *b_base = (const T *)g.b.base;
     const int64_t a_ld = g.a.ld, a_sub = g.a.sub, b_ld = g.b.ld, b_sub = g.b.sub;
     // Two register sets.  Step t: tile t+1 (fetched during step t-1) goes from
-    // registers into the free LDS buffer, tile t+2 is fetched, and tile t is
-    // multiplied out of the other buffer, so the LDS writes and the global
-    // loads both overlap the MFMAs; one barrier per step.
+    // registers into the free LDS buffer, tile t+2 is fetched (feed, below),
+    // and tile t is multiplied out of the other buffer, so the LDS writes and
+    // the global loads both overlap the MFMAs; one barrier per step.
     // NSET = 1 keeps one set (the store of tile t+1 precedes the load of tile
     // t+2 into the same registers): 8 to 16 fewer registers, for the builds
     // capped at 128.
@@ -380,17 +380,26 @@ __device__ __forceinline__ void gemm_body(const GemmDesc &g)
     const int lx = lane & 15, lk = lane >> 4;
     auto step = [&](int t, auto cur_c) {
         constexpr int cur = decltype(cur_c)::value;
-        if (t + 1 < ntiles) {
-            TA::store(ra[(cur ^ 1) % NSET], As[cur ^ 1]);
-            if constexpr (BFRAG)
-                load_bfrag(t + 1, fbr[cur ^ 1]);
-            else
-                TB::store(rb[(cur ^ 1) % NSET], Bs[cur ^ 1]);
-        }
-        if (t + 2 < ntiles) {
-            TA::load(ra[cur % NSET], a_base, a_ld, a_sub, i0, kbeg + (int64_t)(t + 2) * BK);
-            if constexpr (!BFRAG) TB::load(rb[cur % NSET], b_base, b_ld, b_sub, j0, kbeg + (int64_t)(t + 2) * BK);
-        }
+        auto feed = [&] {
+            if (t + 1 < ntiles) {
+                TA::store(ra[(cur ^ 1) % NSET], As[cur ^ 1]);
+                if constexpr (BFRAG)
+                    load_bfrag(t + 1, fbr[cur ^ 1]);
+                else
+                    TB::store(rb[(cur ^ 1) % NSET], Bs[cur ^ 1]);
+            }
+            if (t + 2 < ntiles) {
+                TA::load(ra[cur % NSET], a_base, a_ld, a_sub, i0, kbeg + (int64_t)(t + 2) * BK);
+                if constexpr (!BFRAG) TB::load(rb[cur % NSET], b_base, b_ld, b_sub, j0, kbeg + (int64_t)(t + 2) * BK);
+            }
+        };
+        // Where in the step: FP64 first (later was 4% slower in the split-K);
+        // FP32 after the products (forward 208 -> 188 us, split-K and column-dot
+        // 1 to 2%, n <= 64 on 8192 points, 1024 sets), bf16 before the last
+        // column block's products, so that the step's fragment reads do not
+        // queue in LDS behind the stores (n <= 64 on 65 536 points, 1024 sets,
+        // forward + backward 6.46 -> 6.38 ms).
+        if constexpr (CT == CT_F64) feed();
         const T *LA = As[cur];
         const T *LB = Bs[cur];
         if constexpr (CT == CT_BF3) {
@@ -404,6 +413,11 @@ __device__ __forceinline__ void gemm_body(const GemmDesc &g)
                         fa[a][p] = *(const bf8 *)(LA + p * TA::ELEMS + TA::at(wm0 + a * 16 + lx, kk + 8 * lk));
 #pragma unroll
                 for (int b = 0; b < FN; ++b) {
+                    if (b == FN - 1) { // (kk takes one value)
+                        __builtin_amdgcn_sched_barrier(0);
+                        feed();
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
                     bf8 fb[3];
 #pragma unroll
                     for (int p = 0; p < 3; ++p) {
@@ -449,6 +463,7 @@ __device__ __forceinline__ void gemm_body(const GemmDesc &g)
                     if ((kk + 4) % kFlush<CT, EPI> == 0) flush(1.0);
             }
         }
+        if constexpr (CT == CT_F32) feed();
         if constexpr (CT == CT_BF3)
             flush(cur == 1 ? -1.0 : 1.0); // every step (kFlush == BK)
         else if (MIXED && kFlush<CT, EPI> >= BK && ((t + 1) * BK) % kFlush<CT, EPI> == 0)
