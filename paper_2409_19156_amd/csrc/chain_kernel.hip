@@ -11,8 +11,10 @@
 // reaches its degree K = (n - alpha)/2: the lane assembles R and its
 // r-derivatives, applies the angular factor, and stores.  For a fixed column
 // the 64 lanes of a wave store 128 consecutive points: 1 KB contiguous per
-// store instruction (16 bytes per lane), marked non-temporal because outputs
-// are not re-read by this kernel.
+// store instruction (16 bytes per lane).  With an angular factor stores are
+// marked non-temporal; for radial values alone plain ones are faster (n <= 200,
+// 100 000 points, orders 0 to 2, 24.5 GB: 4 577 -> 4 501 us), where for the
+// basis they made no difference or lost 3% (n <= 50, 8192 points, 86 us).
 //
 // Arithmetic: the endpoint-anchored difference form of the beta = 0 Jacobi
 // recurrence (see zp_internal.hpp) with the derivatives with respect to
@@ -60,6 +62,14 @@ __device__ __forceinline__ void store_fmt(void *base, int fmt, int64_t sub, int6
         break;
     }
     }
+}
+
+template <bool NONTEMPORAL, class T> __device__ __forceinline__ void store(T v, T *p)
+{
+    if constexpr (NONTEMPORAL)
+        __builtin_nontemporal_store(v, p);
+    else
+        *p = v;
 }
 
 __device__ __forceinline__ void store_plane(const Planes &o, int q, int64_t idx, double v)
@@ -275,9 +285,9 @@ __global__ __launch_bounds__(kBlock) void chain_kernel(const Chain *__restrict__
                     double *dst = (double *)base + idx;
                     if (live[NPL - 1]) {
                         const d2 pair = {vq[0], vq[NPL - 1]};
-                        __builtin_nontemporal_store(pair, (d2 *)dst);
+                        store<ANG>(pair, (d2 *)dst);
                     } else if (live[0]) {
-                        __builtin_nontemporal_store(vq[0], dst);
+                        store<ANG>(vq[0], dst);
                     }
                 }
                 continue;
