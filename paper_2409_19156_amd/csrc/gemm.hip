@@ -394,8 +394,8 @@ __device__ __forceinline__ void gemm_body(const GemmDesc &g)
             }
         };
         // Where in the step: FP64 first (later was 4% slower in the split-K);
-        // FP32 after the products (forward 208 -> 188 us, split-K and column-dot
-        // 1 to 2%, n <= 64 on 8192 points, 1024 sets), bf16 before the last
+        // FP32 after the products (n <= 64 on 8192 points, 1024 sets: forward
+        // 397 -> 381 us, split-K and column-dot 1 to 2%), bf16 before the last
         // column block's products, so that the step's fragment reads do not
         // queue in LDS behind the stores (n <= 64 on 65 536 points, 1024 sets,
         // forward + backward 6.46 -> 6.38 ms).
@@ -585,7 +585,7 @@ __global__ __launch_bounds__(kThreads) void gemm_kernel(GemmDesc g)
 // and column-dot 18% faster than one workgroup per CU.  Also for the FP32
 // split-K and column-dot with their narrow tiles (98 and 127 registers): 7%
 // and 9% faster than 64 x 32 wave tiles at one workgroup per CU.  The FP32
-// forward and the bf16 instances need 170-220 registers and keep one
+// forward (178 registers) and the bf16 instances (208 to 232) keep one
 // workgroup per CU.
 template <int CT, int ALAY, int BLAY, int EPI, int SHAPE>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void gemm_kernel_w4(GemmDesc g)
@@ -598,19 +598,21 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
 // holds, so a launch takes ceil(tiles / CUs) tiles' time.  In quarters of a
 // wide tile a small one costs 1.1 (FP32, FP64) or, for bf16, whose A fragments
 // it reads for 32 columns instead of 128, 2.  FP64 with at most one wide tile
-// per CU gains from the small tiles' occupancy what they cost.  Measured, wide
+// per CU gains from the small tiles' occupancy what they cost, unless the next
+// chunk's basis runs beside it (2145 x 65 536 x 1024, chunks of one wide tile
+// per CU: 4 400 us, with small tiles 4 760).  Measured, wide
 // -> small, modes x points x sets, us per forward (basis included):
 //   FP32   861 x 16 384 x  64 (128 ->    256 tiles)   101 ->  55
 //   FP32  2145 x  2 048 x 300 ( 48 ->    160 tiles)    194 ->  79
 //   FP32   861 x 40 000 x 128 (313 ->  1 250 tiles)    203 -> 155
 //   FP32   861 x 65 536 x 128 (512 ->  2 048 tiles)    253 -> 252  stays wide
-//   FP32  2145 x  8 192 x 1024 (512 -> 2 048 tiles)    397 -> 417  stays wide
+//   FP32  2145 x  8 192 x 1024 (512 -> 2 048 tiles)    382 -> 417  stays wide
 //   FP64   861 x 16 384 x 256 (256 ->  1 024 tiles)    159 -> 153
 //   FP64   861 x 65 536 x 256 (1 024 -> 4 096 tiles)   568 -> 628  stays wide
 //   FP64  5151 x  4 096 x 256 ( 64 ->    256 tiles)    741 -> 253
 //   bf16  2145 x  8 192 x  64 ( 64 ->    128 tiles)    137 -> 108
 //   bf16   861 x 16 384 x 256 (256 ->  1 024 tiles)     96 -> 118  stays wide
-template <int CT> bool small_tiles(int64_t M, int64_t N)
+template <int CT> bool small_tiles(int64_t M, int64_t N, bool beside)
 {
     using W = CfgE<CT, EPI_STORE, WIDE>;
     using S = CfgE<CT, EPI_STORE, SMALL>;
@@ -620,7 +622,7 @@ template <int CT> bool small_tiles(int64_t M, int64_t N)
         return (((M + bm - 1) / bm) * ((N + bn - 1) / bn) + cus - 1) / cus;
     };
     const int64_t wide = rounds(W::BM, W::BN), small = rounds(S::BM, S::BN);
-    if (CT == CT_F64 && wide == 1) return true;
+    if (CT == CT_F64 && wide == 1 && !beside) return true;
     return (CT == CT_BF3 ? 20 : 11) * small < 40 * wide;
 }
 
@@ -648,7 +650,7 @@ hipError_t launch_t(const GemmDesc &g, hipStream_t s)
         if (gemm_narrow(g.M, g.N, g.splits)) return launch_shape<CT, ALAY, BLAY, EPI, NARROW>(g, s);
     }
     if constexpr (EPI == EPI_STORE) {
-        if (small_tiles<CT>(g.M, g.N)) return launch_shape<CT, ALAY, BLAY, EPI, SMALL>(g, s);
+        if (small_tiles<CT>(g.M, g.N, g.beside)) return launch_shape<CT, ALAY, BLAY, EPI, SMALL>(g, s);
     }
     return launch_shape<CT, ALAY, BLAY, EPI, kShape<CT, EPI>>(g, s);
 }

@@ -545,6 +545,7 @@ zp_status series_fwd_run(const Plan &pl, int64_t M, const double *d_r, const dou
         g.K = Mp;
         g.splits = 1;
         g.epi = EPI_STORE;
+        g.beside = pipeline.on();
         g.C = d_f + p0 * B;
         g.ldc = B;
         st = launch_gemm(g, cs);
@@ -860,6 +861,7 @@ extern "C" zp_status zp_series_jvp(const int32_t *h_n, const int32_t *h_m, int64
         g.K = K;
         g.splits = 1;
         g.epi = EPI_STORE;
+        g.beside = pipeline.on();
         g.C = d_tf + p0 * B;
         g.ldc = B;
         st = launch_gemm(g, cs);

@@ -57,6 +57,7 @@ struct GemmDesc {
     // first (workgroups in flight share an A panel), 1 = down a column of
     // tiles first (they share a B panel).
     int order;
+    bool beside; // another kernel runs beside this contraction (pipelined chunks)
 };
 
 // Row-tile height of the column-dot epilogue for a compute type (its
