@@ -571,10 +571,13 @@ __device__ __forceinline__ void gemm_body(const GemmDesc &g)
     }
 }
 
+// (FP32 here is the forward, with one register set: 165 instead of 178
+// registers leave room for three instead of two waves of the next chunk's basis
+// kernel beside it on a SIMD.)
 template <int CT, int ALAY, int BLAY, int EPI>
 __global__ __launch_bounds__(kThreads) void gemm_kernel(GemmDesc g)
 {
-    gemm_body<CT, ALAY, BLAY, EPI, 2, WIDE>(g);
+    gemm_body<CT, ALAY, BLAY, EPI, CT == CT_F32 ? 1 : 2, WIDE>(g);
 }
 
 // The same kernel compiled for four waves per SIMD (at most 128 registers,
@@ -585,7 +588,7 @@ __global__ __launch_bounds__(kThreads) void gemm_kernel(GemmDesc g)
 // and column-dot 18% faster than one workgroup per CU.  Also for the FP32
 // split-K and column-dot with their narrow tiles (98 and 127 registers): 7%
 // and 9% faster than 64 x 32 wave tiles at one workgroup per CU.  The FP32
-// forward (178 registers) and the bf16 instances (208 to 232) keep one
+// forward (165 registers) and the bf16 instances (208 to 232) keep one
 // workgroup per CU.
 template <int CT, int ALAY, int BLAY, int EPI, int SHAPE>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void gemm_kernel_w4(GemmDesc g)
