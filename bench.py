@@ -32,9 +32,9 @@ FP64_PEAK_TFS = 78.6  # MI355X FP64 MFMA (dense), published
 # for 1048576 KiB written: x1.0).  Valid only for the kernel sources it was
 # taken on; reported as null once they change.
 TRAFFIC = {"sources": ("paper_2409_19156_amd/csrc/chain_kernel.hip", "paper_2409_19156_amd/csrc/zp_internal.hpp"),
-           "sha256": "3a57c2c967d0012d97e8508ab1e3eae43f26d23c1440cfc79c5f75ec5123ffa2",
-           "fetch_kib": 469.0, "fetch_scale": 1048576.0 / 524299.8,
-           "write_kib": 424769.9, "write_scale": 1.0}
+           "sha256": "51d1aab6acd17f9847219985a85a20d0b72e485b7372ebd245cc2e9e6e23d735",
+           "fetch_kib": 465.0, "fetch_scale": 1048576.0 / 524299.5,
+           "write_kib": 424796.3, "write_scale": 1.0}
 
 
 def measured_traffic():

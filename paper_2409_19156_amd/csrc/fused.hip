@@ -39,7 +39,7 @@ typedef double d4 __attribute__((ext_vector_type(4)));
 constexpr int kThreads = 256; // kSlices waves
 static_assert(kThreads == 64 * kSlices, "one wave per slice");
 
-// x^e for e >= 0 by binary powewin.
+// x^e for e >= 0 by binary powering (about 2 log2(e) roundings).
 __device__ __forceinline__ double ipow(double x, int e)
 {
     double acc = 1.0;
