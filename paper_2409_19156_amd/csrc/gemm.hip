@@ -43,10 +43,13 @@
 
 namespace zp {
 
-bool gemm_narrow(int64_t M, int64_t N, int splits)
+int64_t gemm_narrow_splits(int64_t M, int64_t N)
 {
-    return ((M + 127) / 128) * ((N + 127) / 128) * (int64_t)splits < 4 * (int64_t)device_cus();
+    const int64_t tiles = std::max<int64_t>(1, ((M + 127) / 128) * ((N + 127) / 128));
+    return (4 * (int64_t)device_cus() - 1) / tiles;
 }
+
+bool gemm_narrow(int64_t M, int64_t N, int splits) { return splits <= gemm_narrow_splits(M, N); }
 
 namespace {
 
@@ -235,7 +238,7 @@ template <> struct Cfg<CT_BF3> {
 // FP64 split-K and column-dot take it on small problems (below), where twice
 // the workgroups fill the chip better.
 //
-// Small shape (forward only): 32 x 16 wave tiles, a 64 x 64 workgroup tile, for
+// Small shape (forward and split-K): 32 x 16 wave tiles, a 64 x 64 workgroup tile, for
 // bf16 128 x 32 (its A tile has to give every thread a 16-byte load).  A
 // workgroup sums over all modes, so with fewer 128 x 128 tiles than CUs the
 // launch takes one such tile's time whatever its size; a quarter of the tile
@@ -642,6 +645,20 @@ hipError_t launch_shape(const GemmDesc &g, hipStream_t s)
     return hipGetLastError();
 }
 
+// The split-K of few output tiles, FP64 and FP32: the small shape instead of
+// the narrow one when its rounds of workgroups end first, a small tile costing
+// 0.55 of a narrow one's time, or when the narrow tiles leave CUs to
+// themselves.  dL/dc, us, at the same split counts: FP64 n <= 40, 16384 points,
+// 64 sets 46.0 -> 43.4; n <= 64, 2048 points, 300 sets 70.2 -> 66.8; with more
+// rounds (n <= 64, 8192 points, 256 sets) 160 -> 166, which stays narrow.
+bool small_partial(int64_t M, int64_t N, int splits)
+{
+    const int64_t cus = device_cus();
+    auto rounds = [&](int64_t bm) { return ((M + bm - 1) / bm * ((N + 63) / 64) * splits + cus - 1) / cus; };
+    const int64_t narrow = rounds(128), small = rounds(64);
+    return narrow == 1 || 11 * small < 20 * narrow;
+}
+
 // FP64 split-K and column-dot: the narrow shape when the wide tiles give fewer
 // than four workgroups per CU (n <= 40 series, 861 modes x 16 384 points x 256
 // sets: forward + backward 0.54 -> 0.50 ms); larger problems keep the wide
@@ -649,6 +666,10 @@ hipError_t launch_shape(const GemmDesc &g, hipStream_t s)
 template <int CT, int ALAY, int BLAY, int EPI>
 hipError_t launch_t(const GemmDesc &g, hipStream_t s)
 {
+    if constexpr (CT != CT_BF3 && EPI == EPI_PARTIAL) {
+        if (gemm_narrow(g.M, g.N, g.splits) && small_partial(g.M, g.N, g.splits))
+            return launch_shape<CT, ALAY, BLAY, EPI, SMALL>(g, s);
+    }
     if constexpr (CT == CT_F64 && EPI != EPI_STORE) {
         if (gemm_narrow(g.M, g.N, g.splits)) return launch_shape<CT, ALAY, BLAY, EPI, NARROW>(g, s);
     }

@@ -108,21 +108,28 @@ int splits_large(int64_t M, int64_t B, int64_t Kp)
 // written and read back, where a pad (128 k of one tile) takes `alone` us in a
 // workgroup that has its CU to itself and `busy` us of a full CU's time (from
 // the contractions of n <= 64 on 65536 points: 4390, 2570 and 1972 us; alone:
-// 34 workgroups took 157 us for 17 pads in FP64).  Another count is taken
-// when the model gives it a tenth less: analysis n <= 64, 4257 points, 64
-// sets: 2 -> 12 splits of at most 3 pads, FP64 contraction 157 -> 39 us; n <=
-// 40, 16384 points, 64 sets: 16 -> 32 splits, dL/dc 88 -> 56 us.
+// 34 workgroups took 157 us for 17 pads in FP64).  Where the contraction can
+// take its small tiles (FP64, FP32), a pad of those takes `alone_small` or 0.55
+// of `busy` (times of 1 to 16 pads per split, n <= 40, 4096 points, 64 sets: 4.7
+// us a pad in FP64).  Another count is taken when the model gives it a tenth
+// less: analysis n <= 64, 4257 points, 64 sets: 2 -> 7 splits of at most 5 pads,
+// dL/dc in FP64 157 -> 36 us; n <= 32, 32768 points, 64 sets 64 -> 58 us.
 int splits_for(int64_t M, int64_t B, int64_t Kp, int ct)
 {
     const int large = splits_large(M, B, Kp);
     const int64_t units = Kp / kPad;
     const int64_t bn = ct == CT_BF3 ? 128 : 64; // the contraction's tile width (FP64: on problems this size)
     const double alone = ct == CT_F64 ? 9.2 : ct == CT_F32 ? 6.0 : 8.0;
+    const double alone_small = ct == CT_F64 ? 4.7 : 3.2;
     const double busy = ct == CT_F64 ? 8.1 : ct == CT_F32 ? 4.7 : 7.3;
-    const int64_t tiles = ((M + 127) / 128) * ((B + bn - 1) / bn);
+    const int64_t cols = (B + bn - 1) / bn;
+    const int64_t tiles = (M + 127) / 128 * cols, small_tiles = (M + 63) / 64 * cols;
+    const int64_t most = ct == CT_BF3 ? 0 : gemm_narrow_splits(M, B); // with more, wide tiles
+    const double partials = (double)M * (double)B * 16.0 / 4e6;
     auto cost = [&](int64_t s) {
-        const double n = (double)((tiles * s + 255) / 256), q = (double)((units + s - 1) / s);
-        return q * std::max(alone, busy * n) + (double)s * (double)M * (double)B * 16.0 / 4e6;
+        double pad = std::max(alone, busy * (double)((tiles * s + 255) / 256));
+        if (s <= most) pad = std::min(pad, std::max(alone_small, 0.55 * busy * (double)((small_tiles * s + 255) / 256)));
+        return (double)((units + s - 1) / s) * pad + (double)s * partials;
     };
     int best = large;
     double best_cost = 0.9 * cost(large);

@@ -159,6 +159,8 @@ zp_status launch_grad_reduce(const Plan &p, const double *part, int S, int64_t M
 // Whether an FP64 split-K or column-dot of these sizes takes the narrow tiles
 // (64 columns): its B operand then needs 64, not 128, columns of padding.
 bool gemm_narrow(int64_t M, int64_t N, int splits);
+// The largest split count for which it does.
+int64_t gemm_narrow_splits(int64_t M, int64_t N);
 
 // zp_series_bwd for checked arguments; w: nullable weights of the rows of g
 // (dL/dc only), norm: dL/dc divided by the integrals of Z_k^2.
