@@ -372,7 +372,6 @@ zp_status basis_into(const Plan &plan, const double *r, const double *th, int64_
 {
     Planes o{};
     o.ld = ld;
-    o.sub = Mp * ld;
     o.plane[0] = z;
     o.fmt[0] = ct == CT_F64 ? F64 : F32;
     const int dfmt = ct == CT_F64 ? F64 : F32;
@@ -502,12 +501,10 @@ zp_status series_fwd_run(const Plan &pl, int64_t M, const double *d_r, const dou
         st = pipeline.before_basis(chunk);
         if (st != ZP_OK) return st;
         Planes o{};
-        const int zfmt = ct == CT_F64 ? F64 : ct == CT_F32 ? F32 : B16X3;
         const int dfmt = ct == CT_F64 ? F64 : F32;
         int J = 0;
         if (have_cache) { // keep Z, dZ/dr, dZ/dtheta for the backward
             o.ld = CL.Pp;
-            o.sub = Mp * CL.Pp;
             o.plane[0] = cache + CL.z_off + zsz * (size_t)p0;
             o.fmt[0] = ct == CT_F64 ? F64 : F32;
             o.plane[1] = cache + CL.zr_off + dsize_of(ct) * (size_t)p0;
@@ -517,9 +514,8 @@ zp_status series_fwd_run(const Plan &pl, int64_t M, const double *d_r, const dou
             J = 1;
         } else if (ct != CT_BF3) {
             o.ld = pcp;
-            o.sub = Mp * pcp;
             o.plane[0] = zb;
-            o.fmt[0] = zfmt;
+            o.fmt[0] = dfmt;
             st = launch_zero_pad(zb, ct, M, pc, Mp, pcp, Mp * pcp, cs);
             if (st != ZP_OK) return st;
         }
@@ -831,7 +827,6 @@ extern "C" zp_status zp_series_jvp(const int32_t *h_n, const int32_t *h_m, int64
             if (with_c) o.kb = zbuf;
             if (with_dir) o.kb_dir = zbuf + esz * (size_t)((with_c ? 1 : 0) * Mp) * (size_t)pcp;
         } else {
-            o.sub = K * pcp;
             for (int b2 = 0; b2 < nblk; ++b2) {
                 st = launch_zero_pad(zbuf + esz * (size_t)(b2 * Mp) * (size_t)pcp, ct, M, pc, Mp, pcp, 0, cs);
                 if (st != ZP_OK) return st;
@@ -1033,7 +1028,6 @@ zp_status zp_series_bwd2(const int32_t *h_n, const int32_t *h_m, int64_t M, cons
         // basis-derived planes of the chunk
         Planes o{};
         o.ld = pcp;
-        o.sub = Mp * pcp;
         if (run_u) {
             o.plane[1] = ws + L.zr_off;
             o.fmt[1] = dfmt;

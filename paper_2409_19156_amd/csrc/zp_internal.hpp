@@ -189,12 +189,11 @@ void clear_plans3(); // three-dimensional series tables (series3d.cpp)
 
 // ------------------------------------------------------------- outputs --
 
-enum PlaneFmt : int32_t { F64 = 0, F32 = 1, B16X3 = 2 };
+enum PlaneFmt : int32_t { F64 = 0, F32 = 1 };
 
 // Where the chain kernel writes.  plane[q] for q = 0..4 is R (or Z), d/dr,
 // d2/dr2, d3/dr3, d/dtheta; null planes are not written.  Column i of a plane
-// starts ld elements after column i-1.  A B16X3 plane is three bf16 planes
-// (hi, mid, lo) sub elements apart.
+// starts ld elements after column i-1.
 // kb, if not null, receives Z once more as three bf16 planes (kb_sub apart) in
 // the k-blocked layout the series forward contracts over: the mode index is
 // the emission index e (chain-major order, see Plan::d_perm) and element
@@ -202,17 +201,16 @@ enum PlaneFmt : int32_t { F64 = 0, F32 = 1, B16X3 = 2 };
 // dir, if not null, receives the directional derivative
 //   dZ = dr[p] dZ/dr + dtheta[p] dZ/dtheta
 // of the basis along per-point tangents (dr, dtheta; either may be null),
-// in format dir_fmt with the planes' ld and sub; kb_dir, if not null, gets its
+// in format dir_fmt with the planes' ld; kb_dir, if not null, gets its
 // k-blocked bf16 copy (like kb).
 // sec_r / sec_t, if not null (with J = 2 and the basis), receive the
 // derivatives of that directional derivative along r and theta:
 //   sec_r = dr[p] d2Z/dr2 + dtheta[p] d2Z/(dr dtheta)
 //   sec_t = dr[p] d2Z/(dr dtheta) + dtheta[p] d2Z/dtheta2
-// in format sec_fmt with the planes' ld and sub.
+// in format sec_fmt with the planes' ld.
 struct Planes {
     void *plane[5];
     int64_t ld;
-    int64_t sub;
     int32_t fmt[5];
     void *kb;
     int64_t kb_ld;
