@@ -36,8 +36,8 @@
  *     any device work: on error nothing is written and no kernel is launched.
  *     M == 0 or P == 0 (or B == 0 for the series) is a successful no-op.
  *   - The library allocates device memory only for its cached per-mode-list
- *     tables ("plans"), which zp_cache_clear() releases, and holds one fixed
- *     array per GPU for zp_series_fwd_noalloc.  Calls from several
+ *     tables ("plans"), which zp_cache_clear() releases, and holds two fixed
+ *     arrays per GPU for zp_series_fwd_noalloc.  Calls from several
  *     host threads are safe; calls that write the same buffers race, as any
  *     asynchronous work does.
  */
@@ -345,12 +345,14 @@ zp_status zp_series_analysis(const int32_t *h_n, const int32_t *h_m, int64_t M, 
  * cannot allocate device memory: code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc.  It calls no hipMalloc / hipFree
  * and creates no stream or event; its workspace and its plan tables live in a
- * fixed device array of ZP_NOALLOC_SCRATCH_BYTES per GPU, which the library
- * holds until the process ends.  Work runs on `stream` alone, in chunks of
- * points that fit the array.
+ * fixed device array of ZP_NOALLOC_SCRATCH_BYTES per GPU (and 18 MiB more for
+ * tables that no workspace shares), which the library holds until the process
+ * ends.  Work runs on `stream` alone, in chunks of points that fit the array.
  *   Arguments and output as zp_series_fwd.
  *   A call whose mode list differs from the previous call's on this GPU
- *   copies the new tables into the array and waits for `stream` once.
+ *   copies the new tables into the array and waits for `stream` once; with the
+ *   same list no call does, whatever its sizes and precision, and the tables
+ *   stay where they are: captured calls stay valid until the list changes.
  *   Every call on a GPU shares that GPU's array: calls that overlap on one
  *   GPU (on other streams, or from host threads without ordering) race.
  * Errors: as zp_series_fwd; ZP_ERR_WORKSPACE when the tables plus the

@@ -353,7 +353,7 @@ size_t plan_image(const Plan &p, std::vector<unsigned char> *host, PlanOffsets *
     return o->total;
 }
 
-void plan_bind(Plan &p, const void *base, const PlanOffsets &o, bool fused)
+void plan_bind(Plan &p, const void *base, const PlanOffsets &o, const void *fused)
 {
     const unsigned char *b = (const unsigned char *)base;
     p.d_chains = (const Chain *)b;
@@ -363,13 +363,15 @@ void plan_bind(Plan &p, const void *base, const PlanOffsets &o, bool fused)
     p.d_perm = (const int32_t *)(b + o.perm);
     p.d_quads = nullptr;
     if (!fused) return;
-    p.d_achains = (const Chain *)(b + o.achains);
-    p.d_row_chain = (const int32_t *)(b + o.row_chain);
-    p.d_quads = (const Quad *)(b + o.quads);
-    p.d_slice_off = (const int32_t *)(b + o.slice_off);
-    p.d_qsteps = (const QuadStep *)(b + o.qsteps);
-    p.d_entry_hdr = (const int32_t *)(b + o.entry_hdr);
-    p.d_entry_cols = (const int32_t *)(b + o.entry_cols);
+    const unsigned char *f = (const unsigned char *)fused;
+    auto at = [&](size_t off) { return f + (off - o.achains); };
+    p.d_achains = (const Chain *)at(o.achains);
+    p.d_row_chain = (const int32_t *)at(o.row_chain);
+    p.d_quads = (const Quad *)at(o.quads);
+    p.d_slice_off = (const int32_t *)at(o.slice_off);
+    p.d_qsteps = (const QuadStep *)at(o.qsteps);
+    p.d_entry_hdr = (const int32_t *)at(o.entry_hdr);
+    p.d_entry_cols = (const int32_t *)at(o.entry_cols);
 }
 
 static zp_status upload(Plan &p)
@@ -381,7 +383,7 @@ static zp_status upload(Plan &p)
     if (st != ZP_OK) return st;
     st = hip_check(hipMemcpy(p.dmem, host.data(), o.total, hipMemcpyHostToDevice), "hipMemcpy(plan)");
     if (st != ZP_OK) return st;
-    plan_bind(p, p.dmem, o);
+    plan_bind(p, p.dmem, o, (const unsigned char *)p.dmem + o.achains);
     return ZP_OK;
 }
 

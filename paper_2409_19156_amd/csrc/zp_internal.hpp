@@ -178,9 +178,9 @@ struct PlanOffsets {
 };
 // Size of the image (and, if host is not null, the image itself).
 size_t plan_image(const Plan &p, std::vector<unsigned char> *host, PlanOffsets *o);
-// Point the plan's device table pointers into an image at base (fused: the
-// fused kernels' tables are there too; null otherwise).
-void plan_bind(Plan &p, const void *base, const PlanOffsets &o, bool fused = true);
+// Point the plan's device table pointers into an image at base; the fused
+// kernels' tables (the image from achains on) lie at `fused`, null: nowhere.
+void plan_bind(Plan &p, const void *base, const PlanOffsets &o, const void *fused);
 
 // Cached plan for the current device, uploaded on first use.
 zp_status get_plan(const int32_t *n, const int32_t *m, int64_t M, std::shared_ptr<Plan> *out);
