@@ -41,11 +41,11 @@ __global__ __launch_bounds__(kThreads) void mix_kernel(const int32_t *__restrict
                                                        const int32_t *__restrict__ jl, const int32_t *__restrict__ l,
                                                        const double *__restrict__ c, int64_t B,
                                                        const double *__restrict__ phi, int64_t QB, int64_t U,
-                                                       double *__restrict__ T)
+                                                       int64_t e0, double *__restrict__ T)
 {
     __shared__ double red[kSub][kWave];
     const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
-    const int64_t e = (int64_t)blockIdx.x * kWave + lane, el = e < QB ? e : QB - 1;
+    const int64_t e = e0 + (int64_t)blockIdx.x * kWave + lane, el = e < QB ? e : QB - 1;
     const int64_t q = el / B, b = el - q * B;
     const Turn ph(phi[q]);
     for (int64_t u = blockIdx.y; u < U; u += gridDim.y) {
@@ -71,12 +71,12 @@ __global__ __launch_bounds__(kThreads) void unmix_kernel(const int32_t *__restri
                                                          const int32_t *__restrict__ l,
                                                          const double *__restrict__ gT, int64_t B,
                                                          const double *__restrict__ phi, int64_t Q, int64_t J,
-                                                         double *__restrict__ grad_c)
+                                                         int64_t t0, double *__restrict__ grad_c)
 {
     __shared__ Turn ph[kThreads];
     __shared__ double red[kSub][kWave];
     const int lane = threadIdx.x & (kWave - 1), wave = (int)threadIdx.x / kWave;
-    const int64_t t = (int64_t)blockIdx.x * kWave + lane;
+    const int64_t t = t0 + (int64_t)blockIdx.x * kWave + lane;
     const bool live = t < J * B;
     const int64_t j = live ? t / B : 0, b = live ? t - j * B : 0;
     const int lj = l[j];
@@ -152,11 +152,14 @@ zp_status launch_fourier_mix(const Plan3 &p, const double *c, int64_t B, const d
 {
     const int64_t U = (int64_t)p.un.size(), QB = Q * B;
     if (U == 0 || QB == 0) return ZP_OK;
-    const int64_t bx = (QB + kWave - 1) / kWave;
-    if (bx > INT32_MAX) return set_error(ZP_ERR_ARG, "Q * B too large for one launch");
-    const dim3 grid((unsigned)bx, (unsigned)std::min<int64_t>(U, 65535));
-    hipLaunchKernelGGL(mix_kernel, grid, dim3(kThreads), 0, s, p.d_uptr, p.d_jl, p.d_l, c, B, phi, QB, U, T);
-    return hip_check(hipGetLastError(), "fourier mix launch");
+    constexpr int64_t kMost = max_workgroups(kThreads) * kWave; // elements of one launch
+    for (int64_t e0 = 0; e0 < QB; e0 += kMost) {
+        const dim3 grid((unsigned)((std::min(kMost, QB - e0) + kWave - 1) / kWave), (unsigned)std::min<int64_t>(U, 65535));
+        hipLaunchKernelGGL(mix_kernel, grid, dim3(kThreads), 0, s, p.d_uptr, p.d_jl, p.d_l, c, B, phi, QB, U, e0, T);
+        const zp_status st = hip_check(hipGetLastError(), "fourier mix launch");
+        if (st != ZP_OK) return st;
+    }
+    return ZP_OK;
 }
 
 zp_status launch_fourier_unmix(const Plan3 &p, const double *gT, int64_t B, const double *phi, int64_t Q,
@@ -164,11 +167,14 @@ zp_status launch_fourier_unmix(const Plan3 &p, const double *gT, int64_t B, cons
 {
     const int64_t J = (int64_t)p.n.size();
     if (J == 0 || B == 0) return ZP_OK;
-    const int64_t bx = (J * B + kWave - 1) / kWave;
-    if (bx > INT32_MAX) return set_error(ZP_ERR_ARG, "J * B too large for one launch");
-    hipLaunchKernelGGL(unmix_kernel, dim3((unsigned)bx), dim3(kThreads), 0, s, p.d_owner, p.d_l, gT, B, phi, Q, J,
-                       grad_c);
-    return hip_check(hipGetLastError(), "fourier unmix launch");
+    constexpr int64_t kMost = max_workgroups(kThreads) * kWave;
+    for (int64_t t0 = 0; t0 < J * B; t0 += kMost) {
+        const dim3 grid((unsigned)((std::min(kMost, J * B - t0) + kWave - 1) / kWave));
+        hipLaunchKernelGGL(unmix_kernel, grid, dim3(kThreads), 0, s, p.d_owner, p.d_l, gT, B, phi, Q, J, t0, grad_c);
+        const zp_status st = hip_check(hipGetLastError(), "fourier unmix launch");
+        if (st != ZP_OK) return st;
+    }
+    return ZP_OK;
 }
 
 zp_status launch_fourier_phi_grad(const Plan3 &p, const double *gT, const double *c, int64_t B, const double *phi,
@@ -177,7 +183,7 @@ zp_status launch_fourier_phi_grad(const Plan3 &p, const double *gT, const double
     const int64_t J = (int64_t)p.n.size();
     if (Q == 0) return ZP_OK;
     const int64_t bx = (Q + kWave - 1) / kWave;
-    if (bx > INT32_MAX) return set_error(ZP_ERR_ARG, "Q too large for one launch");
+    if (bx > max_workgroups(kThreads)) return set_error(ZP_ERR_ARG, "Q too large for one launch");
     // enough workgroups to fill the chip, each with some modes per wave
     const int64_t want = std::max<int64_t>(1, std::min((J + 8 * kSub - 1) / (8 * kSub), (512 + bx - 1) / bx));
     const int64_t ny = std::max<int64_t>(1, std::min(want, part_rows));

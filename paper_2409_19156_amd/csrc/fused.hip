@@ -981,21 +981,22 @@ __global__ __launch_bounds__(kThreads) void grad_reduce_kernel(const double *__r
                                                                const int32_t *row_chain, const Emit *emits, int norm,
                                                                int accumulate, double *__restrict__ out)
 {
-    const int64_t b = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    const int64_t e = b / B; // emission, set b - e B
-    if (e >= M) return;
-    const Emit em = emits[e];
-    const int64_t o = em.col * B + (b - e * B);
-    double v = 0.0;
+    const int64_t stride = (int64_t)gridDim.x * kThreads;
+    for (int64_t b = (int64_t)blockIdx.x * kThreads + threadIdx.x; b < M * B; b += stride) {
+        const int64_t e = b / B; // emission, set b - e B
+        const Emit em = emits[e];
+        const int64_t o = em.col * B + (b - e * B);
+        double v = 0.0;
 #pragma unroll 8
-    for (int k = 0; k < S; ++k) v += part[k * M * B + o];
-    if (accumulate) v += out[o];
-    if (norm) {
-        int lo = row_chain[e >> 4];
-        while (e >= chains[lo].emit_off + chains[lo].emit_cnt) ++lo;
-        v *= inv_norm(em.K, chains[lo].alpha);
+        for (int k = 0; k < S; ++k) v += part[k * M * B + o];
+        if (accumulate) v += out[o];
+        if (norm) {
+            int lo = row_chain[e >> 4];
+            while (e >= chains[lo].emit_off + chains[lo].emit_cnt) ++lo;
+            v *= inv_norm(em.K, chains[lo].alpha);
+        }
+        out[o] = v;
     }
-    out[o] = v;
 }
 
 // Two workgroups of four waves per CU is what the larger tiles' registers
@@ -1014,10 +1015,7 @@ bool small_rows(int64_t M, int64_t B) { return M < (1 << 24) && B < (1 << 20) &&
 // 156 -> 94 us with 128 sets, 157 -> 137 with 192, 162 -> 180 with 256, where
 // the GEMM's larger tiles win.  With the directional derivative (n <= 64,
 // 65536 points) 1502 -> 1288 us with 96 sets, 1521 -> 1712 with 128.
-bool fused_fwd_ok(int64_t M, int64_t P, int64_t B, bool dir)
-{
-    return B <= (dir ? 96 : 128) && small_rows(M, B) && (P + 15) / 16 * ((B + 15) / 16) <= INT32_MAX;
-}
+bool fused_fwd_ok(int64_t M, int64_t B, bool dir) { return B <= (dir ? 96 : 128) && small_rows(M, B); }
 
 zp_status launch_fused_fwd(const Plan &p, const double *r, const double *th, int64_t P, const double *c,
                            const double *c2, const double *tr, const double *tt, int64_t B, double *f, hipStream_t s)
@@ -1029,27 +1027,35 @@ zp_status launch_fused_fwd(const Plan &p, const double *r, const double *th, int
     const int fn = (int)((tiles + nsb - 1) / nsb);
     int fm = 4;
     while (fm > 1 && (P + 16 * fm - 1) / (16 * fm) * nsb < wanted_workgroups()) fm /= 2;
-    if (c2) {
-        fn == 2 ? launch_fwd_n<2, true>(g, fm, s) : launch_fwd_n<1, true>(g, fm, s);
-    } else {
-        switch (fn) {
-        case 1: launch_fwd_n<1, false>(g, fm, s); break;
-        case 2: launch_fwd_n<2, false>(g, fm, s); break;
-        case 3: launch_fwd_n<3, false>(g, fm, s); break;
-        default: launch_fwd_n<4, false>(g, fm, s); break;
+    const int64_t most = max_workgroups(kThreads) / nsb * 16; // points of one launch, 16 or more to a workgroup
+    for (int64_t p0 = 0; p0 < P; p0 += most) {
+        g.r = r + p0;
+        g.th = th + p0;
+        g.P = std::min(most, P - p0);
+        g.tr = tr ? tr + p0 : nullptr;
+        g.tt = tt ? tt + p0 : nullptr;
+        g.f = f + p0 * B;
+        if (c2) {
+            fn == 2 ? launch_fwd_n<2, true>(g, fm, s) : launch_fwd_n<1, true>(g, fm, s);
+        } else {
+            switch (fn) {
+            case 1: launch_fwd_n<1, false>(g, fm, s); break;
+            case 2: launch_fwd_n<2, false>(g, fm, s); break;
+            case 3: launch_fwd_n<3, false>(g, fm, s); break;
+            default: launch_fwd_n<4, false>(g, fm, s); break;
+            }
         }
+        const zp_status st = hip_check(hipGetLastError(), "fused forward launch");
+        if (st != ZP_OK) return st;
     }
-    return hip_check(hipGetLastError(), "fused forward launch");
+    return ZP_OK;
 }
 
 // As the forward, by the sets alone.  Column-dot GEMM (basis kept) -> fused:
 // (n <= 64, 65536 points) 1104 -> 586 us with 64 sets, 1113 -> 876 with 96,
 // 1097 -> 1164 with 128; (n <= 40, 16384 points) 114 -> 78, 115 -> 113, 104 ->
 // 148 us; the derivative planes then need not be written either.
-bool fused_dot_ok(int64_t M, int64_t P, int64_t B)
-{
-    return B <= kFusedDotSets && small_rows(M, B) && (P + 15) / 16 * ((B + 3) / 4) <= INT32_MAX;
-}
+bool fused_dot_ok(int64_t M, int64_t B) { return B <= kFusedDotSets && small_rows(M, B); }
 
 namespace {
 // Contraction steps of four sets per chunk: 32 sets at most (with 64 the
@@ -1059,6 +1065,8 @@ int dot_steps(int64_t B) { return B <= 4 ? 1 : B <= 8 ? 2 : B <= 16 ? 4 : 8; }
 } // namespace
 
 int64_t fused_dot_chunks(int64_t B) { return (B + 4 * dot_steps(B) - 1) / (4 * dot_steps(B)); }
+
+int64_t fused_dot_points(int64_t B) { return max_workgroups(kThreads) / fused_dot_chunks(B) * 16; }
 
 zp_status launch_fused_dot(const Plan &p, const double *r, const double *th, int64_t P, const double *c,
                            const double *u, const double *ur, const double *ut, bool second, int64_t B,
@@ -1105,7 +1113,7 @@ zp_status launch_fused_grad(const Plan &p, const double *r, const double *th, in
     S = std::min(S, std::max<int64_t>(1, (int64_t)(part_bytes / (8 * (size_t)M * (size_t)B))));
     const int64_t batches = ((nb + S - 1) / S + kSlices - 1) / kSlices * kSlices;
     S = (nb + batches - 1) / batches;
-    if (tiles * S * nsb > INT32_MAX) return set_error(ZP_ERR_ARG, "too many modes for one launch");
+    if (tiles * S * nsb > max_workgroups(kThreads)) return set_error(ZP_ERR_ARG, "too many modes for one launch");
     GradArgs g{p.d_achains, p.d_row_chain, p.d_coefs, p.d_emits, r, th, P, M, wq, tr, tt, g_up, (uint32_t)B, (int)S, tiles,
                batches, S > 1 ? part : out, norm && S == 1};
     if (tr || tt)
@@ -1120,8 +1128,7 @@ zp_status launch_fused_grad(const Plan &p, const double *r, const double *th, in
 zp_status launch_grad_reduce(const Plan &p, const double *part, int S, int64_t M, int64_t B, bool norm,
                              bool accumulate, double *C, hipStream_t s)
 {
-    const int64_t blocks = (M * B + kThreads - 1) / kThreads;
-    if (blocks > INT32_MAX) return set_error(ZP_ERR_ARG, "M * B too large for one launch");
+    const int64_t blocks = std::min((M * B + kThreads - 1) / kThreads, max_workgroups(kThreads));
     hipLaunchKernelGGL(grad_reduce_kernel, dim3((unsigned)blocks), dim3(kThreads), 0, s, part, S, M, B, p.d_achains,
                        p.d_row_chain, p.d_emits, norm ? 1 : 0, accumulate ? 1 : 0, C);
     return hip_check(hipGetLastError(), "gradient reduce launch");

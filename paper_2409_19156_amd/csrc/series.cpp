@@ -242,13 +242,15 @@ int64_t chunk_for(int64_t M, int64_t P, int64_t B, int ct, bool fwd, bool bwd, b
     return std::min<int64_t>(lo * kPad, P);
 }
 
-// launch_fused_dot over chunks of points whose partial sums fit ws.
+// launch_fused_dot over chunks of points that one launch takes and whose
+// partial sums fit ws.
 zp_status fused_dot(const Plan &plan, const double *r, const double *th, int64_t P, const double *c, const double *u,
                     const double *ur, const double *ut, bool second, int64_t B, const double *g, double *out_r,
                     double *out_t, void *ws, size_t ws_bytes, hipStream_t s)
 {
     const int64_t chunks = fused_dot_chunks(B);
-    const int64_t Pc = chunks == 1 ? P : std::min<int64_t>(P, (int64_t)(ws_bytes / (16 * (size_t)chunks)));
+    const int64_t fit = chunks == 1 ? P : (int64_t)(ws_bytes / (16 * (size_t)chunks));
+    const int64_t Pc = std::min({P, fit, fused_dot_points(B)});
     if (Pc <= 0) return set_error(ZP_ERR_WORKSPACE, "workspace smaller than the minimum (zp_series_workspace)");
     for (int64_t p0 = 0; p0 < P; p0 += Pc) {
         zp_status st = launch_fused_dot(plan, r + p0, th + p0, std::min(Pc, P - p0), c, u, ur ? ur + p0 : nullptr,
@@ -430,9 +432,9 @@ size_t series_fwd_min_ws(int64_t M, int64_t P, int64_t B, int32_t prec)
     return WsLayout(M, std::min<int64_t>(P, kPad), B, ct_of(prec), true, false, false).total;
 }
 
-bool series_fwd_fused(int64_t M, int64_t P, int64_t B, int32_t prec)
+bool series_fwd_fused(int64_t M, int64_t B, int32_t prec)
 {
-    return ct_of(prec) == CT_F64 && fused_fwd_ok(M, P, B, false);
+    return ct_of(prec) == CT_F64 && fused_fwd_ok(M, B, false);
 }
 
 zp_status series_fwd_run(const Plan &pl, int64_t M, const double *d_r, const double *d_theta, int64_t P,
@@ -443,7 +445,7 @@ zp_status series_fwd_run(const Plan &pl, int64_t M, const double *d_r, const dou
     zp_status st = ZP_OK;
     const int ct = ct_of(prec);
     const bool have_cache = d_cache != nullptr;
-    if (pl.d_quads && series_fwd_fused(M, P, B, prec)) { // the basis is formed inside the contraction
+    if (pl.d_quads && series_fwd_fused(M, B, prec)) { // the basis is formed inside the contraction
         if (have_cache) { // the backward may still read it
             const CacheLayout CL(M, P, ct);
             char *cache = (char *)d_cache;
@@ -622,7 +624,7 @@ zp_status series_bwd_run(const Plan &pl, int64_t M, const double *d_r, const dou
     char *ws = (char *)d_ws;
     const int64_t Mp = L.Mp, Bp = L.Bp;
     bool need_rt = d_grad_r || d_grad_theta;
-    if (need_rt && ct == CT_F64 && fused_dot_ok(M, P, B)) {
+    if (need_rt && ct == CT_F64 && fused_dot_ok(M, B)) {
         // dL/dr and dL/dtheta first, with the whole workspace, which is free
         // again (in stream order) for dL/dc below
         st = fused_dot(*plan, d_r, d_theta, P, d_c, nullptr, nullptr, nullptr, false, B, d_g, d_grad_r, d_grad_theta,
@@ -775,7 +777,7 @@ extern "C" zp_status zp_series_jvp(const int32_t *h_n, const int32_t *h_m, int64
     std::shared_ptr<Plan> plan;
     st = get_plan(h_n, h_m, M, &plan);
     if (st != ZP_OK) return st;
-    if (ct == CT_F64 && fused_fwd_ok(M, P, B, with_dir))
+    if (ct == CT_F64 && fused_fwd_ok(M, B, with_dir))
         return launch_fused_fwd(*plan, d_r, d_theta, P, with_c ? d_tc : nullptr, with_dir ? d_c : nullptr, d_tr,
                                 d_ttheta, B, d_tf, s);
     // pipelined chunks when the workspace holds two chunk buffers (as the forward)
@@ -991,7 +993,7 @@ zp_status zp_series_bwd2(const int32_t *h_n, const int32_t *h_m, int64_t M, cons
     char *ws = (char *)d_ws;
     const int64_t Mp = L.Mp, Bp = L.Bp;
     bool rt_done = false;
-    if ((run_u || run_e) && ct == CT_F64 && fused_dot_ok(M, P, B)) { // before the workspace is used otherwise
+    if ((run_u || run_e) && ct == CT_F64 && fused_dot_ok(M, B)) { // before the workspace is used otherwise
         st = fused_dot(*plan, d_r, d_theta, P, run_e ? d_c : nullptr, run_u ? d_uc : nullptr, d_ur, d_ut, true, B, d_g,
                        d_out_r, d_out_t, ws, ws_bytes, s);
         if (st != ZP_OK) return st;

@@ -88,7 +88,7 @@ zp_status series_fwd_run(const Plan &plan, int64_t M, const double *d_r, const d
                          size_t ws_bytes, bool allow_pipe, hipStream_t s);
 // Whether series_fwd_run takes the fused kernel, which needs no workspace but
 // the fused tables of the plan (plan.d_quads not null).
-bool series_fwd_fused(int64_t M, int64_t P, int64_t B, int32_t prec);
+bool series_fwd_fused(int64_t M, int64_t B, int32_t prec);
 
 // ---- FP64 without a stored basis (fused.hip) ----
 
@@ -96,7 +96,7 @@ bool series_fwd_fused(int64_t M, int64_t P, int64_t B, int32_t prec);
 // (c or c2 nullable, one of them given; tr, tt nullable), where
 // fused_fwd_ok(.., dir = c2 given) says that the kernel takes the sizes and
 // is the faster one.
-bool fused_fwd_ok(int64_t M, int64_t P, int64_t B, bool dir);
+bool fused_fwd_ok(int64_t M, int64_t B, bool dir);
 zp_status launch_fused_fwd(const Plan &p, const double *r, const double *th, int64_t P, const double *c,
                            const double *c2, const double *tr, const double *tt, int64_t B, double *f, hipStream_t s);
 
@@ -104,9 +104,10 @@ zp_status launch_fused_fwd(const Plan &p, const double *r, const double *th, int
 // Second order: the same with u in place of c (if u), plus the sums of the
 // second-order planes Er, Et along (ur, ut) with c (if c).  out_r, out_t
 // nullable.  part: 16 fused_dot_chunks(B) P bytes, needed when there is more
-// than one chunk.
-bool fused_dot_ok(int64_t M, int64_t P, int64_t B);
+// than one chunk.  P: at most fused_dot_points(B).
+bool fused_dot_ok(int64_t M, int64_t B);
 int64_t fused_dot_chunks(int64_t B);
+int64_t fused_dot_points(int64_t B);
 zp_status launch_fused_dot(const Plan &p, const double *r, const double *th, int64_t P, const double *c,
                            const double *u, const double *ur, const double *ut, bool second, int64_t B,
                            const double *g, double *part, double *out_r, double *out_t, hipStream_t s);

@@ -239,4 +239,8 @@ zp_status launch_chain_kernel_polar(const Plan &plan, const double *d_r, int64_t
 zp_status set_error(zp_status s, const std::string &msg);
 zp_status hip_check(hipError_t e, const char *what);
 
+// Workgroups that one dimension of a launch can hold: fewer than 2^32 work
+// items.  (More is no error: the count wraps, and work is left out.)
+constexpr int64_t max_workgroups(int64_t threads) { return (((int64_t)1 << 32) - 1) / threads; }
+
 } // namespace zp
