@@ -108,17 +108,30 @@ zp_status upload3(Plan3 &p)
 
 } // namespace
 
-// A cached list equal to this one, on any device (null: none).  Its modes have
-// been checked and its distinct pairs are known.
-static std::shared_ptr<Plan3> find_plan3(const int32_t *n, const int32_t *m, const int32_t *l, int64_t J)
+static bool same_list(const Plan3 &p, const int32_t *n, const int32_t *m, const int32_t *l, int64_t J)
+{
+    return (int64_t)p.n.size() == J && std::equal(p.n.begin(), p.n.end(), n) &&
+           std::equal(p.m.begin(), p.m.end(), m) && std::equal(p.l.begin(), p.l.end(), l);
+}
+
+// A cached list equal to this one (null: none): the one on device dev, now the
+// most recently used, or else another device's.  Its modes have been checked and
+// its distinct pairs are known.  dev < 0: for its pairs only, no use of the list.
+static std::shared_ptr<Plan3> find_plan3(const int32_t *n, const int32_t *m, const int32_t *l, int64_t J, int dev)
 {
     if (J <= 0 || !n || !m || !l) return nullptr;
     std::lock_guard<std::mutex> lock(g_mu3);
-    for (const auto &p : g_cache3)
-        if ((int64_t)p->n.size() == J && std::equal(p->n.begin(), p->n.end(), n) &&
-            std::equal(p->m.begin(), p->m.end(), m) && std::equal(p->l.begin(), p->l.end(), l))
-            return p;
-    return nullptr;
+    std::shared_ptr<Plan3> other;
+    for (auto it = g_cache3.begin(); it != g_cache3.end(); ++it) {
+        if ((other && (*it)->device != dev) || !same_list(**it, n, m, l, J)) continue;
+        if ((*it)->device == dev) {
+            g_cache3.splice(g_cache3.begin(), g_cache3, it);
+            return g_cache3.front();
+        }
+        other = *it;
+        if (dev < 0) break;
+    }
+    return other;
 }
 
 // As get_plan: the lookup under the lock, a missing plan built without it,
@@ -130,9 +143,7 @@ zp_status get_plan3(const int32_t *n, const int32_t *m, const int32_t *l, int64_
     if (st != ZP_OK) return st;
     auto lookup = [&]() -> bool { // under the lock
         for (auto it = g_cache3.begin(); it != g_cache3.end(); ++it) {
-            Plan3 &p = **it;
-            if (p.device == dev && (int64_t)p.n.size() == J && std::equal(p.n.begin(), p.n.end(), n) &&
-                std::equal(p.m.begin(), p.m.end(), m) && std::equal(p.l.begin(), p.l.end(), l)) {
+            if ((*it)->device == dev && same_list(**it, n, m, l, J)) {
                 g_cache3.splice(g_cache3.begin(), g_cache3, it);
                 *out = g_cache3.front();
                 return true;
@@ -186,10 +197,13 @@ size_t al(size_t x) { return (x + 255) / 256 * 256; }
 
 // known: the list's cached plan, if there is one (18 513 modes: a comparison
 // takes about 10 us, checking and deduplicating the list again about 150).
+// use: the call goes on to use the list on the current device.
 zp_status checks3(const int32_t *n, const int32_t *m, const int32_t *l, int64_t J, int64_t P, int64_t Q, int64_t B,
-                  int32_t prec, std::shared_ptr<Plan3> *known)
+                  int32_t prec, bool use, std::shared_ptr<Plan3> *known)
 {
-    *known = find_plan3(n, m, l, J);
+    int dev = -1;
+    if (use && hipGetDevice(&dev) != hipSuccess) dev = -1; // reported where the device is used
+    *known = find_plan3(n, m, l, J, dev);
     if (!*known) {
         zp_status st = check_modes_arg(n, m, J);
         if (st != ZP_OK) return st;
@@ -251,7 +265,7 @@ zp_status zp_series3d_workspace(const int32_t *h_n, const int32_t *h_m, const in
                                 int64_t Q, int64_t B, int32_t prec, size_t *full_bytes, size_t *min_bytes)
 {
     std::shared_ptr<Plan3> known;
-    zp_status st = checks3(h_n, h_m, h_l, J, P, Q, B, prec, &known);
+    zp_status st = checks3(h_n, h_m, h_l, J, P, Q, B, prec, false, &known);
     if (st != ZP_OK) return st;
     if (!full_bytes) return set_error(ZP_ERR_ARG, "null full_bytes");
     const int64_t U = distinct_pairs(h_n, h_m, J, known);
@@ -267,7 +281,7 @@ zp_status zp_series3d_cache_bytes(const int32_t *h_n, const int32_t *h_m, const 
                                   int32_t prec, size_t *bytes)
 {
     std::shared_ptr<Plan3> known;
-    zp_status st = checks3(h_n, h_m, h_l, J, P, 0, 0, prec, &known);
+    zp_status st = checks3(h_n, h_m, h_l, J, P, 0, 0, prec, false, &known);
     if (st != ZP_OK) return st;
     return zp_series_cache_bytes(distinct_pairs(h_n, h_m, J, known), P, prec, bytes);
 }
@@ -278,7 +292,7 @@ zp_status zp_series3d_fwd(const int32_t *h_n, const int32_t *h_m, const int32_t 
                           void *stream)
 {
     std::shared_ptr<Plan3> known;
-    zp_status st = checks3(h_n, h_m, h_l, J, P, Q, B, prec, &known);
+    zp_status st = checks3(h_n, h_m, h_l, J, P, Q, B, prec, true, &known);
     if (st != ZP_OK) return st;
     if (J == 0 || P == 0 || Q == 0 || B == 0) return ZP_OK;
     if (!d_r || !d_theta || !d_phi || !d_c || !d_f) return set_error(ZP_ERR_ARG, "null pointer");
@@ -306,7 +320,7 @@ zp_status zp_series3d_bwd(const int32_t *h_n, const int32_t *h_m, const int32_t 
                           void *stream)
 {
     std::shared_ptr<Plan3> known;
-    zp_status st = checks3(h_n, h_m, h_l, J, P, Q, B, prec, &known);
+    zp_status st = checks3(h_n, h_m, h_l, J, P, Q, B, prec, true, &known);
     if (st != ZP_OK) return st;
     if (J == 0 || P == 0 || Q == 0 || B == 0) return ZP_OK;
     if (!d_r || !d_theta || !d_phi || !d_c || !d_g) return set_error(ZP_ERR_ARG, "null pointer");
