@@ -1008,14 +1008,22 @@ bool small_rows(int64_t M, int64_t B) { return M < (1 << 24) && B < (1 << 20) &&
 
 } // namespace
 
-// Chosen by the sets alone (and the 32-bit offsets), so that a point's row
-// does not depend on how many points a call has.  Forward, basis + GEMM ->
-// fused: (n <= 64, 65536 points) 755 -> 382 us with 64 sets, 787 -> 751 with
-// 128; (n <= 40, 2048 points, 128 sets) 139 -> 23 us; (n <= 40, 16384 points)
-// 156 -> 94 us with 128 sets, 157 -> 137 with 192, 162 -> 180 with 256, where
-// the GEMM's larger tiles win.  With the directional derivative (n <= 64,
-// 65536 points) 1502 -> 1288 us with 96 sets, 1521 -> 1712 with 128.
-bool fused_fwd_ok(int64_t M, int64_t B, bool dir) { return B <= (dir ? 96 : 128) && small_rows(M, B); }
+// Chosen by the sets and the modes alone (and the 32-bit offsets), so that a
+// point's row does not depend on how many points a call has or on whether it
+// fills a cache.  Forward, basis + GEMM -> fused, us: (n <= 64, 65536 points)
+// 565 -> 382 with 64 sets, 771 -> 598 with 96, 785 -> 745 with 128; (n <= 40,
+// 2048 points) 57 -> 24 and (16384 points) 99 -> 98 with 128.  A call that fills a
+// cache writes the planes as well, which the GEMM then reads, while the fused
+// kernel forms the basis again: (n <= 64, 65536 points) 1145 -> 1247 with 96 sets,
+// 1150 -> 1404 with 128; (n <= 40, 16384 points) 138 -> 142, 139 -> 161.  Autograd
+// keeps a basis from 97 sets on (the column dot's limit), so there the line is
+// 96: forward and backward of 97 to 128 sets, fused -> GEMM, 2757 -> 2520 (n <=
+// 64, 65536 points), 329 -> 311 (n <= 40, 16384), 127 -> 115 (n <= 20, 16384).  The
+// contraction pads the modes to 128 or 256: up to 192 modes it loses with a
+// cache too, 340 -> 356 (n <= 16, 65536 points), 193 -> 202 (n <= 14, 16384).
+// With the directional derivative (n <= 64, 65536 points) 1502 -> 1288 with 96
+// sets, 1521 -> 1712 with 128.
+bool fused_fwd_ok(int64_t M, int64_t B, bool dir) { return B <= (dir || M > 192 ? 96 : 128) && small_rows(M, B); }
 
 zp_status launch_fused_fwd(const Plan &p, const double *r, const double *th, int64_t P, const double *c,
                            const double *c2, const double *tr, const double *tt, int64_t B, double *f, hipStream_t s)
