@@ -11,10 +11,9 @@
 // reaches its degree K = (n - alpha)/2: the lane assembles R and its
 // r-derivatives, applies the angular factor, and stores.  For a fixed column
 // the 64 lanes of a wave store 128 consecutive points: 1 KB contiguous per
-// store instruction (16 bytes per lane).  With an angular factor stores are
-// marked non-temporal; for radial values alone plain ones are faster (n <= 200,
-// 100 000 points, orders 0 to 2, 24.5 GB: 4 577 -> 4 501 us), where for the
-// basis they made no difference or lost 3% (n <= 50, 8192 points, 86 us).
+// store instruction (16 bytes per lane).  Stores are marked non-temporal, except
+// those of radial tables of some sizes (plain_stores, below); for the basis plain
+// ones made no difference or lost 3% (n <= 50, 8192 points, 86 us).
 //
 // Arithmetic: the endpoint-anchored difference form of the beta = 0 Jacobi
 // recurrence (see zp_internal.hpp) with the derivatives with respect to
@@ -128,7 +127,7 @@ typedef double d2 __attribute__((ext_vector_type(2)));
 // lane (nt even) both lie on one radius, and the lane's radial recurrence
 // (the state sized RS below) runs once for both.  Every value is formed
 // exactly as for the same point given as (r_p, theta_p).
-template <int J, bool ANG, bool KB, int NPL, bool DIR, bool SEC, bool POLAR>
+template <int J, bool ANG, bool KB, int NPL, bool DIR, bool SEC, bool POLAR, bool PLAIN>
 __global__ __launch_bounds__(kBlock) void chain_kernel(const Chain *__restrict__ chains,
                                                        const Coef *__restrict__ coefs,
                                                        const Emit *__restrict__ emits,
@@ -276,9 +275,9 @@ __global__ __launch_bounds__(kBlock) void chain_kernel(const Chain *__restrict__
                     double *dst = (double *)base + idx;
                     if (live[NPL - 1]) {
                         const d2 pair = {vq[0], vq[NPL - 1]};
-                        store<ANG>(pair, (d2 *)dst);
+                        store<!PLAIN>(pair, (d2 *)dst);
                     } else if (live[0]) {
-                        store<ANG>(vq[0], dst);
+                        store<!PLAIN>(vq[0], dst);
                     }
                 }
                 continue;
@@ -334,7 +333,7 @@ __global__ __launch_bounds__(kBlock) void chain_kernel(const Chain *__restrict__
 // resident slot on 256 CUs, so the heaviest chains do not form a tail.
 constexpr int64_t kMinWorkgroups = 8192;
 
-template <int J, bool ANG, bool KB, int NPL, bool DIR = false, bool SEC = false, bool POLAR = false>
+template <int J, bool ANG, bool KB, int NPL, bool DIR = false, bool SEC = false, bool POLAR = false, bool PLAIN = false>
 hipError_t launch(const Plan &plan, const double *r, const double *th, int64_t P, const Planes &o, hipStream_t s,
                   int64_t nt = 0)
 {
@@ -345,9 +344,43 @@ hipError_t launch(const Plan &plan, const double *r, const double *th, int64_t P
     const Chain *list = use_pieces ? plan.d_pieces : plan.d_chains;
     const size_t count = use_pieces ? plan.pieces.size() : plan.chains.size();
     const dim3 grid((unsigned)tiles, (unsigned)count);
-    hipLaunchKernelGGL((chain_kernel<J, ANG, KB, NPL, DIR, SEC, POLAR>), grid, dim3(kBlock), 0, s, list, plan.d_coefs,
+    hipLaunchKernelGGL((chain_kernel<J, ANG, KB, NPL, DIR, SEC, POLAR, PLAIN>), grid, dim3(kBlock), 0, s, list, plan.d_coefs,
                        plan.d_emits, r, th, P, o, nt);
     return hipGetLastError();
+}
+
+// Whether a radial table (two points per lane) takes plain stores, by the length
+// P of its columns and its size.  Plain stores leave their lines in the 256 MB
+// last-level cache, so that a table which about fits it is taken up by the cache,
+// and lines that two waves share are completed there before they go to memory;
+// non-temporal ones go past it, but reach memory as whole lines where columns
+// start on 64-byte boundaries (P a multiple of 8).  Orders 0 and 2, non-temporal /
+// plain, us:
+//                                n <= 16, 2     n <= 50, 0     n <= 100, 2    n <= 200, 2
+//   P multiple of 8    50 MB       10.4 / 10.8    11.1 / 12.7    18.3 / 20.5   27.1 / 28.6
+//                     100 MB       19.1 / 17.9    19.6 / 17.8    24.2 / 23.9   28.1 / 28.2
+//                     128 MB       24.4 / 21.9    25.0 / 22.9    32.4 / 25.4   36.6 / 36.9
+//                     290 MB       54.4 / 44.5    55.1 / 45.1    61.1 / 46.8   70.1 / 55.6
+//                     330 MB       62.0 / 63.2    62.7 / 63.3    69.7 / 70.0   76.6 / 77.7
+//                     2.5 GB        467 / 542      477 / 533      494 / 573     516 / 589
+//                    25.0 GB                                     4879 / 5863   4881 / 5850
+//   P = 2 modulo 4     64 MB       15.1 / 12.9    16.3 / 13.6    19.6 / 21.2   27.3 / 28.5
+//                     200 MB       50.1 / 32.8    50.9 / 32.7    57.0 / 35.8   61.3 / 39.9
+//                     1.0 GB        244 / 235      249 / 243      274 / 256     286 / 267
+//                     2.5 GB        613 / 630      624 / 646      690 / 693     708 / 698
+//                    25.0 GB                                     6861 / 7012   7015 / 7165
+// Columns of more than about 1.5 MB (8 MB where they start anywhere) lose earlier:
+// n <= 16, order 0, 160 MB, P = 246 912: 27.8 / 30.2; 1.2 GB, P = 1 851 850: 272 / 282.
+// With columns on 256-byte boundaries plain stores win again by 1 to 2% from 1.6
+// GB on while columns are short (n <= 200, P = 100 000, order 2, 24.5 GB: 4585 /
+// 4510; n <= 100, order 2, 2.5 GB: 481 / 472; n <= 16, 2.5 GB, P = 3.9e6: 439 / 477).
+// Odd P (one point per lane) is non-temporal throughout.
+bool plain_stores(int64_t P, int64_t bytes)
+{
+    constexpr int64_t kMiB = 1 << 20;
+    if (P % 8) return bytes >= 72 * kMiB && bytes <= 1024 * kMiB && P <= (1 << 20);
+    if (bytes >= (P < 2048 ? 112 : 92) * kMiB && bytes <= 288 * kMiB && P <= 3 << 16) return true;
+    return P % 32 == 0 && bytes >= 1500 * kMiB && P <= (1 << 18);
 }
 
 template <int J, bool ANG, bool DIR = false>
@@ -356,7 +389,13 @@ hipError_t launch_npl(const Plan &plan, const double *r, const double *th, int64
     bool all_f64 = !DIR || o.dir_fmt == F64;
     for (int q = 0; q < 5; ++q)
         if (o.plane[q] && o.fmt[q] != F64) all_f64 = false;
-    if (all_f64 && (o.ld % 2) == 0) return launch<J, ANG, false, 2, DIR>(plan, r, th, P, o, s);
+    if (all_f64 && (o.ld % 2) == 0) {
+        if constexpr (!ANG) {
+            if (plain_stores(P, 8 * P * (J + 1) * (int64_t)plan.n.size()))
+                return launch<J, ANG, false, 2, DIR, false, false, true>(plan, r, th, P, o, s);
+        }
+        return launch<J, ANG, false, 2, DIR>(plan, r, th, P, o, s);
+    }
     return launch<J, ANG, false, 1, DIR>(plan, r, th, P, o, s);
 }
 
