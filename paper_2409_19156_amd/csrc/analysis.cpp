@@ -72,8 +72,6 @@ void gauss_legendre_r(int64_t N, std::vector<long double> &r, std::vector<long d
     }
 }
 
-size_t al(size_t x) { return (x + 255) / 256 * 256; }
-
 constexpr int64_t kMaxGridRadii = 4096;
 
 } // namespace
@@ -107,15 +105,7 @@ zp_status zp_analysis_grid(int64_t nr, int64_t nt, double *h_r, double *h_theta,
 zp_status zp_series_analysis_workspace(int64_t M, int64_t P, int64_t B, int32_t prec, size_t *full_bytes,
                                        size_t *min_bytes)
 {
-    if (M < 0 || P < 0 || B < 0) return set_error(ZP_ERR_ARG, "negative M, P or B");
-    if (!full_bytes) return set_error(ZP_ERR_ARG, "null full_bytes");
-    size_t f = 0, mn = 0;
-    zp_status st = zp_series_workspace(M, P, B, prec, &f, &mn);
-    if (st != ZP_OK) return st;
-    const size_t head = al(8 * (size_t)P * (size_t)B);
-    *full_bytes = head + f;
-    if (min_bytes) *min_bytes = head + mn;
-    return ZP_OK;
+    return zp_series_workspace(M, P, B, prec, full_bytes, min_bytes); // no weighted copy of the samples
 }
 
 zp_status zp_series_analysis(const int32_t *h_n, const int32_t *h_m, int64_t M, const double *d_r,
@@ -136,8 +126,7 @@ zp_status zp_series_analysis(const int32_t *h_n, const int32_t *h_m, int64_t M, 
     size_t f = 0, mn = 0;
     st = zp_series_workspace(M, P, B, prec, &f, &mn);
     if (st != ZP_OK) return st;
-    const size_t head = al(8 * (size_t)P * (size_t)B);
-    if (ws_bytes < head + mn)
+    if (ws_bytes < mn)
         return set_error(ZP_ERR_WORKSPACE, "workspace smaller than the minimum (zp_series_analysis_workspace)");
     std::shared_ptr<Plan> plan;
     st = get_plan(h_n, h_m, M, &plan);
@@ -145,7 +134,7 @@ zp_status zp_series_analysis(const int32_t *h_n, const int32_t *h_m, int64_t M, 
     // the weights go with the samples' conversion, the norms with the
     // reduction of the partial sums
     return series_bwd_run(*plan, M, d_r, d_theta, P, nullptr, B, prec, d_f, d_w, true, nullptr, d_c, nullptr, nullptr,
-                          (char *)d_ws + head, ws_bytes - head, s);
+                          d_ws, ws_bytes, s);
 }
 
 } // extern "C"
