@@ -46,8 +46,13 @@ def _points(x: torch.Tensor, name: str) -> torch.Tensor:
     return x.reshape(-1).contiguous()
 
 
+# The raw handle without a Stream object around it (2 us of a 10 us call), where
+# this torch has it.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(dev: torch.device) -> int:
-    return torch._C._cuda_getCurrentRawStream(dev.index)
+    return _raw_stream(dev.index) if _raw_stream else torch.cuda.current_stream(dev).cuda_stream
 
 
 _HERE = contextlib.nullcontext()
@@ -55,7 +60,7 @@ _HERE = contextlib.nullcontext()
 
 def _on(dev: torch.device):
     """Context with ``dev`` current (nothing to do where it is already)."""
-    return _HERE if torch._C._cuda_getDevice() == dev.index else torch.cuda.device(dev)
+    return _HERE if torch.cuda.current_device() == dev.index else torch.cuda.device(dev)
 
 
 def basis_polar(n, m, r: torch.Tensor, theta: torch.Tensor, mask: int = Z,
@@ -406,9 +411,9 @@ class ZernikeSeries(torch.autograd.Function):
         c, r, theta = ctx.saved_tensors
         need = tuple(bool(x) for x in ctx.needs_input_grad[:3])
         args = (c, r, theta, g.contiguous(), ctx.modes, ctx.prec, ctx.cache, ctx.budget, need)
-        if torch.is_grad_enabled() or forward_ad._current_level >= 0:
+        if torch.is_grad_enabled() or any(forward_ad.unpack_dual(x).tangent is not None for x in args[:4]):
             gc, gr, gt = _SeriesBackward.apply(*args)
-        else:  # nobody differentiates the gradients: no graph node for them
+        else:  # nobody differentiates the gradients, in either mode: no graph node for them
             nh, mh = ctx.modes
             gc, gr, gt = series_backward(nh, mh, c=c, r=r, theta=theta, g=args[3], prec=ctx.prec, cache=ctx.cache,
                                          need=need, mem_budget=ctx.budget)
