@@ -91,8 +91,11 @@ static void build_quads(Plan &plan)
             Q.spread = *std::max_element(Q.alpha, Q.alpha + 4) - Q.alpha_min;
             for (int k = 0; k <= Q.kmax; ++k) {
                 for (size_t y = 0; y < 4; ++y) {
-                    const Coef cf = k ? step_coef(k, Q.alpha[y]) : Coef{};
-                    if (k) a_lo[y] = -a_lo[y] * (long double)(Q.alpha[y] + k) / (long double)k;
+                    // past its own last degree a chain stands still: beyond the
+                    // disc it would go on growing, to infinity before the others
+                    const bool own = k <= ch[(size_t)chain_of(q, y)].kmax;
+                    const Coef cf = k && own ? step_coef(k, Q.alpha[y]) : Coef{};
+                    if (k && own) a_lo[y] = -a_lo[y] * (long double)(Q.alpha[y] + k) / (long double)k;
                     plan.qsteps.push_back({cf.cc_lo, cf.bs_lo, (double)a_lo[y], 0.0});
                     plan.qsteps.push_back({cf.cc_hi, cf.bs_hi, 1.0, 0.0});
                 }

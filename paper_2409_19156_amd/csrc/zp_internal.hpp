@@ -70,8 +70,8 @@ struct Emit {
 // QuadStep: recurrence step k of one chain (k = 0: no step) for one anchor,
 // and the factor a from v_k to R / r^alpha: (-1)^k C(k+alpha, k) for the low
 // anchor, 1 for the high one.  Rows of eight: [chain y][low, high].  Every
-// chain of a quad has steps up to the quad's kmax, whether it is asked for
-// their degrees or not.
+// chain of a quad has steps up to the quad's kmax; past its own last degree
+// they change nothing (cc = bs = 0).
 struct QuadStep {
     double cc, bs, a, pad;
 };
