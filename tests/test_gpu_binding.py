@@ -1,5 +1,5 @@
-"""The binding's shortcuts: the current stream without torch's private raw
-handle, and gradients without a graph node only where nothing differentiates
+"""The binding's shortcuts: the current stream and device with and without
+torch's private functions, and gradients without a graph node only where nothing differentiates
 them (a tangent on what the backward reads is refused, not dropped)."""
 from __future__ import annotations
 
@@ -26,6 +26,7 @@ def test_current_stream(monkeypatch, raw):
     zp, n, m, c, r, th, _ = _case()
     if not raw:
         monkeypatch.setattr(zp, "_raw_stream", None)
+        monkeypatch.setattr(zp, "_current_device", torch.cuda.current_device)
     ref = zp.series_forward(n, m, r, th, c)
     torch.cuda.synchronize()
     s = torch.cuda.Stream()
