@@ -623,7 +623,7 @@ template <int CT> bool small_tiles(int64_t M, int64_t N, bool beside)
     using W = CfgE<CT, EPI_STORE, WIDE>;
     using S = CfgE<CT, EPI_STORE, SMALL>;
     if (N > (int64_t)65535 * S::BN) return false; // grid.y
-    const int64_t cus = device_cus();
+    const int64_t cus = std::max(1, device_cus()); // (0 where the count is not known)
     auto rounds = [&](int64_t bm, int64_t bn) {
         return (((M + bm - 1) / bm) * ((N + bn - 1) / bn) + cus - 1) / cus;
     };
