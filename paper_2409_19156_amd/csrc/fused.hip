@@ -975,28 +975,28 @@ template <int R, bool DIR> void launch_grad_n(const GradArgs &g, int fn, int64_t
         launch_grad_t<R, 1, DIR>(g, nsb, s);
 }
 
-// out[m][b] = (out +) sum over splits, in order; norm: times the inverse mode norms.
+// out[m][b] = (out +) sum over splits, in order; norm: times the inverse mode
+// norms.  One coefficient per thread, from i0 on.
 __global__ __launch_bounds__(kThreads) void grad_reduce_kernel(const double *__restrict__ part, int S, int64_t M,
                                                                int64_t B, const Chain *chains,
                                                                const int32_t *row_chain, const Emit *emits, int norm,
-                                                               int accumulate, double *__restrict__ out)
+                                                               int accumulate, int64_t i0, double *__restrict__ out)
 {
-    const int64_t stride = (int64_t)gridDim.x * kThreads;
-    for (int64_t b = (int64_t)blockIdx.x * kThreads + threadIdx.x; b < M * B; b += stride) {
-        const int64_t e = b / B; // emission, set b - e B
-        const Emit em = emits[e];
-        const int64_t o = em.col * B + (b - e * B);
-        double v = 0.0;
+    const int64_t b = i0 + (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    const int64_t e = b / B; // emission, set b - e B
+    if (e >= M) return;
+    const Emit em = emits[e];
+    const int64_t o = em.col * B + (b - e * B);
+    double v = 0.0;
 #pragma unroll 8
-        for (int k = 0; k < S; ++k) v += part[k * M * B + o];
-        if (accumulate) v += out[o];
-        if (norm) {
-            int lo = row_chain[e >> 4];
-            while (e >= chains[lo].emit_off + chains[lo].emit_cnt) ++lo;
-            v *= inv_norm(em.K, chains[lo].alpha);
-        }
-        out[o] = v;
+    for (int k = 0; k < S; ++k) v += part[k * M * B + o];
+    if (accumulate) v += out[o];
+    if (norm) {
+        int lo = row_chain[e >> 4];
+        while (e >= chains[lo].emit_off + chains[lo].emit_cnt) ++lo;
+        v *= inv_norm(em.K, chains[lo].alpha);
     }
+    out[o] = v;
 }
 
 // Two workgroups of four waves per CU is what the larger tiles' registers
@@ -1136,10 +1136,15 @@ zp_status launch_fused_grad(const Plan &p, const double *r, const double *th, in
 zp_status launch_grad_reduce(const Plan &p, const double *part, int S, int64_t M, int64_t B, bool norm,
                              bool accumulate, double *C, hipStream_t s)
 {
-    const int64_t blocks = std::min((M * B + kThreads - 1) / kThreads, max_workgroups(kThreads));
-    hipLaunchKernelGGL(grad_reduce_kernel, dim3((unsigned)blocks), dim3(kThreads), 0, s, part, S, M, B, p.d_achains,
-                       p.d_row_chain, p.d_emits, norm ? 1 : 0, accumulate ? 1 : 0, C);
-    return hip_check(hipGetLastError(), "gradient reduce launch");
+    constexpr int64_t kMost = max_workgroups(kThreads) * kThreads;
+    for (int64_t i0 = 0; i0 < M * B; i0 += kMost) {
+        const int64_t blocks = (std::min(kMost, M * B - i0) + kThreads - 1) / kThreads;
+        hipLaunchKernelGGL(grad_reduce_kernel, dim3((unsigned)blocks), dim3(kThreads), 0, s, part, S, M, B, p.d_achains,
+                           p.d_row_chain, p.d_emits, norm ? 1 : 0, accumulate ? 1 : 0, i0, C);
+        const zp_status st = hip_check(hipGetLastError(), "gradient reduce launch");
+        if (st != ZP_OK) return st;
+    }
+    return ZP_OK;
 }
 
 } // namespace zp

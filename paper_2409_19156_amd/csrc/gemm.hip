@@ -735,29 +735,27 @@ __device__ __forceinline__ void put2(void *dst, int ct, int64_t idx, int64_t sub
     }
 }
 
-// Row conversion: dst[r][c] for r < rows_pad, c < ldd
+// Row conversion: dst[r][c] for r0 <= r < r0 + gridDim.x (padded rows), c < ldd
 // (even), two columns per lane; zero outside src's R x C; rows times roww if
 // that is set.
 __global__ __launch_bounds__(256) void convert_rows_kernel(const double *__restrict__ src, int64_t R, int64_t C,
-                                                           int64_t lds, int ct, void *dst, int64_t rows_pad,
-                                                           int64_t ldd, int64_t sub,
-                                                           const double *__restrict__ roww)
+                                                           int64_t lds, int ct, void *dst, int64_t ldd, int64_t sub,
+                                                           const double *__restrict__ roww, int64_t r0)
 {
+    const int64_t r = r0 + blockIdx.x;
     const int64_t c = ((int64_t)blockIdx.y * 256 + threadIdx.x) * 2;
     if (c >= ldd) return;
-    for (int64_t r = blockIdx.x; r < rows_pad; r += gridDim.x) {
-        double v0 = 0.0, v1 = 0.0;
-        if (r < R) {
-            if (c < C) v0 = src[r * lds + c];
-            if (c + 1 < C) v1 = src[r * lds + c + 1];
-            if (roww) {
-                const double w = roww[r];
-                v0 *= w;
-                v1 *= w;
-            }
+    double v0 = 0.0, v1 = 0.0;
+    if (r < R) {
+        if (c < C) v0 = src[r * lds + c];
+        if (c + 1 < C) v1 = src[r * lds + c + 1];
+        if (roww) {
+            const double w = roww[r];
+            v0 *= w;
+            v1 *= w;
         }
-        put2(dst, ct, r * ldd + c, sub, v0, v1);
     }
+    put2(dst, ct, r * ldd + c, sub, v0, v1);
 }
 
 // Eight values (k = 8 kg .. 8 kg + 7 of one column) -> one 16-byte fragment
@@ -837,18 +835,17 @@ __global__ __launch_bounds__(256) void convert_g_bwd_kernel(const double *__rest
 // and points that hold no pad (scanning the whole operand took 23 us per 8192
 // points of n <= 64 for 32 768 pad elements).
 __global__ __launch_bounds__(256) void zero_kb8_kernel(uint16_t *dst, int64_t M, int64_t P, int64_t ld, int64_t sub,
-                                                       int64_t g0, int64_t groups, int64_t p0)
+                                                       int64_t g0, int64_t p0, int64_t blocks_per_row)
 {
-    const int64_t p = p0 + (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int64_t gq = g0 + blockIdx.x / blocks_per_row;
+    const int64_t p = p0 + blockIdx.x % blocks_per_row * 256 + threadIdx.x;
     if (p >= ld) return;
-    for (int64_t gq = g0 + blockIdx.y; gq < groups; gq += gridDim.y) {
-        uint16_t *at = dst + (gq * ld + p) * 8;
-        if (gq * 8 >= M || p >= P) {
+    uint16_t *at = dst + (gq * ld + p) * 8;
+    if (gq * 8 >= M || p >= P) {
 #pragma unroll
-            for (int q = 0; q < 3; ++q) *(u4 *)(at + q * sub) = u4{0, 0, 0, 0};
-        } else {
-            for (int e = (int)(M - gq * 8); e < 8; ++e) at[e] = at[e + sub] = at[e + 2 * sub] = 0;
-        }
+        for (int q = 0; q < 3; ++q) *(u4 *)(at + q * sub) = u4{0, 0, 0, 0};
+    } else {
+        for (int e = (int)(M - gq * 8); e < 8; ++e) at[e] = at[e + sub] = at[e + 2 * sub] = 0;
     }
 }
 
@@ -865,17 +862,17 @@ __global__ __launch_bounds__(256) void zero_kernel(T *dst, int64_t rows, int64_t
     }
 }
 
-// C = (C +) sum of the S partial sums, in order (M N contiguous elements).
+// C = (C +) sum of the S partial sums, in order: n contiguous elements of
+// partial sums `total` apart.
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const double *__restrict__ part, int S, int64_t total,
-                                                            double *C, int accumulate)
+                                                            int64_t n, double *C, int accumulate)
 {
-    const int64_t stride = (int64_t)gridDim.x * 256;
-    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < total; e += stride) {
-        double s = 0.0;
+    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (e >= n) return;
+    double s = 0.0;
 #pragma unroll 8
-        for (int k = 0; k < S; ++k) s += part[(int64_t)k * total + e];
-        C[e] = accumulate ? C[e] + s : s;
-    }
+    for (int k = 0; k < S; ++k) s += part[(int64_t)k * total + e];
+    C[e] = accumulate ? C[e] + s : s;
 }
 
 __global__ void coldot_reduce_kernel(const double *__restrict__ part, int T, int64_t P, double *out1, double *out2)
@@ -922,9 +919,13 @@ zp_status launch_convert(const double *src, int64_t R, int64_t C, int64_t lds, i
 {
     if (ldd % 2 || sub % 2 || ((uintptr_t)dst & 15))
         return set_error(ZP_ERR_ARG, "internal: conversion target not padded or aligned");
-    const dim3 grid((unsigned)std::min(rows_pad, max_workgroups(256)), (unsigned)((ldd / 2 + 255) / 256));
-    hipLaunchKernelGGL(convert_rows_kernel, grid, dim3(256), 0, s, src, R, C, lds, ct, dst, rows_pad, ldd, sub, roww);
-    return hip_check(hipGetLastError(), "convert launch");
+    for (int64_t r0 = 0; r0 < rows_pad; r0 += max_workgroups(256)) {
+        const dim3 grid((unsigned)std::min(rows_pad - r0, max_workgroups(256)), (unsigned)((ldd / 2 + 255) / 256));
+        hipLaunchKernelGGL(convert_rows_kernel, grid, dim3(256), 0, s, src, R, C, lds, ct, dst, ldd, sub, roww, r0);
+        const zp_status st = hip_check(hipGetLastError(), "convert launch");
+        if (st != ZP_OK) return st;
+    }
+    return ZP_OK;
 }
 
 zp_status launch_convert_gather_frag(const double *src, const int32_t *perm, int64_t R, int64_t C, int64_t lds,
@@ -950,8 +951,9 @@ zp_status launch_zero_kb8(void *dst, int64_t M, int64_t Mp, int64_t P, int64_t l
 {
     auto zero = [&](int64_t g0, int64_t p0) {
         if (g0 >= Mp / 8 || p0 >= ld) return;
-        const dim3 grid((unsigned)((ld - p0 + 255) / 256), (unsigned)std::min<int64_t>(Mp / 8 - g0, 65535));
-        hipLaunchKernelGGL(zero_kb8_kernel, grid, dim3(256), 0, s, (uint16_t *)dst, M, P, ld, sub, g0, Mp / 8, p0);
+        const int64_t per_row = (ld - p0 + 255) / 256;
+        hipLaunchKernelGGL(zero_kb8_kernel, dim3((unsigned)(per_row * (Mp / 8 - g0))), dim3(256), 0, s,
+                           (uint16_t *)dst, M, P, ld, sub, g0, p0, per_row);
     };
     zero(M / 8, 0);           // the groups with pad modes, every point
     if (M >= 8) zero(0, P);   // the pad points (of all groups)
@@ -978,10 +980,15 @@ zp_status launch_zero_pad(void *dst, int ct, int64_t rows, int64_t cols, int64_t
 zp_status launch_splitk_reduce(const double *part, int S, int64_t M, int64_t N, double *C, bool accumulate,
                                hipStream_t s)
 {
-    const int64_t blocks = std::min((M * N + 255) / 256, max_workgroups(256));
-    hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)blocks), dim3(256), 0, s, part, S, M * N, C,
-                       accumulate ? 1 : 0);
-    return hip_check(hipGetLastError(), "split-K reduce launch");
+    constexpr int64_t kMost = max_workgroups(256) * 256;
+    for (int64_t e0 = 0; e0 < M * N; e0 += kMost) {
+        const int64_t n = std::min(kMost, M * N - e0);
+        hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, part + e0, S, M * N,
+                           n, C + e0, accumulate ? 1 : 0);
+        const zp_status st = hip_check(hipGetLastError(), "split-K reduce launch");
+        if (st != ZP_OK) return st;
+    }
+    return ZP_OK;
 }
 
 zp_status launch_coldot_reduce(const double *part, int T, int64_t P, double *out1, double *out2, hipStream_t s)
