@@ -30,6 +30,7 @@
 //   A = (-1)^K C(K+alpha, K) (low) or 1 (high).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <climits>
 
 #include "bf16.hpp"
@@ -391,12 +392,24 @@ hipError_t launch_npl(const Plan &plan, const double *r, const double *th, int64
         if (o.plane[q] && o.fmt[q] != F64) all_f64 = false;
     if (all_f64 && (o.ld % 2) == 0) {
         if constexpr (!ANG) {
-            if (plain_stores(P, 8 * P * (J + 1) * (int64_t)plan.n.size()))
+            if (plain_stores(o.ld, 8 * o.ld * (J + 1) * (int64_t)plan.n.size()))
                 return launch<J, ANG, false, 2, DIR, false, false, true>(plan, r, th, P, o, s);
         }
         return launch<J, ANG, false, 2, DIR>(plan, r, th, P, o, s);
     }
     return launch<J, ANG, false, 1, DIR>(plan, r, th, P, o, s);
+}
+
+// Points of one launch (one per lane; a multiple of what a lane may take).
+constexpr int64_t kMostPoints = max_workgroups(kBlock) * kBlock;
+
+// The plain planes from point p0 of their columns on.
+Planes from_point(const Planes &o, int64_t p0)
+{
+    Planes x = o;
+    for (int q = 0; q < 5; ++q)
+        if (x.plane[q]) x.plane[q] = (char *)x.plane[q] + p0 * (x.fmt[q] == F64 ? 8 : 4);
+    return x;
 }
 
 } // namespace
@@ -406,13 +419,23 @@ zp_status launch_chain_kernel_polar(const Plan &plan, const double *d_r, int64_t
 {
     const int64_t P = nr * nt;
     if (P <= 0 || plan.chains.empty()) return ZP_OK;
-    if ((P + kBlock - 1) / kBlock > (int64_t)INT_MAX) return set_error(ZP_ERR_ARG, "too many points for one launch");
     bool all_f64 = true;
     for (int q = 0; q < 5; ++q)
         if (out.plane[q] && out.fmt[q] != F64) all_f64 = false;
     if (out.kb || out.dir || out.kb_dir || out.sec_r || out.sec_t || J < 0 || J > 3)
         return set_error(ZP_ERR_ARG, "internal: polar grids take plain basis planes");
-    const bool two = all_f64 && (nt % 2) == 0; // a lane's two points then share their radius
+    if (P > kMostPoints) { // some rows at a time, or some angles of one row
+        const int64_t rows = std::max<int64_t>(1, kMostPoints / nt), cols = rows > 1 ? nt : std::min(nt, kMostPoints);
+        for (int64_t i = 0; i < nr; i += rows)
+            for (int64_t j = 0; j < nt; j += cols) {
+                const zp_status st = launch_chain_kernel_polar(plan, d_r + i, std::min(rows, nr - i), d_theta + j,
+                                                               std::min(cols, nt - j), J, from_point(out, i * nt + j), s);
+                if (st != ZP_OK) return st;
+            }
+        return ZP_OK;
+    }
+    // a lane's two points then share their radius and start an aligned pair
+    const bool two = all_f64 && (nt % 2) == 0 && (out.ld % 2) == 0;
     hipError_t e;
     switch (J) {
     case 0:
@@ -439,10 +462,18 @@ zp_status launch_chain_kernel(const Plan &plan, const double *d_r, const double 
                               bool angular, const Planes &out, hipStream_t s)
 {
     if (P <= 0 || plan.chains.empty()) return ZP_OK;
-    if ((P + kBlock - 1) / kBlock > (int64_t)INT_MAX) return set_error(ZP_ERR_ARG, "too many points for one launch");
     hipError_t e;
     const bool dir = out.dir || out.kb_dir;
     const bool sec = out.sec_r || out.sec_t;
+    if (P > kMostPoints) {
+        if (dir || sec || out.kb) return set_error(ZP_ERR_ARG, "too many points for one launch");
+        for (int64_t p0 = 0; p0 < P; p0 += kMostPoints) {
+            const zp_status st = launch_chain_kernel(plan, d_r + p0, d_theta ? d_theta + p0 : nullptr,
+                                                     std::min(kMostPoints, P - p0), J, angular, from_point(out, p0), s);
+            if (st != ZP_OK) return st;
+        }
+        return ZP_OK;
+    }
     if (sec) { // second-order planes (with the plain planes and dir): J = 2, one point per lane
         if (!angular || J != 2 || out.kb || out.kb_dir)
             return set_error(ZP_ERR_ARG, "internal: second-order output needs the basis, J = 2, no k-blocked copy");

@@ -5,6 +5,8 @@
 // wrote up to a quarter slower), non-temporal or plain.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "zp_internal.hpp"
 
 namespace zp {
@@ -37,17 +39,21 @@ extern "C" zp_status zp_stream_fill(double *d_out, int64_t n, double value, int3
     if (n < 0) return set_error(ZP_ERR_ARG, "n < 0");
     if (n == 0) return ZP_OK;
     if (!d_out || ((uintptr_t)d_out & 15)) return set_error(ZP_ERR_ARG, "output must be non-null and 16-byte aligned");
-    const int64_t n2 = n / 2;
-    double *tail = (n & 1) ? d_out + (n - 1) : nullptr;
-    const int64_t lanes = n2 + (tail ? 1 : 0);
-    const int64_t blocks = (lanes + 255) / 256;
-    if (blocks > 0x7FFFFFFF) return set_error(ZP_ERR_ARG, "buffer too large for one launch");
     const d2 v = {value, value};
-    if (nontemporal)
-        hipLaunchKernelGGL(fill_kernel<true>, dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream, (d2 *)d_out,
-                           n2, value, tail, v);
-    else
-        hipLaunchKernelGGL(fill_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream, (d2 *)d_out,
-                           n2, value, tail, v);
-    return hip_check(hipGetLastError(), "fill launch");
+    constexpr int64_t kMost = max_workgroups(256) * 256 * 2; // doubles of one launch
+    for (int64_t i0 = 0; i0 < n; i0 += kMost) {
+        const int64_t left = std::min(kMost, n - i0), n2 = left / 2;
+        double *out = d_out + i0;
+        double *tail = (left & 1) ? out + (left - 1) : nullptr;
+        const int64_t blocks = (n2 + (tail ? 1 : 0) + 255) / 256;
+        if (nontemporal)
+            hipLaunchKernelGGL(fill_kernel<true>, dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream, (d2 *)out,
+                               n2, value, tail, v);
+        else
+            hipLaunchKernelGGL(fill_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream, (d2 *)out,
+                               n2, value, tail, v);
+        const zp_status st = hip_check(hipGetLastError(), "fill launch");
+        if (st != ZP_OK) return st;
+    }
+    return ZP_OK;
 }

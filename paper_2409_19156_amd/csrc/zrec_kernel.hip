@@ -14,6 +14,8 @@
 // Requested modes are stored when their (n, |m|) entry is formed.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "zp_internal.hpp"
 
 namespace zp {
@@ -21,7 +23,8 @@ namespace {
 
 template <int J>
 __global__ void zrec_kernel(const int32_t *__restrict__ off, const int32_t *__restrict__ cols,
-                            const double *__restrict__ r, int64_t P, int64_t M, int nmax, double *__restrict__ out)
+                            const double *__restrict__ r, int64_t P, int64_t M, int nmax, int64_t ld,
+                            double *__restrict__ out)
 {
     extern __shared__ double lds[];
     const int nt = blockDim.x;
@@ -62,7 +65,7 @@ __global__ void zrec_kernel(const int32_t *__restrict__ off, const int32_t *__re
                 if (!live) continue;
                 const int64_t col = cols[c];
 #pragma unroll
-                for (int j = 0; j <= J; ++j) out[((int64_t)j * M + col) * P + p] = v[j];
+                for (int j = 0; j <= J; ++j) out[((int64_t)j * M + col) * ld + p] = v[j];
             }
         }
     }
@@ -82,11 +85,15 @@ zp_status launch_j(const Plan &plan, const double *r, int64_t P, double *out, hi
     while (nt > 16 && per_thread * (size_t)nt > (size_t)limit) nt /= 2;
     if (per_thread * (size_t)nt > (size_t)limit) return set_error(ZP_ERR_ARG, "recursion triangle too large for LDS");
     const size_t bytes = per_thread * (size_t)nt;
-    const int64_t blocks = (P + nt - 1) / nt;
-    if (blocks > INT32_MAX) return set_error(ZP_ERR_ARG, "too many points for one launch");
-    hipLaunchKernelGGL(zrec_kernel<J>, dim3((unsigned)blocks), dim3(nt), bytes, s, plan.d_zrec_off, plan.d_zrec_cols,
-                       r, P, (int64_t)plan.n.size(), nmax, out);
-    return hip_check(hipGetLastError(), "recursion kernel launch");
+    const int64_t most = (max_workgroups(nt) - 1) * nt;
+    for (int64_t p0 = 0; p0 < P; p0 += most) {
+        const int64_t pc = std::min(most, P - p0);
+        hipLaunchKernelGGL(zrec_kernel<J>, dim3((unsigned)((pc + nt - 1) / nt)), dim3(nt), bytes, s, plan.d_zrec_off,
+                           plan.d_zrec_cols, r + p0, pc, (int64_t)plan.n.size(), nmax, P, out + p0);
+        st = hip_check(hipGetLastError(), "recursion kernel launch");
+        if (st != ZP_OK) return st;
+    }
+    return ZP_OK;
 }
 
 } // namespace
