@@ -120,7 +120,7 @@ zp_status zp_series_analysis(const int32_t *h_n, const int32_t *h_m, int64_t M, 
     if (!d_c) return set_error(ZP_ERR_ARG, "null pointer");
     hipStream_t s = (hipStream_t)stream;
     if (P == 0) // an empty quadrature: every coefficient is zero
-        return launch_zero_pad(d_c, CT_F64, 0, 0, M, B, 0, s);
+        return launch_zero_pad(d_c, CT_F64, 0, 0, M, B, s);
     if (!d_r || !d_theta || !d_w || !d_f) return set_error(ZP_ERR_ARG, "null pointer");
     if (!d_ws || ((uintptr_t)d_ws & 255)) return set_error(ZP_ERR_ARG, "workspace must be non-null and 256-byte aligned");
     size_t f = 0, mn = 0;

@@ -208,7 +208,7 @@ struct FwdArgs {
 // registers, accumulators in vector registers: a build that kept them in
 // accumulation registers moved them at every step).  Measured, n <= 64, 65536
 // points: 1 set 130 us where the basis + GEMM took 745 (the basis alone writes
-// 1.1 GB), 64 sets 376 us (47.9 TFLOP/s) from 755; n <= 20, 5000 points, 8
+// 1.1 GB), 64 sets 382 us (47.1 TFLOP/s) from 755; n <= 20, 5000 points, 8
 // sets 54 -> under 15 us a call.
 template <int FM, int FN, bool DIR>
 __global__ __launch_bounds__(kThreads, 2) void fwd_kernel(FwdArgs g)

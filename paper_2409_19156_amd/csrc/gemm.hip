@@ -960,10 +960,8 @@ zp_status launch_zero_kb8(void *dst, int64_t M, int64_t Mp, int64_t P, int64_t l
     return hip_check(hipGetLastError(), "zero-pad launch");
 }
 
-zp_status launch_zero_pad(void *dst, int ct, int64_t rows, int64_t cols, int64_t rows_pad, int64_t ld, int64_t sub,
-                          hipStream_t s)
+zp_status launch_zero_pad(void *dst, int ct, int64_t rows, int64_t cols, int64_t rows_pad, int64_t ld, hipStream_t s)
 {
-    (void)sub;
     if (ct == CT_BF3) return set_error(ZP_ERR_ARG, "internal: zero pad of FP64 or FP32 planes only");
     const bool sides = ld > cols && rows > 0;
     const int64_t row0 = sides ? 0 : rows;

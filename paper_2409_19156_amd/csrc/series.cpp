@@ -381,7 +381,7 @@ zp_status basis_into(const Plan &plan, const double *r, const double *th, int64_
     o.fmt[1] = dfmt;
     o.plane[4] = zt;
     o.fmt[4] = dfmt;
-    zp_status st = launch_zero_pad(z, zct_of(ct), M, Pc, M, ld, Mp * ld, s);
+    zp_status st = launch_zero_pad(z, zct_of(ct), M, Pc, M, ld, s);
     if (st != ZP_OK) return st;
     return launch_chain_kernel(plan, r + p0, th + p0, Pc, zr ? 1 : 0, true, o, s);
 }
@@ -489,7 +489,7 @@ zp_status series_fwd_run(const Plan &pl, int64_t M, const double *d_r, const dou
     char *cache = (char *)d_cache;
     const size_t zsz = zsize_of(ct); // the cache's Z element
     if (have_cache) {
-        st = launch_zero_pad(cache + CL.z_off, zct_of(ct), M, P, Mp, CL.Pp, Mp * CL.Pp, s);
+        st = launch_zero_pad(cache + CL.z_off, zct_of(ct), M, P, Mp, CL.Pp, s);
         if (st != ZP_OK) return st;
     }
     st = pipeline.start();
@@ -518,7 +518,7 @@ zp_status series_fwd_run(const Plan &pl, int64_t M, const double *d_r, const dou
             o.ld = pcp;
             o.plane[0] = zb;
             o.fmt[0] = dfmt;
-            st = launch_zero_pad(zb, ct, M, pc, Mp, pcp, Mp * pcp, cs);
+            st = launch_zero_pad(zb, ct, M, pc, Mp, pcp, cs);
             if (st != ZP_OK) return st;
         }
         if (ct == CT_BF3) {
@@ -769,7 +769,7 @@ extern "C" zp_status zp_series_jvp(const int32_t *h_n, const int32_t *h_m, int64
     if (with_dir && !d_c) return set_error(ZP_ERR_ARG, "null coefficients with a point tangent");
     hipStream_t s = (hipStream_t)stream;
     if (M == 0 || (!with_c && !with_dir)) // the tangent is zero
-        return launch_zero_pad(d_tf, CT_F64, 0, 0, P, B, 0, s);
+        return launch_zero_pad(d_tf, CT_F64, 0, 0, P, B, s);
     if (!d_ws || ((uintptr_t)d_ws & 255)) return set_error(ZP_ERR_ARG, "workspace must be non-null and 256-byte aligned");
     const int ct = ct_of(prec);
     int64_t Pc = jvp_chunk_for(M, P, B, ct, ws_bytes);
@@ -830,7 +830,7 @@ extern "C" zp_status zp_series_jvp(const int32_t *h_n, const int32_t *h_m, int64
             if (with_dir) o.kb_dir = zbuf + esz * (size_t)((with_c ? 1 : 0) * Mp) * (size_t)pcp;
         } else {
             for (int b2 = 0; b2 < nblk; ++b2) {
-                st = launch_zero_pad(zbuf + esz * (size_t)(b2 * Mp) * (size_t)pcp, ct, M, pc, Mp, pcp, 0, cs);
+                st = launch_zero_pad(zbuf + esz * (size_t)(b2 * Mp) * (size_t)pcp, ct, M, pc, Mp, pcp, cs);
                 if (st != ZP_OK) return st;
             }
             if (with_c) {
@@ -986,7 +986,7 @@ zp_status zp_series_bwd2(const int32_t *h_n, const int32_t *h_m, int64_t M, cons
     bool run_u = want_rt && need_u;   // column-dot of uc g^T with dZ/dr, dZ/dtheta
     bool run_e = want_rt && need_dir; // column-dot of c g^T with Er, Et
     if (d_out_c && !need_dir) {
-        st = launch_zero_pad(d_out_c, CT_F64, 0, 0, M, B, 0, s);
+        st = launch_zero_pad(d_out_c, CT_F64, 0, 0, M, B, s);
         if (st != ZP_OK) return st;
     }
     const Bwd2Layout L(M, Pc, B, ct, Bwd2Layout(M, Pc, B, ct, false).total > ws_bytes);
@@ -1022,8 +1022,8 @@ zp_status zp_series_bwd2(const int32_t *h_n, const int32_t *h_m, int64_t M, cons
         const int64_t pcp = pad_up(pc);
         if (!run_c && !run_u && !run_e) { // the r / theta outputs of this chunk are zero
             if (rt_done) break;
-            if (d_out_r) st = launch_zero_pad(d_out_r + p0, CT_F64, 0, 0, 1, pc, 0, s);
-            if (st == ZP_OK && d_out_t) st = launch_zero_pad(d_out_t + p0, CT_F64, 0, 0, 1, pc, 0, s);
+            if (d_out_r) st = launch_zero_pad(d_out_r + p0, CT_F64, 0, 0, 1, pc, s);
+            if (st == ZP_OK && d_out_t) st = launch_zero_pad(d_out_t + p0, CT_F64, 0, 0, 1, pc, s);
             if (st != ZP_OK) return st;
             continue;
         }
@@ -1037,7 +1037,7 @@ zp_status zp_series_bwd2(const int32_t *h_n, const int32_t *h_m, int64_t M, cons
             o.fmt[4] = dfmt;
         }
         if (run_c) {
-            st = launch_zero_pad(ws + L.d_off, zct_of(ct), M, pc, M, pcp, Mp * pcp, s); // pad points, as basis_into
+            st = launch_zero_pad(ws + L.d_off, zct_of(ct), M, pc, M, pcp, s); // pad points, as basis_into
             if (st != ZP_OK) return st;
             o.dir = ws + L.d_off;
             o.dir_fmt = zfmt;

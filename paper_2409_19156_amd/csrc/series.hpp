@@ -146,8 +146,7 @@ zp_status launch_zero_kb8(void *dst, int64_t M, int64_t Mp, int64_t P, int64_t l
 
 // Zero the pad region of a [rows_pad][ld] plane (FP64 or FP32) whose valid
 // block is [rows][cols].
-zp_status launch_zero_pad(void *dst, int ct, int64_t rows, int64_t cols, int64_t rows_pad, int64_t ld, int64_t sub,
-                          hipStream_t s);
+zp_status launch_zero_pad(void *dst, int ct, int64_t rows, int64_t cols, int64_t rows_pad, int64_t ld, hipStream_t s);
 
 // C[i][j] (=|+=) sum_s part[s][i][j] for s = 0..S-1, fixed order.
 zp_status launch_splitk_reduce(const double *part, int S, int64_t M, int64_t N, double *C, bool accumulate,
