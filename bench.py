@@ -32,9 +32,9 @@ FP64_PEAK_TFS = 78.6  # MI355X FP64 MFMA (dense), published
 # for 1048576 KiB written: x1.0).  Valid only for the kernel sources it was
 # taken on; reported as null once they change.
 TRAFFIC = {"sources": ("paper_2409_19156_amd/csrc/chain_kernel.hip", "paper_2409_19156_amd/csrc/zp_internal.hpp"),
-           "sha256": "3e080526f842128b253dfb8c1023478605bba82c24d8ecd642a75b110687ec3f",
-           "fetch_kib": 465.5, "fetch_scale": 1048576.0 / 524299.5,
-           "write_kib": 424725.6, "write_scale": 1.0}
+           "sha256": "97850b6b6ab824477382bb486aba537a2073a9450d5e5a7b46a888621ba65852",
+           "fetch_kib": 466.5, "fetch_scale": 1048576.0 / 524299.5,
+           "write_kib": 424780.5, "write_scale": 1.0}
 
 
 def measured_traffic():
@@ -534,7 +534,7 @@ def main():
                    "modes": wl.M, "points": wl.P, "outputs": 5, "entries": entries},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": measured_traffic(),
-                     "kernel": "chain_kernel<3, true, false, 2, false, false, false>", "bytes_per_launch": bytes_per_launch,
+                     "kernel": "chain_kernel<3, true, false, 2, false, false, false, false>", "bytes_per_launch": bytes_per_launch,
                      "avg_launch_us": ms * 1e3, "measured_fill_GBs": fill_gbs, "fill_GBs": fill_rates,
                      "frac_of_measured_fill": achieved / fill_gbs},
         "basis_polar": {"entry": "zp_basis_polar (64 radii x 128 angles, same output)", "ms": ms_polar,
