@@ -1107,18 +1107,36 @@ zp_status launch_fused_dot(const Plan &p, const double *r, const double *th, int
 // sets) 153 -> 100 us.
 bool fused_grad_ok(int64_t M, int64_t P, int64_t B) { return B <= 32 && small_rows(M, B) && P < ((int64_t)1 << 40); }
 
+namespace {
+constexpr int kGradRows = 2; // row tiles of 16 modes per workgroup
+int64_t grad_set_blocks(int64_t B) { return B <= 16 ? 1 : (B + 31) / 32; }
+
+// Point ranges of the gradient: six workgroups per CU (grad_kernel).
+int64_t grad_splits(int64_t M, int64_t P, int64_t B)
+{
+    const int64_t tiles = (M + 16 * kGradRows - 1) / (16 * kGradRows), nb = (P + 63) / 64;
+    const int64_t wanted = 6 * (int64_t)device_cus() / (tiles * grad_set_blocks(B));
+    return std::min((nb + kSlices - 1) / kSlices, std::max<int64_t>(1, wanted));
+}
+} // namespace
+
+size_t fused_grad_bytes(int64_t M, int64_t P, int64_t B)
+{
+    if (M <= 0 || P <= 0 || B <= 0) return 0;
+    return 8 * (size_t)grad_splits(M, P, B) * (size_t)M * (size_t)B;
+}
+
 zp_status launch_fused_grad(const Plan &p, const double *r, const double *th, int64_t P, const double *wq,
                             const double *tr, const double *tt, const double *g_up, int64_t B, bool norm,
                             double *part, size_t part_bytes, double *out, hipStream_t s)
 {
     const int64_t M = (int64_t)p.n.size();
-    constexpr int R = 2;
+    constexpr int R = kGradRows;
     const int fn = B <= 16 ? 1 : 2;
-    const int64_t nsb = (B + 16 * fn - 1) / (16 * fn);
+    const int64_t nsb = grad_set_blocks(B);
     const int64_t tiles = (M + 16 * R - 1) / (16 * R);
     const int64_t nb = (P + 63) / 64;
-    int64_t S = std::min((nb + kSlices - 1) / kSlices, std::max<int64_t>(1, 6 * (int64_t)device_cus() / (tiles * nsb)));
-    S = std::min(S, std::max<int64_t>(1, (int64_t)(part_bytes / (8 * (size_t)M * (size_t)B))));
+    int64_t S = std::min(grad_splits(M, P, B), std::max<int64_t>(1, (int64_t)(part_bytes / (8 * (size_t)M * (size_t)B))));
     const int64_t batches = ((nb + S - 1) / S + kSlices - 1) / kSlices * kSlices;
     S = (nb + batches - 1) / batches;
     if (tiles * S * nsb > max_workgroups(kThreads)) return set_error(ZP_ERR_ARG, "too many modes for one launch");

@@ -242,6 +242,19 @@ int64_t chunk_for(int64_t M, int64_t P, int64_t B, int ct, bool fwd, bool bwd, b
     return std::min<int64_t>(lo * kPad, P);
 }
 
+// Whether no call of these sizes stores a basis, or has more than one chunk of
+// sets to add: the forward, the column dots and the gradients are all fused.
+// Such calls ask for the gradient's partial sums and the smallest chunked
+// workspace, which the checks want, not for planes that they never write: 2145
+// modes, 65 536 points, 1 to 32 sets 3.5 GB -> 64 MiB.  (What was asked for up to
+// kSmallRequest stays: a larger "full" than the minimum does no harm there.)
+constexpr size_t kSmallRequest = (size_t)64 << 20;
+bool all_fused(int64_t M, int64_t P, int64_t B, int ct)
+{
+    return ct == CT_F64 && fused_grad_ok(M, P, B) && fused_fwd_ok(M, B, true) && fused_dot_ok(M, B) &&
+           fused_dot_chunks(B) == 1;
+}
+
 // launch_fused_dot over chunks of points that one launch takes and whose
 // partial sums fit ws.
 zp_status fused_dot(const Plan &plan, const double *r, const double *th, int64_t P, const double *c, const double *u,
@@ -406,9 +419,10 @@ zp_status zp_series_workspace(int64_t M, int64_t P, int64_t B, int32_t prec, siz
     // Sized for the most demanding use: backward without a cache, or the
     // forward-mode derivative.
     const int64_t P1 = std::min<int64_t>(P, kPad);
+    const size_t least = std::max({WsLayout(M, P1, B, ct, true, true, false).total, JvpLayout(M, P1, B, ct).total, (size_t)256});
     *full_bytes = std::max({WsLayout(M, P, B, ct, true, true, false, false).total, JvpLayout(M, P, B, ct).total, (size_t)256});
-    if (min_bytes)
-        *min_bytes = std::max({WsLayout(M, P1, B, ct, true, true, false).total, JvpLayout(M, P1, B, ct).total, (size_t)256});
+    if (all_fused(M, P, B, ct)) *full_bytes = std::min(*full_bytes, std::max({least, fused_grad_bytes(M, P, B), kSmallRequest}));
+    if (min_bytes) *min_bytes = least;
     return ZP_OK;
 }
 
@@ -954,8 +968,10 @@ zp_status zp_series_bwd2_workspace(int64_t M, int64_t P, int64_t B, int32_t prec
     if (prec < ZP_FP64 || prec > ZP_BF16X3) return set_error(ZP_ERR_PREC, "unknown prec");
     const int ct = ct_of(prec);
     const int64_t P1 = std::min<int64_t>(P, kPad);
+    const size_t least = std::max({Bwd2Layout(M, P1, B, ct).total, JvpLayout(M, P1, B, ct).total, (size_t)256});
     *full_bytes = std::max({Bwd2Layout(M, P, B, ct, false).total, JvpLayout(M, P, B, ct).total, (size_t)256});
-    if (min_bytes) *min_bytes = std::max({Bwd2Layout(M, P1, B, ct).total, JvpLayout(M, P1, B, ct).total, (size_t)256});
+    if (all_fused(M, P, B, ct)) *full_bytes = std::min(*full_bytes, std::max({least, fused_grad_bytes(M, P, B), kSmallRequest}));
+    if (min_bytes) *min_bytes = least;
     return ZP_OK;
 }
 

@@ -115,8 +115,10 @@ zp_status launch_fused_dot(const Plan &p, const double *r, const double *th, int
 // out[k][b] = sum_p Z_k(p) w[p] g[p][b] (w nullable: 1), or with the
 // directional derivative along (tr, tt) in place of Z if either is given;
 // norm: divided by the integral of Z_k^2.  part: workspace of part_bytes for
-// the partial sums of point ranges (any size).
+// the partial sums of point ranges (any size; fused_grad_bytes for as many
+// ranges as are wanted).
 bool fused_grad_ok(int64_t M, int64_t P, int64_t B);
+size_t fused_grad_bytes(int64_t M, int64_t P, int64_t B);
 zp_status launch_fused_grad(const Plan &p, const double *r, const double *th, int64_t P, const double *w,
                             const double *tr, const double *tt, const double *g, int64_t B, bool norm, double *part,
                             size_t part_bytes, double *out, hipStream_t s);
