@@ -421,7 +421,8 @@ zp_status zp_series_workspace(int64_t M, int64_t P, int64_t B, int32_t prec, siz
     const int64_t P1 = std::min<int64_t>(P, kPad);
     const size_t least = std::max({WsLayout(M, P1, B, ct, true, true, false).total, JvpLayout(M, P1, B, ct).total, (size_t)256});
     *full_bytes = std::max({WsLayout(M, P, B, ct, true, true, false, false).total, JvpLayout(M, P, B, ct).total, (size_t)256});
-    if (all_fused(M, P, B, ct)) *full_bytes = std::min(*full_bytes, std::max({least, fused_grad_bytes(M, P, B), kSmallRequest}));
+    if (*full_bytes > kSmallRequest && all_fused(M, P, B, ct))
+        *full_bytes = std::min(*full_bytes, std::max({least, fused_grad_bytes(M, P, B), kSmallRequest}));
     if (min_bytes) *min_bytes = least;
     return ZP_OK;
 }
@@ -970,7 +971,8 @@ zp_status zp_series_bwd2_workspace(int64_t M, int64_t P, int64_t B, int32_t prec
     const int64_t P1 = std::min<int64_t>(P, kPad);
     const size_t least = std::max({Bwd2Layout(M, P1, B, ct).total, JvpLayout(M, P1, B, ct).total, (size_t)256});
     *full_bytes = std::max({Bwd2Layout(M, P, B, ct, false).total, JvpLayout(M, P, B, ct).total, (size_t)256});
-    if (all_fused(M, P, B, ct)) *full_bytes = std::min(*full_bytes, std::max({least, fused_grad_bytes(M, P, B), kSmallRequest}));
+    if (*full_bytes > kSmallRequest && all_fused(M, P, B, ct))
+        *full_bytes = std::min(*full_bytes, std::max({least, fused_grad_bytes(M, P, B), kSmallRequest}));
     if (min_bytes) *min_bytes = least;
     return ZP_OK;
 }
